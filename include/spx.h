@@ -277,7 +277,7 @@ int spx_autotune(spx_plan* plan, void* stream);
  * (both), the diffusive phase's refill threshold (a wave refills its dead lanes once at least
  * this many are dead), the ballistic phase's, and the diffusive phase's deferral threshold (a
  * wave tests the steps that left their clearance balls once at least this many lanes hold
- * one; default 8).  Any pointer may be NULL. */
+ * one and their wait is worth a test pass; default 8).  Any pointer may be NULL. */
 int spx_get_launch(const spx_plan* plan, int32_t* blocks, int32_t* threads, int32_t* refill_min,
                    int32_t* refill_ballistic, int32_t* defer_min);
 /* Override them: threads a multiple of 64 in [64, 1024], thresholds in [1, 64]; blocks <= 0

@@ -565,10 +565,8 @@ __device__ __forceinline__ void collide(const SegDev<R>& s, const TabDev<R>& tb,
 // step -lam_th ln(RN) is formed as -(lam_th ln 2) log2(RN) with lam_l2 = lam_th ln 2, and
 // sin^2 = 1 - mu^2 with one fused multiply-add (exact product, one rounding).
 template <typename R>
-__device__ __forceinline__ R diffusive_draw(R lam_l2, const uint32_t* k, R* d)
+__device__ __forceinline__ R diffusive_direction(R lam_l2, R u0, R mu, R u2, R* d)
 {
-    const R u0 = u21<R>(k[0]), u2 = u21<R>(k[2]);
-    const R mu = sym21<R>(k[1]);       // 2 u1 - 1
     const R st = m_sqrt(fma(-mu, mu, (R)1));
     R sp, cp;
     m_sincos2pi(u2, &sp, &cp);
@@ -576,6 +574,32 @@ __device__ __forceinline__ R diffusive_draw(R lam_l2, const uint32_t* k, R* d)
     d[1] = st * sp;
     d[2] = mu;
     return -lam_l2 * m_log2(u0);
+}
+template <typename R>
+__device__ __forceinline__ R diffusive_draw(R lam_l2, const uint32_t* k, R* d)
+{
+    return diffusive_direction(lam_l2, u21<R>(k[0]), sym21<R>(k[1]), u21<R>(k[2]), d);
+}
+// The same draw in FP32 straight from the block: v_alignbit puts the top 21 bits k of a word under
+// the exponent of 2^23, which makes the float 2^23 + k in one instruction instead of a shift and a
+// conversion, and the multiply-add that scales it takes the 2^23 off again (its constants and
+// results fit the significand, so the values are u21 and sym21 exactly).  An odd step's codes are
+// first aligned to the top of a word: 11 bits of word i, then 10 of word w.
+__device__ __forceinline__ float code_float(uint32_t top)
+{
+    return __uint_as_float(__builtin_amdgcn_alignbit(0x4B000000u >> 21, top, 11));
+}
+__device__ __forceinline__ float diffusive_draw32(float lam_l2, uint4 w, bool odd, float* d)
+{
+    if (odd) {
+        w.x = __builtin_amdgcn_alignbit(w.x, w.w << 22, 11);
+        w.y = __builtin_amdgcn_alignbit(w.y, w.w << 12, 11);
+        w.z = __builtin_amdgcn_alignbit(w.z, w.w << 2, 11);
+    }
+    const float u0 = __builtin_fmaf(code_float(w.x), 0x1p-21f, 0x1p-21f - 4.f);
+    const float mu = __builtin_fmaf(code_float(w.y), 0x1p-20f, 0x1p-20f - 9.f);
+    const float u2 = __builtin_fmaf(code_float(w.z), 0x1p-21f, 0x1p-21f - 4.f);
+    return diffusive_direction(lam_l2, u0, mu, u2, d);
 }
 
 // Compensated (Kahan) accumulation: the position is s - c with c the rounding lost so far,
@@ -714,6 +738,8 @@ __device__ __forceinline__ void compensated_step(float* x, float* xc, float ell,
 // Slack between the clearance and the ball radius [mm]: far above the FP32 rounding of the
 // position and of the surface test at chamber sizes up to metres.
 constexpr float CLEAR_MARGIN = 0.02f;
+// Rounds of two steps a wave takes at most between its checks for held steps and ended walks.
+constexpr int WALK_ADVANCES = 64;
 
 // A diffusive step of the batched FP32 path (event p.e + 1).  p.r2 is the squared radius of
 // a clearance ball around p.x: the clearance of p.x less CLEAR_MARGIN.  A step that ends
@@ -722,55 +748,105 @@ constexpr float CLEAR_MARGIN = 0.02f;
 // is added to the offset.  Otherwise the step is tested as usual and, if it ends in the gas,
 // the ball is rebuilt around its end.  Outcome and arithmetic are those of the tested step.
 //
-// Such a step is taken in two halves, so that a wave can defer its surface tests.
-// diffusive_advance takes the next steps while they stay in the clearance ball: both steps
-// of the current Philox block (one if the next event is odd).  A step that leaves the ball
-// is held (direction in p.d, length in p.r2: the ball is rebuilt after the test anyway) and
-// sets held.  diffusive_resolve tests a held step and finishes it.  The advance needs only
-// two numbers of the particle's segment (its thermal mean free path and the Philox counter
-// word), passed per lane, so lanes of different segments advance together; the test needs
-// the segment's geometry.
+// Such a step is taken in two halves, so that a wave can defer its surface tests.  A step that
+// leaves its clearance ball is held (direction in p.d, length in p.r2: the ball is rebuilt after
+// the test anyway); diffusive_resolve tests a held step and finishes it.  A step needs only two
+// numbers of the particle's segment (its thermal mean free path and the Philox counter word),
+// kept per lane, so lanes of different segments walk together; the test needs the segment's
+// geometry.  In this walk p.ndiff holds the events taken before the walk: every later event but
+// the last one of a history that ends on a surface is a step that ended in the gas.
 //
-// One diffusive sub-step from block w (the odd or the even half) for a lane where `active`:
-// every lane draws and forms the move; the commit and the hold are written under the lanes'
-// masks, so inactive lanes keep their state.
-__device__ __forceinline__ void diffusive_substep(float lam_l2, uint4 w, bool odd, bool active, Particle<float>& p,
-                                                  bool& held)
+// One diffusive step from block w (its odd or its even half) from offset `from`: leaves the step in
+// dir, ell and the offset it reaches in `to`, and returns whether that stays in the ball.
+__device__ __forceinline__ bool diffusive_substep(float lam_l2, uint4 w, bool odd, float r2, const float* from,
+                                                  float* to, float* dir, float& ell)
 {
-    uint32_t k[3];
-    diffusive_codes(w, odd, k);
-    float dir[3];
-    const float ell = diffusive_draw(lam_l2, k, dir);   // diffusive only after a gas collision
-    float t[3];
-    offset_try(p.xc, ell, dir, t);
-    const bool ok = offset_holds(t, p.r2);
-    const bool commit = active && ok, hold = active && !ok;
-    // the writes under the lanes' masks (cheaper than selecting between old and new values)
-    if (commit) {
+    ell = diffusive_draw32(lam_l2, w, odd, dir);   // diffusive only after a gas collision
+    offset_try(from, ell, dir, to);
+    return offset_holds(to, r2);
+}
+
+// One step of a lane near its event cap: the step of event p.e + 1 (its block drawn for this one
+// step).  Returns whether the step left the ball and is held.
+__device__ __forceinline__ bool diffusive_single(float lam_l2, uint32_t cfgcat, uint32_t k0, uint32_t k1,
+                                                 uint32_t pid, Particle<float>& p)
+{
+    ++p.e;
+    const uint4 w = diffusive_block(pid, p.e, cfgcat, k0, k1);
+    float dir[3], t[3], ell;
+    if (diffusive_substep(lam_l2, w, (p.e & 1u) != 0, p.r2, p.xc, t, dir, ell)) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) p.xc[i] = t[i];
-        ++p.ndiff;
-        ++p.e;
+        return false;
     }
-    if (hold) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) p.d[i] = dir[i];
+    p.r2 = ell;
+    return true;
+}
+
+// Steps of the lanes that enter (A of them, none held, each at least 2 WALK_ADVANCES + 1 events
+// below its cap) until those that hold a step have waited long enough.  Returns whether the lane
+// holds a step (in p.d, p.r2).
+//
+// Bound by VALU issue: every instruction of a wave takes four clocks of its SIMD (a transcendental
+// eight; a 32x32->64 multiply-add four, as an addition), so the round below (both steps of a Philox
+// block) is written for its instruction count, 83 against 113 in a form that selected, committed and
+// counted each step apart.  A lane leaves the loop with the step that leaves its ball, so its
+// registers keep offset, direction and length without a copy; the even step goes from p.xc to b, the
+// odd one from b back to p.xc; the events are counted in steps of two.  A lane whose next event is
+// odd takes only that step first.
+//
+// When to test the held steps: a test pass costs the wave the same for few and many held steps, a
+// lane that waits costs its share of every round, so the mean cost of a hold is least when the
+// rounds idled (summed over the lanes) are worth one pass: idle_max.  defer_min is a lower bound on
+// the lanes that hold.  A fixed seven rounds between checks and a test at defer_min held steps took
+// 39.1 ms of diffusive kernel on 3 x 1e7 atoms at 0.5 / 0 / 2 Pa, this form 32.4 ms; 3.65 and
+// 3.35 ms on four cathodes.
+__device__ __forceinline__ bool walk_group(float lam_l2, uint32_t cfgcat, uint32_t k0, uint32_t k1, uint32_t pid,
+                                           int A, int defer_min, int idle_max, Particle<float>& p)
+{
+    float dir[3], b[3], ell;
+    bool held = true, odd = true;           // odd: the last step taken or held is the odd one of its block
+    uint32_t e = (p.e + 1) & ~1u;           // the even event of the block
+    uint4 w = diffusive_block(pid, e, cfgcat, k0, k1);
+    bool in = true;
+    if (p.e & 1u) {
+        in = odd = diffusive_substep(lam_l2, w, false, p.r2, p.xc, b, dir, ell);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) b[i] = p.xc[i];
+    }
+    if (in) in = diffusive_substep(lam_l2, w, true, p.r2, b, p.xc, dir, ell);
+    if (in) {
+        int idle = 0, n = 1;
+        for (;;) {
+            const int out = A - __popcll(__ballot(true));
+            idle += out;
+            if (++n > WALK_ADVANCES || (idle >= idle_max && out >= defer_min)) {
+                held = false;
+                break;
+            }
+            e += 2;
+            w = philox4x32_10(make_uint4(pid, e, cfgcat, 2u), k0, k1);
+            if (!diffusive_substep(lam_l2, w, false, p.r2, p.xc, b, dir, ell)) {
+                odd = false;
+                break;
+            }
+            if (!diffusive_substep(lam_l2, w, true, p.r2, b, p.xc, dir, ell)) break;
+        }
+    }
+    p.e = e + (odd ? 1u : 0u);
+    if (held) {
+        if (odd) {                          // the offset before the odd step
+#pragma unroll
+            for (int i = 0; i < 3; ++i) p.xc[i] = b[i];
+        }
 #pragma unroll
         for (int i = 0; i < 3; ++i) p.d[i] = dir[i];
         p.r2 = ell;
-        ++p.e;
     }
-    held = held || hold;
-}
-
-__device__ __forceinline__ Term diffusive_advance(float lam_l2, uint32_t cfgcat, uint32_t k0, uint32_t k1,
-                                                  uint32_t pid, uint32_t cap, Particle<float>& p, bool& held)
-{
-    if (p.e >= cap) return Term{HIT_ESCAPED, -1, 0.f};
-    const uint4 w = diffusive_block(pid, p.e + 1, cfgcat, k0, k1);
-    // the even step of the block (if the next event is even), then its odd step unless the
-    // even one is held or the cap is reached (a capped history escapes at its next step)
-    diffusive_substep(lam_l2, w, false, ((p.e + 1) & 1u) == 0, p, held);
-    diffusive_substep(lam_l2, w, true, !held && p.e < cap, p, held);
-    return Term{HIT_NONE, -1, 0.f};
+    return held;
 }
 
 __device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& s, Particle<float>& p)
@@ -787,7 +863,6 @@ __device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& s, Partic
     }
     if (!(ell < m_inf<float>())) return Term{HIT_ESCAPED, -1, 0.f};
     compensated_step(p.x, p.xc, ell, dir);
-    ++p.ndiff;
     const float c = clearance(s, p.x) - CLEAR_MARGIN;
     p.r2 = c > 0.f ? c * c : -1.f;
     return Term{HIT_NONE, -1, 0.f};
@@ -897,7 +972,6 @@ __device__ __forceinline__ void coop_walk(uint32_t k0, uint32_t k1, uint32_t cap
 #pragma unroll
             for (int i = 0; i < 3; ++i) p.xc[i] = nx[i];
             p.e += (uint32_t)f;
-            p.ndiff += (uint32_t)f;
             if (hold) {
 #pragma unroll
                 for (int i = 0; i < 3; ++i) p.d[i] = hd[i];

@@ -90,7 +90,8 @@ struct TransportArgs {
     int32_t n_seg;
     int32_t refill_min;         // diffusive phase: refill a wave's dead lanes once at least this many
     int32_t refill_ballistic;   // ballistic phase: the same threshold
-    int32_t defer_min;          // diffusive phase: held steps that trigger a wave's surface tests
+    int32_t defer_min;          // diffusive phase: held steps a wave's surface tests wait for at least
+    int32_t walk_idle;          // diffusive phase: ... and the idle rounds of the lanes that hold them
     uint32_t chunk_ballistic;   // ballistic phase: tickets a wave claims per atomic
     uint32_t n_bins;            // tally bins of the plan
     int32_t lds_counters;       // per-segment counters privatised in LDS
@@ -128,9 +129,11 @@ constexpr uint64_t TICKET_CHUNK = 128;       // queued atoms a diffusive wave cl
 // counter; the chunk of a round is also kept small enough for every wave to take several
 constexpr uint64_t TICKET_CHUNK_BALLISTIC_MAX = 512;
 constexpr int DEFER_MIN = 8;                  // default: held diffusive steps that trigger a wave's surface tests
-// advances (two diffusive steps each) a wave takes between its checks for held steps, dead
-// lanes and the end of the walk; the checks (ballots, branches) then cost little per step
-constexpr int ADVANCES_PER_CHECK = 7;
+// Idle rounds of held lanes (summed over the lanes) that one pass of the surface tests is worth
+// without absorbing objects.  Diffusive kernel, single target / four cathodes / half the 64-chamber
+// sweep: 34.5 / 3.46 / 85.7 ms at 64, 33.9 / 3.37 / 84.0 at 128, 34.1 / 3.46 / 84.4 at 192, 35.9 /
+// 3.82 / 88.4 at 400.
+constexpr int WALK_IDLE = 128;
 constexpr int COOP_MAX = 8;                   // drained waves with at most this many live lanes walk cooperatively
 constexpr size_t LDS_TALLY_MAX = 49152;      // bytes: up to 12288 bins
 constexpr size_t LDS_ARRIVALS_MAX = 4096;     // bytes: arrival histograms of up to 6 segments

@@ -305,6 +305,7 @@ __device__ __forceinline__ void escape_capped(const TransportArgs& a, const Bloc
         R &= ~__ballot(mine);
         if (mine) {
             capped = false;
+            p.ndiff = p.e - p.ndiff;
             terminate<ARR>(a, bt, segs[sL], pid, p, Term{HIT_ESCAPED, -1, 0.f}, acc);
         }
     }
@@ -315,57 +316,61 @@ __device__ __forceinline__ void escape_capped(const TransportArgs& a, const Bloc
 template <bool ARR>
 __device__ __forceinline__ void resolve_held(const TransportArgs& a, const BlockTally& bt,
                                              const SegDev<float>* __restrict__ segs, int seg, uint32_t pid,
-                                             Particle<float>& p, LaneAcc& acc, bool& held, uint64_t H)
+                                             Particle<float>& p, LaneAcc& acc, bool held, uint64_t H)
 {
     const int sL = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)H) - 1);
     acc.c[C_TESTED] += held ? 1u : 0u;
     if (__ballot(held && seg != sL) == 0) {
         if (held) {
-            held = false;
             const SegDev<float>& S = segs[sL];
             const Term t = diffusive_resolve(S, p);
-            if (t.state != HIT_NONE) terminate<ARR>(a, bt, S, pid, p, t, acc);
+            if (t.state != HIT_NONE) {
+                p.ndiff = p.e - p.ndiff - 1u;
+                terminate<ARR>(a, bt, S, pid, p, t, acc);
+            }
         }
     } else if (held) {
-        held = false;
         const SegDev<float>& S = segs[seg];
         const Term t = diffusive_resolve(S, p);
-        if (t.state != HIT_NONE) terminate<ARR>(a, bt, S, pid, p, t, acc);
+        if (t.state != HIT_NONE) {
+            p.ndiff = p.e - p.ndiff - 1u;
+            terminate<ARR>(a, bt, S, pid, p, t, acc);
+        }
     }
 }
 
-// Diffusive steps of the lanes in segment S with deferred surface tests: a lane whose
-// step leaves its clearance ball holds the step and idles until at least a.defer_min lanes
-// hold one (or every diffusive lane does, or the loop is about to end); then the held
-// steps are tested together, so the long test runs in few iterations.  No step is held
-// when the loop returns.
+// Diffusive steps of the wave's walkers with deferred surface tests: groups of steps (walk_group),
+// the steps that left their balls tested together after each.  Walkers within a group's length of
+// the event cap are rare: while the wave has one, it takes single steps.  Returns when the wave
+// should refill, has no walker left, or walks its last ones cooperatively; no step is held then.
 template <bool ARR>
 __device__ __forceinline__ void diffusive_loop(const TransportArgs& a, const BlockTally& bt,
                                                const SegDev<float>* __restrict__ segs, int seg, float lam_l2,
                                                uint32_t cfgcat, uint32_t pid, Particle<float>& p, LaneAcc& acc,
                                                bool drained)
 {
-    bool held = false;
+    constexpr uint32_t REACH = 2 * WALK_ADVANCES + 1;     // events a group takes at most
+    const uint32_t far = a.cap > REACH ? a.cap - REACH : 0u;
+    uint64_t M = __ballot(p.st == ST_DIFFUSIVE);
     for (;;) {
-        // several advances (two steps each) between the wave's checks below: a lane that holds
-        // a step, or reaches the cap, sits out the rest of them
-        bool capped = false;
-#pragma unroll
-        for (int rep = 0; rep < ADVANCES_PER_CHECK; ++rep)
-            if (p.st == ST_DIFFUSIVE && !held && !capped)
-                capped = diffusive_advance(lam_l2, cfgcat, a.k0, a.k1, pid, a.cap, p, held).state != HIT_NONE;
-        escape_capped<ARR>(a, bt, segs, seg, pid, p, acc, capped);
-        const uint64_t H = __ballot(held);
-        const uint64_t M = __ballot(p.st == ST_DIFFUSIVE);
-        bool stop = M == 0 || (!drained && __popcll(__ballot(p.st == ST_DEAD)) >= a.refill_min) ||
-                    (drained && __popcll(M) <= COOP_MAX);
-        if (H != 0 && (stop || H == M || __popcll(H) >= a.defer_min)) {
-            resolve_held<ARR>(a, bt, segs, seg, pid, p, acc, held, H);
-            const uint64_t M2 = __ballot(p.st == ST_DIFFUSIVE);
-            stop = M2 == 0 || (!drained && __popcll(__ballot(p.st == ST_DEAD)) >= a.refill_min) ||
-                   (drained && __popcll(M2) <= COOP_MAX);
+        bool held = false;
+        if (__ballot(p.st == ST_DIFFUSIVE && p.e >= far) == 0) {
+            if (p.st == ST_DIFFUSIVE) {
+                const int A = __popcll(M);
+                held = walk_group(lam_l2, cfgcat, a.k0, a.k1, pid, A, a.defer_min < A ? a.defer_min : A, a.walk_idle,
+                                  p);
+            }
+        } else {
+            const bool walks = p.st == ST_DIFFUSIVE;
+            escape_capped<ARR>(a, bt, segs, seg, pid, p, acc, walks && p.e >= a.cap);
+            if (p.st == ST_DIFFUSIVE) held = diffusive_single(lam_l2, cfgcat, a.k0, a.k1, pid, p);
         }
-        if (stop) break;
+        const uint64_t H = __ballot(held);
+        if (H != 0) resolve_held<ARR>(a, bt, segs, seg, pid, p, acc, held, H);
+        M = __ballot(p.st == ST_DIFFUSIVE);
+        if (M == 0 || (!drained && __popcll(__ballot(p.st == ST_DEAD)) >= a.refill_min) ||
+            (drained && __popcll(M) <= COOP_MAX))
+            break;
     }
 }
 
@@ -484,7 +489,7 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs& a, const SegDev<f
                 }
                 p.E = r.E;
                 p.e = r.e;
-                p.ndiff = 0;
+                p.ndiff = r.e;         // events before the walk
                 p.ncoll = 0;
                 p.r2 = -1.f;           // no clearance ball yet: the first step is tested
                 p.st = ST_DIFFUSIVE;
@@ -747,6 +752,12 @@ int build_transport32(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* 
     a.refill_min = sh.refill_min;
     a.refill_ballistic = sh.refill_ballistic;
     a.defer_min = sh.defer_min;
+    // a pass of the surface tests takes about 180 instructions, and 70 more per absorbing object of
+    // the segment (its test and its clearance): the idle rounds it is worth grow with it (four cathodes
+    // in chimneys, seven objects a run: diffusive kernel 2.87 ms at 128 idle rounds, 2.66 at 400)
+    size_t n_obj = 0;
+    for (const auto& s : P->seg) n_obj += s.objs.size();
+    a.walk_idle = WALK_IDLE + (int32_t)(WALK_IDLE * 70 * n_obj / (180 * (size_t)P->n_seg));
     a.n_bins = (uint32_t)P->n_bins_total;
     bool lc, lt, la;
     const size_t smem = transport32_lds(P, o.arr_E != nullptr, &lc, &lt, &la);
