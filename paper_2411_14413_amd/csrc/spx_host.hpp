@@ -88,6 +88,7 @@ struct TransportArgs {
     uint32_t k0, k1;            // Philox key (seed words)
     uint32_t cap;
     int32_t n_seg;
+    int32_t n_simd;             // SIMDs of the device
     int32_t refill_min;         // diffusive phase: refill a wave's dead lanes once at least this many
     int32_t refill_ballistic;   // ballistic phase: the same threshold
     int32_t defer_min;          // diffusive phase: held steps a wave's surface tests wait for at least
@@ -123,7 +124,8 @@ constexpr uint64_t QUEUE_SLACK_WAVES = 8192;  // waves that may leave slots unus
 constexpr size_t LDS_COUNTERS_MAX = 16384;   // bytes: up to 256 segments
 constexpr int RT_MAX_NODES = 256;             // nodes of a measured racetrack profile
 constexpr int OBJ_MAX_SEG = 32;               // absorbing objects of one (config, cathode) run
-constexpr uint64_t TICKET_CHUNK = 128;       // queued atoms a diffusive wave claims per global atomic
+constexpr uint64_t TICKET_CHUNK = 128;       // queued atoms a diffusive wave claims per global atomic, at most
+constexpr uint64_t TICKET_CHUNK_MIN = 8;     // tickets of either phase a wave claims per global atomic, at least
 // launch tickets a ballistic wave claims per global atomic, at most: ballistic histories are
 // short, so their waves come back for tickets often and small chunks queue them on the one
 // counter; the chunk of a round is also kept small enough for every wave to take several

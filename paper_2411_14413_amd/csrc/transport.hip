@@ -117,6 +117,18 @@ __device__ __forceinline__ void terminate(const TransportArgs& a, const BlockTal
     p.st = ST_DEAD;
 }
 
+// Tickets a wave claims at once out of `total`: at most `most`, in a small run the share of one SIMD.
+// There the phase lasts as long as its longest histories, which step fastest alone on a SIMD: with
+// 128 tickets a claim, 1e4 atoms (one target, 0.5 Pa) ran on 80 waves of 1024 SIMDs' (0.147 +
+// 0.392 ms ballistic + diffusive; a SIMD's share: 0.126 + 0.265), 1e5 in 0.156 + 0.453 (0.153 +
+// 0.411).  Sharing among two or four times as many waves: 0.130 + 0.298 and 0.130 + 0.319; 0.159 +
+// 0.430 and 0.202 + 0.481.
+__host__ __device__ __forceinline__ uint64_t chunk_of(uint64_t total, int n_simd, uint64_t most)
+{
+    const uint64_t share = (total + (uint64_t)n_simd - 1) / (uint64_t)n_simd;
+    return share < TICKET_CHUNK_MIN ? TICKET_CHUNK_MIN : share < most ? share : most;
+}
+
 // Number of set bits of the wave-wide mask m in the lanes below this one (mbcnt).
 __device__ __forceinline__ uint64_t lanes_below(uint64_t m)
 {
@@ -464,6 +476,7 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs& a, const SegDev<f
     BlockTally bt;
     lds_setup(a, bt, lds);
     const uint64_t total = a.qstate[QS_QUEUE];   // written by the ballistic phase of this round
+    const uint64_t chunk = chunk_of(total, a.n_simd, TICKET_CHUNK);
     const int lane = threadIdx.x & 63;
     Particle<float> p;
     p.st = ST_DEAD;
@@ -478,7 +491,7 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs& a, const SegDev<f
         const uint64_t dead = __ballot(p.st == ST_DEAD);
         const int n_dead = __popcll(dead);
         if (!T.drained && n_dead > 0 && (n_dead >= a.refill_min || n_dead == 64)) {
-            const uint64_t my = claim(T, &a.qstate[QS_DIFFUSIVE], TICKET_CHUNK, total, dead, lane);
+            const uint64_t my = claim(T, &a.qstate[QS_DIFFUSIVE], chunk, total, dead, lane);
             const uint32_t qpid = my != ~0ull ? a.queue[my].pid : 0xFFFFFFFFu;
             if (qpid != 0xFFFFFFFFu) {                 // empty slots (left unused by a wave) are skipped
                 const ThermRec r = a.queue[my];
@@ -749,6 +762,7 @@ int build_transport32(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* 
     a.k1 = (uint32_t)(seed >> 32);
     a.cap = P->params.event_cap;
     a.n_seg = P->n_seg;
+    a.n_simd = 4 * P->n_cu;
     a.refill_min = sh.refill_min;
     a.refill_ballistic = sh.refill_ballistic;
     a.defer_min = sh.defer_min;
@@ -786,6 +800,7 @@ int build_transport32(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* 
         // still gives every wave about four chunks of the round
         uint64_t cb = TICKET_CHUNK;
         while (2 * cb <= TICKET_CHUNK_BALLISTIC_MAX && 2 * cb * 4 * waves <= a.total) cb *= 2;
+        cb = chunk_of(a.total, a.n_simd, cb);
         a.chunk_ballistic = (uint32_t)cb;
         KLaunch reset;
         reset.func = (const void*)k_round_reset;
