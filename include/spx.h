@@ -67,7 +67,7 @@ extern "C" {
 #define SPX_C_THERMALIZED 6     /* particles that reached the diffusive (thermalised) state */
 #define SPX_C_TESTED 7          /* diffusive steps tested against the surfaces: a work counter, not a
                                    result (the batched FP32 walk tests only the steps that leave their
-                                   clearance balls; the plain FP64 path tests every step) */
+                                   clearance balls; the FP64 path counts every step) */
 #define SPX_N_COUNTERS 8
 
 /* Magnetron cathode: planar circular target (Methods, "The SIMTRA Python wrapper": the
@@ -154,7 +154,7 @@ typedef struct spx_params {
     double E_th_kT;              /* thermalisation threshold in units of k_B T (3) */
     uint32_t event_cap;          /* flights per particle before ESCAPED (2^20) */
     int32_t table_ne, table_ns;  /* scattering-table nodes in log10(eps) and b/b_max (256, 257) */
-    int32_t precision;           /* 32: batched FP32 transport; 64: plain FP64 per-segment comparator */
+    int32_t precision;           /* 32: FP32 transport; 64: FP64 transport */
     double log_eps_lo, log_eps_hi; /* table range of log10(eps) (-10, 0) */
 } spx_params;
 
@@ -226,7 +226,8 @@ int spx_plan_layout(const spx_plan* plan, uint64_t* h_bin_off, uint64_t* h_first
  *   d_records   spx_record[n_particles_total]; nullable
  * precision 32 runs the whole plan as one persistent launch (replayed from a HIP
  * graph built on the first run and updated in place for new seeds and buffers);
- * precision 64 runs one plain FP64 launch per segment.  Asynchronous. */
+ * precision 64 enqueues the same two phases in FP64 (every position, energy and decision in
+ * double) on `stream`, without a graph.  Asynchronous. */
 int spx_run(spx_plan* plan, uint64_t seed, uint64_t* d_counts, uint64_t* d_counters,
             double* d_profiles, spx_record* d_records, void* stream);
 
@@ -260,7 +261,7 @@ int spx_run_ex(spx_plan* plan, uint64_t seed, const spx_outputs* out, void* stre
 int spx_run_noalloc(spx_plan* plan, uint64_t seed, const spx_outputs* out, void* stream);
 
 /* Bin edges of the arrival tallies as the kernels use them: energy edges [61] (eV) and the
- * cosines of the angle edges [91], in double (plain FP64 path) and float (batched FP32 path;
+ * cosines of the angle edges [91], in double (FP64 path) and float (FP32 path;
  * the double values rounded).  Any pointer may be NULL. */
 int spx_arrival_edges(double* h_energy_edges, double* h_cos_edges, float* h_energy_edges32, float* h_cos_edges32);
 

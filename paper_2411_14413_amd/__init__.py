@@ -67,8 +67,8 @@ class Plan:
     pressure, T, gas_mass, gas_Z, gas_motion), ``grid`` (center, normal, u_axis,
     half_u, half_v, shape, nu, nv) and ``cathodes`` (each: center, normal, u_axis,
     radius, rt_mu, rt_sigma, rt_lo, rt_hi, U_s, E_i, k_cut, mass, Z, cos_coeff,
-    n_particles, optionally rt_profile: [(r, depth), ...] of a measured racetrack).  ``precision`` 32 = batched FP32 transport (one persistent
-    launch), 64 = plain FP64 comparator (one launch per segment).
+    n_particles, optionally rt_profile: [(r, depth), ...] of a measured racetrack).  ``precision`` 32 = FP32 transport (replayed from a HIP
+    graph), 64 = the same two phases in FP64.
     """
 
     def __init__(self, configs: Sequence, params=None, precision: int = 32):

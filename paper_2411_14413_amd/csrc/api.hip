@@ -607,18 +607,23 @@ static int create(const spx_config* cfgs, int n_cfgs, const spx_params* prm, Pla
     std::vector<uint64_t> tfirst(n + 1, 0);
     for (int o = 0; o < n; ++o) tfirst[o + 1] = tfirst[o] + P->seg[order[o]].N;
     P->n_tickets = tfirst[n];
-    if (prm->precision == 32) {
-        // thermalisation queue of one round of the batched path (48 B per ticket of a round)
-        // thermalised atoms of a round, plus the slots a resident wave may leave unused
-        const uint64_t r = rounds_of(P->n_tickets);
-        const uint64_t waves = std::max<uint64_t>(QUEUE_SLACK_WAVES, (uint64_t)P->n_cu * 32);
+    // thermalisation queue of one round: an atom per ticket of a round (FP32 48 B, FP64 80 B), plus the
+    // slots a resident wave may leave unused
+    const size_t rec = prm->precision == 32 ? sizeof(ThermRec<float>) : sizeof(ThermRec<double>);
+    const uint64_t waves = std::max<uint64_t>(QUEUE_SLACK_WAVES, (uint64_t)P->n_cu * 32);
+    P->round_max = prm->precision == 32 ? ROUND_MAX : ROUND_MAX64;
+    for (;;) {
+        const uint64_t r = rounds_of(P->n_tickets, P->round_max);
         P->queue_cap = (r ? (P->n_tickets + r - 1) / r : 0) + waves * QUEUE_CHUNK;
-        if (dalloc(&P->d_queue, P->queue_cap) != SPX_OK) {
-            set_error("hipMalloc of the thermalisation queue (" + std::to_string(P->queue_cap * sizeof(ThermRec)) +
-                      " bytes) failed");
-            release(P);
-            return SPX_ENOMEM;
+        if (dalloc(&P->d_queue, P->queue_cap * rec) == SPX_OK) break;
+        (void)hipGetLastError();
+        if (prm->precision == 64 && P->round_max > ROUND_MIN64) {
+            P->round_max /= 2;
+            continue;
         }
+        set_error("hipMalloc of the thermalisation queue (" + std::to_string(P->queue_cap * rec) + " bytes) failed");
+        release(P);
+        return SPX_ENOMEM;
     }
     std::vector<uint64_t> bo(P->h_bin_off);
     bo.push_back(P->n_bins_total);
@@ -644,6 +649,10 @@ static int create(const spx_config* cfgs, int n_cfgs, const spx_params* prm, Pla
     P->max_blocks_per_cu = bpc;
     P->blocks = bpc * P->n_cu;
     P->blocks_diff = std::min(P->blocks, bpc_d * P->n_cu);
+    if (prm->precision == 64 && shape_transport64(P) != SPX_OK) {
+        release(P);
+        return SPX_EDEVICE;
+    }
     *out = P;
     return SPX_OK;
 }
@@ -749,26 +758,24 @@ static int run(Plan* P, uint64_t seed, const Outputs& o, hipStream_t st)
     const bool capturing = cs != hipStreamCaptureStatusNone;
     // runs on other streams share the plan's queue and counters: wait for the last one
     if (P->done_recorded && !capturing) SPX_HIP(hipStreamWaitEvent(st, P->done_event, 0));
+    QueueMem q;
+    q.queue = P->d_queue;
+    q.cap = P->queue_cap;
+    q.qstate = P->d_qstate;
+    q.round_max = P->round_max;
     if (P->params.precision == 64) {
-        SPX_TRY(launch_transport64(P, seed, o, st));
+        StreamSink ss(st, nullptr);
+        SPX_TRY(build_transport<double>(P, seed, o, P->d_tfirst, P->n_tickets, P->shape64, q, ss));
     } else if (capturing) {
         // inside a stream capture the kernels go straight onto the capturing stream, so that
         // they become nodes of the caller's graph (a launch of the plan's own graph would not be
         // recorded); the runs of the plan in that graph share its queue and are ordered by the
         // caller
-        QueueMem q;
-        q.queue = P->d_queue;
-        q.cap = P->queue_cap;
-        q.qstate = P->d_qstate;
         StreamSink ss(st, nullptr);
-        SPX_TRY(build_transport32(P, seed, o, P->d_tfirst, P->n_tickets, plan_shape(P), q, ss));
+        SPX_TRY(build_transport<float>(P, seed, o, P->d_tfirst, P->n_tickets, plan_shape(P), q, ss));
     } else {
-        QueueMem q;
-        q.queue = P->d_queue;
-        q.cap = P->queue_cap;
-        q.qstate = P->d_qstate;
         ListSink ls;
-        SPX_TRY(build_transport32(P, seed, o, P->d_tfirst, P->n_tickets, plan_shape(P), q, ls));
+        SPX_TRY(build_transport<float>(P, seed, o, P->d_tfirst, P->n_tickets, plan_shape(P), q, ls));
         bool same = P->graph_exec && ls.L.size() == P->graph_launches.size();
         for (size_t i = 0; same && i < ls.L.size(); ++i) same = ls.L[i].same_shape(P->graph_launches[i]);
         if (!same) {
@@ -872,7 +879,7 @@ static int autotune(Plan* P, hipStream_t st)
             q.cap = P->queue_cap;
             q.qstate = P->d_qstate;
             StreamSink ss(st, ev.data());
-            if (rc == SPX_OK) rc = build_transport32(P, 0x5eed, to, d_tf, tf[n], sh, q, ss);
+            if (rc == SPX_OK) rc = build_transport<float>(P, 0x5eed, to, d_tf, tf[n], sh, q, ss);
             if (rc == SPX_OK && hipEventSynchronize(ev.back()) != hipSuccess) rc = SPX_EDEVICE;
             float b = 0.f, d = 0.f;
             for (size_t r = 0; r + 2 < ev.size() && rc == SPX_OK; r += 3) {

@@ -83,13 +83,13 @@ extern "C" int spx_run_noalloc(spx_plan* P, uint64_t seed, const spx_outputs* ou
     const Shape sh = plan_shape(P);
     QueueMem q;
     q.qstate = (uint64_t*)base;
-    q.queue = (ThermRec*)((unsigned char*)base + SCRATCH_HEAD);
-    q.cap = (SCRATCH_BYTES - SCRATCH_HEAD) / sizeof(ThermRec);
+    q.queue = (unsigned char*)base + SCRATCH_HEAD;
+    q.cap = (SCRATCH_BYTES - SCRATCH_HEAD) / sizeof(ThermRec<float>);
     // every wave may leave one reserved run of queue slots unused in a round
     const uint64_t slack = (uint64_t)sh.blocks * (uint64_t)((sh.threads + 63) / 64) * QUEUE_CHUNK;
     if (slack >= q.cap) {
         set_error("spx_run_noalloc: the launch shape (" + std::to_string(sh.blocks) + " blocks of " +
-                  std::to_string(sh.threads) + " threads) needs " + std::to_string(slack * sizeof(ThermRec)) +
+                  std::to_string(sh.threads) + " threads) needs " + std::to_string(slack * sizeof(ThermRec<float>)) +
                   " bytes of queue slack, more than the " + std::to_string(SCRATCH_BYTES) + "-byte scratch array holds");
         return SPX_EINVAL;
     }
@@ -103,5 +103,5 @@ extern "C" int spx_run_noalloc(spx_plan* P, uint64_t seed, const spx_outputs* ou
     o.arr_A = out->arrival_angle;
     o.esum = out->energy_sum;
     StreamSink sink((hipStream_t)stream, nullptr);
-    return build_transport32(P, seed, o, P->d_tfirst, P->n_tickets, sh, q, sink);
+    return build_transport<float>(P, seed, o, P->d_tfirst, P->n_tickets, sh, q, sink);
 }

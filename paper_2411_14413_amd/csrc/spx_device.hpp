@@ -1,6 +1,6 @@
 // spx_device.hpp -- device-side data layout and the per-event physics of the
 // sputtered-atom transport, written once for R = float (batched transport) and
-// R = double (plain comparator).
+// R = double (reference precision).
 //
 // Method (Thelen et al., arXiv 2411.14413, Methods, "The SIMTRA model" and the
 // calculation paragraph that closes Methods): launch from the racetrack with a
@@ -14,12 +14,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace spx {
 
 enum : int { ST_DEAD = 0, ST_BALLISTIC = 1, ST_DIFFUSIVE = 2 };
 enum : int { HIT_NONE = 0, HIT_DEPOSITED = 1, HIT_WALL = 2, HIT_ESCAPED = 3 };
 // C_TESTED: diffusive steps tested against the surfaces (a work counter: the batched walk tests
-// only the steps that leave their clearance balls, the plain comparator every step)
+// only the steps that leave their clearance balls; the FP64 path counts every step)
 enum : int { C_LAUNCHED = 0, C_DEPOSITED, C_WALL, C_ESCAPED, C_COLLISIONS, C_DIFFUSIVE, C_THERMALIZED, C_TESTED, N_COUNTERS };
 
 // --------------------------------------------------------------------------
@@ -589,16 +591,21 @@ __device__ __forceinline__ float code_float(uint32_t top)
 {
     return __uint_as_float(__builtin_amdgcn_alignbit(0x4B000000u >> 21, top, 11));
 }
-__device__ __forceinline__ float diffusive_draw32(float lam_l2, uint4 w, bool odd, float* d)
+// What the draw adds: the caller of a loop keeps these in registers.
+struct DrawConst {
+    float u = 0x1p-21f - 4.f, mu = 0x1p-20f - 9.f;
+};
+__device__ __forceinline__ float diffusive_draw32(float lam_l2, uint4 w, bool odd, float* d,
+                                                  const DrawConst& c = DrawConst())
 {
     if (odd) {
         w.x = __builtin_amdgcn_alignbit(w.x, w.w << 22, 11);
         w.y = __builtin_amdgcn_alignbit(w.y, w.w << 12, 11);
         w.z = __builtin_amdgcn_alignbit(w.z, w.w << 2, 11);
     }
-    const float u0 = __builtin_fmaf(code_float(w.x), 0x1p-21f, 0x1p-21f - 4.f);
-    const float mu = __builtin_fmaf(code_float(w.y), 0x1p-20f, 0x1p-20f - 9.f);
-    const float u2 = __builtin_fmaf(code_float(w.z), 0x1p-21f, 0x1p-21f - 4.f);
+    const float u0 = __builtin_fmaf(code_float(w.x), 0x1p-21f, c.u);
+    const float mu = __builtin_fmaf(code_float(w.y), 0x1p-20f, c.mu);
+    const float u2 = __builtin_fmaf(code_float(w.z), 0x1p-21f, c.u);
     return diffusive_direction(lam_l2, u0, mu, u2, d);
 }
 
@@ -636,25 +643,17 @@ __device__ __forceinline__ Term hit_term(const SegDev<R>& s, int state, R qu, R 
     return Term{state, tally_bin(s, qu, qv), (float)(-dot3(d, s.sub_n))};
 }
 
-// One flight of a live particle in state MODE (ST_BALLISTIC or ST_DIFFUSIVE): event
-// number p.e + 1.  Returns the terminal outcome (HIT_NONE if still in the gas).
-template <typename R, int MODE>
+// One ballistic flight of a live particle: event number p.e + 1.  Returns the terminal outcome
+// (HIT_NONE if still in the gas; then p.st tells whether the collision thermalised the atom).
+template <typename R>
 __device__ __forceinline__ Term step_mode(const SegDev<R>& s, const TabDev<R>& tb, uint32_t k0, uint32_t k1,
                                           uint32_t pid, uint32_t cap, Particle<R>& p)
 {
     if (p.e >= cap) return Term{HIT_ESCAPED, -1, 0.f};
     const uint32_t e = p.e + 1;
     p.e = e;
-    uint4 r = make_uint4(0u, 0u, 0u, 0u);
-    R ell;
-    if (MODE == ST_BALLISTIC) {
-        r = philox4x32_10(make_uint4(pid, e, s.cfgcat, 0u), k0, k1);
-        ell = s.vacuum ? m_inf<R>() : -lambda_m(s, tb, p.E) * m_log(u01<R>(r.x));
-    } else {
-        uint32_t k[3];
-        diffusive_codes(diffusive_block(pid, e, s.cfgcat, k0, k1), (e & 1u) != 0, k);
-        ell = diffusive_draw(s.lam_l2, k, p.d);   // diffusive only after a gas collision: never in vacuum
-    }
+    const uint4 r = philox4x32_10(make_uint4(pid, e, s.cfgcat, 0u), k0, k1);
+    const R ell = s.vacuum ? m_inf<R>() : -lambda_m(s, tb, p.E) * m_log(u01<R>(r.x));
     R t, qu = (R)0, qv = (R)0;
     const HitF h = hit_test(s, p.x, p.d, ell, t, qu, qv, e == 1u);
     // one compensated move: to the surface hit, else the whole flight (a wave whose lanes
@@ -667,23 +666,33 @@ __device__ __forceinline__ Term step_mode(const SegDev<R>& s, const TabDev<R>& t
     }
     if (hit) return hit_term(s, h.state, qu, qv, p.d);
     if (!finite) return Term{HIT_ESCAPED, -1, 0.f};
-    if (MODE == ST_BALLISTIC) {
-        R V[3] = {(R)0, (R)0, (R)0};
-        if (s.gas_motion) gas_velocity(s, philox4x32_10(make_uint4(pid, e, s.cfgcat, 1u), k0, k1), V);
-        collide(s, tb, p.E, p.d, V, u01<R>(r.y), u01<R>(r.z));
-        ++p.ncoll;
-        if (p.E <= s.E_th) {
-            p.st = ST_DIFFUSIVE;
-            p.r2 = (R)-1;      // no clearance ball yet: the first diffusive step is tested
-        }
-        if (!(m_finite(p.x[0]) && m_finite(p.x[1]) && m_finite(p.x[2]) && m_finite(p.E)))
-            return Term{HIT_ESCAPED, -1, 0.f};
-    } else {
-        // an isotropic unit direction and a finite step keep the position finite
-        ++p.ndiff;
+    R V[3] = {(R)0, (R)0, (R)0};
+    if (s.gas_motion) gas_velocity(s, philox4x32_10(make_uint4(pid, e, s.cfgcat, 1u), k0, k1), V);
+    collide(s, tb, p.E, p.d, V, u01<R>(r.y), u01<R>(r.z));
+    ++p.ncoll;
+    if (p.E <= s.E_th) {
+        p.st = ST_DIFFUSIVE;
+        p.r2 = (R)-1;      // no clearance ball yet: the first diffusive step is tested
     }
+    if (!(m_finite(p.x[0]) && m_finite(p.x[1]) && m_finite(p.x[2]) && m_finite(p.E)))
+        return Term{HIT_ESCAPED, -1, 0.f};
     return Term{HIT_NONE, -1, 0.f};
 }
+
+// What a precision's walk holds besides the particle, and how it steps: see the two walks below.
+// COOP: drained waves with at most this many walkers walk them cooperatively.  FP32: diffusive kernel,
+// single target of 1e5 atoms / four cathodes of 2.3e6 and 2.3e7 / 1e4 atoms at 2 Pa, 0.422 / 0.951 /
+// 3.33 / 1.94 ms at 4, 0.385 / 0.831 / 3.22 / 1.24 at 8, 0.368 / 0.80 / 3.19 / 1.09 at 16, 0.423 / 0.85 /
+// 3.24 / 1.08 at 32.  FP64 (a step's draws weigh five times more): 9e5 atoms at 0.5 / 0 / 2 Pa take 15.5
+// ms at 8, 13.8 at 16, 13.2 at 32.
+template <typename R> struct Walk;
+template <> struct Walk<float> {
+    static constexpr int COOP = 16;
+};
+template <> struct Walk<double> {
+    static constexpr int COOP = 32;
+    double c[3];       // centre of the clearance ball
+};
 
 // Position of a thermalised atom in the batched FP32 walk.  The particle keeps its position
 // as the unevaluated difference x - xc of two floats (as the compensated sum does).  Between
@@ -756,27 +765,74 @@ constexpr int WALK_ADVANCES = 64;
 // geometry.  In this walk p.ndiff holds the events taken before the walk: every later event but
 // the last one of a history that ends on a surface is a step that ended in the gas.
 //
-// One diffusive step from block w (its odd or its even half) from offset `from`: leaves the step in
-// dir, ell and the offset it reaches in `to`, and returns whether that stays in the ball.
-__device__ __forceinline__ bool diffusive_substep(float lam_l2, uint4 w, bool odd, float r2, const float* from,
-                                                  float* to, float* dir, float& ell)
+// Where a step of the FP32 walk starts and ends: an offset from the ball centre.
+struct Spot32 {
+    float o[3];
+};
+__device__ __forceinline__ Spot32 spot_of(const Particle<float>& p) { return Spot32{{p.xc[0], p.xc[1], p.xc[2]}}; }
+__device__ __forceinline__ void stand_at(Particle<float>& p, const Spot32& s)
 {
-    ell = diffusive_draw32(lam_l2, w, odd, dir);   // diffusive only after a gas collision
-    offset_try(from, ell, dir, to);
-    return offset_holds(to, r2);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) p.xc[i] = s.o[i];
+}
+// One diffusive step from block w (its odd or its even half) from spot `from`: leaves the step in
+// dir, ell and the spot it reaches in `to`, and returns whether that stays in the ball.
+__device__ __forceinline__ bool diffusive_substep(float lam_l2, uint4 w, bool odd, float r2, const Walk<float>&,
+                                                  const Spot32& from, Spot32& to, float* dir, float& ell,
+                                                  const DrawConst& c)
+{
+    ell = diffusive_draw32(lam_l2, w, odd, dir, c);   // diffusive only after a gas collision
+    offset_try(from.o, ell, dir, to.o);
+    return offset_holds(to.o, r2);
+}
+
+// Where a step of the FP64 walk starts and ends: a compensated position.  Every step is one
+// compensated add, as the tested step makes it; the ball only decides whether it needs the test.
+struct Spot64 {
+    double x[3], xc[3];
+};
+__device__ __forceinline__ Spot64 spot_of(const Particle<double>& p)
+{
+    return Spot64{{p.x[0], p.x[1], p.x[2]}, {p.xc[0], p.xc[1], p.xc[2]}};
+}
+__device__ __forceinline__ void stand_at(Particle<double>& p, const Spot64& s)
+{
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        p.x[i] = s.x[i];
+        p.xc[i] = s.xc[i];
+    }
+}
+__device__ __forceinline__ bool diffusive_substep(double lam_l2, uint4 w, bool odd, double r2, const Walk<double>& wk,
+                                                  const Spot64& from, Spot64& to, double* dir, double& ell,
+                                                  const DrawConst&)
+{
+    uint32_t k[3];
+    diffusive_codes(w, odd, k);
+    ell = diffusive_draw(lam_l2, k, dir);
+    double q[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        to.x[i] = from.x[i];
+        to.xc[i] = from.xc[i];
+        kahan_add(to.x[i], to.xc[i], ell * dir[i]);
+        q[i] = to.x[i] - wk.c[i];
+    }
+    return fma(q[2], q[2], fma(q[1], q[1], q[0] * q[0])) < r2;     // false for NaN and infinities
 }
 
 // One step of a lane near its event cap: the step of event p.e + 1 (its block drawn for this one
 // step).  Returns whether the step left the ball and is held.
-__device__ __forceinline__ bool diffusive_single(float lam_l2, uint32_t cfgcat, uint32_t k0, uint32_t k1,
-                                                 uint32_t pid, Particle<float>& p)
+template <typename R>
+__device__ __forceinline__ bool diffusive_single(R lam_l2, uint32_t cfgcat, uint32_t k0, uint32_t k1, uint32_t pid,
+                                                 Particle<R>& p, const Walk<R>& wk)
 {
     ++p.e;
     const uint4 w = diffusive_block(pid, p.e, cfgcat, k0, k1);
-    float dir[3], t[3], ell;
-    if (diffusive_substep(lam_l2, w, (p.e & 1u) != 0, p.r2, p.xc, t, dir, ell)) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) p.xc[i] = t[i];
+    R dir[3], ell;
+    auto at = spot_of(p), to = at;
+    if (diffusive_substep(lam_l2, w, (p.e & 1u) != 0, p.r2, wk, at, to, dir, ell, DrawConst())) {
+        stand_at(p, to);
         return false;
     }
 #pragma unroll
@@ -803,21 +859,22 @@ __device__ __forceinline__ bool diffusive_single(float lam_l2, uint32_t cfgcat, 
 // the lanes that hold.  A fixed seven rounds between checks and a test at defer_min held steps took
 // 39.1 ms of diffusive kernel on 3 x 1e7 atoms at 0.5 / 0 / 2 Pa, this form 32.4 ms; 3.65 and
 // 3.35 ms on four cathodes.
-__device__ __forceinline__ bool walk_group(float lam_l2, uint32_t cfgcat, uint32_t k0, uint32_t k1, uint32_t pid,
-                                           int A, int defer_min, int idle_max, Particle<float>& p)
+template <typename R>
+__device__ __forceinline__ bool walk_group(R lam_l2, uint32_t cfgcat, uint32_t k0, uint32_t k1, uint32_t pid, int A,
+                                           int defer_min, int idle_max, Particle<R>& p, const Walk<R>& wk)
 {
-    float dir[3], b[3], ell;
+    R dir[3], ell;
+    auto at = spot_of(p), b = at;
+    DrawConst c;
+    if (std::is_same<R, float>::value) asm("" : "+v"(c.u), "+v"(c.mu));    // not made anew each round
     bool held = true, odd = true;           // odd: the last step taken or held is the odd one of its block
     uint32_t e = (p.e + 1) & ~1u;           // the even event of the block
     uint4 w = diffusive_block(pid, e, cfgcat, k0, k1);
     bool in = true;
     if (p.e & 1u) {
-        in = odd = diffusive_substep(lam_l2, w, false, p.r2, p.xc, b, dir, ell);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) b[i] = p.xc[i];
+        in = odd = diffusive_substep(lam_l2, w, false, p.r2, wk, at, b, dir, ell, c);
     }
-    if (in) in = diffusive_substep(lam_l2, w, true, p.r2, b, p.xc, dir, ell);
+    if (in) in = diffusive_substep(lam_l2, w, true, p.r2, wk, b, at, dir, ell, c);
     if (in) {
         int idle = 0, n = 1;
         for (;;) {
@@ -829,19 +886,17 @@ __device__ __forceinline__ bool walk_group(float lam_l2, uint32_t cfgcat, uint32
             }
             e += 2;
             w = philox4x32_10(make_uint4(pid, e, cfgcat, 2u), k0, k1);
-            if (!diffusive_substep(lam_l2, w, false, p.r2, p.xc, b, dir, ell)) {
+            if (!diffusive_substep(lam_l2, w, false, p.r2, wk, at, b, dir, ell, c)) {
                 odd = false;
                 break;
             }
-            if (!diffusive_substep(lam_l2, w, true, p.r2, b, p.xc, dir, ell)) break;
+            if (!diffusive_substep(lam_l2, w, true, p.r2, wk, b, at, dir, ell, c)) break;
         }
     }
     p.e = e + (odd ? 1u : 0u);
+    if (held && odd) at = b;                // where the odd step started
+    stand_at(p, at);
     if (held) {
-        if (odd) {                          // the offset before the odd step
-#pragma unroll
-            for (int i = 0; i < 3; ++i) p.xc[i] = b[i];
-        }
 #pragma unroll
         for (int i = 0; i < 3; ++i) p.d[i] = dir[i];
         p.r2 = ell;
@@ -849,7 +904,7 @@ __device__ __forceinline__ bool walk_group(float lam_l2, uint32_t cfgcat, uint32
     return held;
 }
 
-__device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& s, Particle<float>& p)
+__device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& s, Particle<float>& p, Walk<float>&)
 {
     const float dir[3] = {p.d[0], p.d[1], p.d[2]};
     const float ell = p.r2;
@@ -868,127 +923,153 @@ __device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& s, Partic
     return Term{HIT_NONE, -1, 0.f};
 }
 
-// One lane along each 16-lane row (DPP row_shr:1): lane j of a row takes src of lane j - 1; the
-// first lane of a row has no source there and keeps old.
+// The same in FP64, with the arithmetic of a step that is always tested.
+__device__ __forceinline__ Term diffusive_resolve(const SegDev<double>& s, Particle<double>& p, Walk<double>& wk)
+{
+    const double dir[3] = {p.d[0], p.d[1], p.d[2]};
+    const double ell = p.r2;
+    double th, qu = 0.0, qv = 0.0;
+    const HitF h = hit_test(s, p.x, dir, ell, th, qu, qv, false);
+    const bool hit = h.state != HIT_NONE;
+    if (!hit && !(ell < m_inf<double>())) return Term{HIT_ESCAPED, -1, 0.f};
+    const double mv = hit ? th : ell;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) kahan_add(p.x[i], p.xc[i], mv * dir[i]);
+    if (hit) return hit_term(s, h.state, qu, qv, dir);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) wk.c[i] = p.x[i];
+    const double c = clearance(s, p.x) - (double)CLEAR_MARGIN;
+    p.r2 = c > 0.0 ? c * c : -1.0;
+    return Term{HIT_NONE, -1, 0.f};
+}
+
+// One lane along each 16-lane row (DPP row_shr:1): lane j of a row takes src of lane j - 1; a lane
+// whose source lies outside the row, or is switched off, keeps old.
 __device__ __forceinline__ float row_shift1(float old, float src)
 {
     return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(src), 0x111, 0xF, 0xF, false));
 }
-
-// Diffusive steps of up to four thermalised particles of a wave (its lanes in G) taken with the
-// whole wave.  Each particle gets a span of 64, 32 or 16 lanes (one, two, or three and four
-// particles); lane j of a span draws step e + 1 + j of its particle (Philox block, direction and
-// length).  The offsets the steps reach, T_j = fma(-ell_j, d_j, T_{j-1}) from T_{-1} = xc, are
-// formed along the spans by shifting the chain one lane per round: within 16-lane rows (DPP), one
-// row of every span per phase, the last offset of a row seeding the first lane of the next.  That
-// is the order of diffusive_substep, one step after the other, so each T_j is the value the
-// step-by-step walk computes, and the committed position, event and step counts are equal.  A
-// particle takes its steps up to the first one that leaves the clearance ball or passes the event
-// cap (a phase ends the chain early once every particle has such a step); the step that leaves
-// the ball is held for the surface test, as diffusive_substep holds it, and a step past the cap
-// is not taken (the history, at the cap, escapes).  Every call therefore takes a step, holds one,
-// or leaves each particle at the cap.  Called by the whole wave with G uniform, 1 to 4 lanes.
-__device__ __forceinline__ void coop_walk(uint32_t k0, uint32_t k1, uint32_t cap, uint64_t G, float lam_l2,
-                                          uint32_t cfgcat, uint32_t pid, Particle<float>& p, bool& held, int lane)
+__device__ __forceinline__ double row_shift1(double old, double src)
 {
-    const int g = __popcll(G);
-    const int sh = g == 1 ? 6 : g == 2 ? 5 : 4;      // log2 of the span
-    const int span = 1 << sh;
-    const int slot = lane >> sh, j = lane & (span - 1);
-    int home[4];                                      // the particles' lanes, in lane order
-    {
-        uint64_t m = G;
+    const int l = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(src), 0x111, 0xF, 0xF, false);
+    const int h = __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(src), 0x111, 0xF, 0xF, false);
+    return __hiloint2double(h, l);
+}
+__device__ __forceinline__ Spot32 row_shift1(const Spot32& old, const Spot32& src)
+{
+    Spot32 r;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            home[q] = m ? __ffsll((unsigned long long)m) - 1 : 0;
-            m &= m - 1;
-        }
+    for (int i = 0; i < 3; ++i) r.o[i] = row_shift1(old.o[i], src.o[i]);
+    return r;
+}
+__device__ __forceinline__ Spot64 row_shift1(const Spot64& old, const Spot64& src)
+{
+    Spot64 r;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        r.x[i] = row_shift1(old.x[i], src.x[i]);
+        r.xc[i] = row_shift1(old.xc[i], src.xc[i]);
     }
-    const int src = slot == 0 ? home[0] : slot == 1 ? home[1] : slot == 2 ? home[2] : home[3];
-    const uint32_t pidw = (uint32_t)__shfl((int)pid, src);
-    const uint32_t e0 = (uint32_t)__shfl((int)p.e, src);
-    const float r2 = __shfl(p.r2, src);
-    const float lam = __shfl(lam_l2, src);
-    const uint32_t cc = (uint32_t)__shfl((int)cfgcat, src);
-    float xc[3];
+    return r;
+}
+// The spot of lane `src`.
+__device__ __forceinline__ Spot32 lane_spot(const Spot32& s, int src)
+{
+    Spot32 r;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) xc[i] = __shfl(p.xc[i], src);
-    const uint32_t ej = e0 + 1u + (uint32_t)j;
-    uint32_t kc[3];
-    diffusive_codes(diffusive_block(pidw, ej, cc, k0, k1), (ej & 1u) != 0, kc);
-    float dir[3];
-    const float ell = diffusive_draw(lam, kc, dir);
-    const bool allowed = ej <= cap && slot < g;        // steps within the event cap
-    const float nell = -ell;
-    // t: the lane's offset T_j; u: its input T_{j-1} (at the first lane of a row, the row's seed,
-    // which the shift leaves in place)
-    float t[3], u[3];
+    for (int i = 0; i < 3; ++i) r.o[i] = __shfl(s.o[i], src);
+    return r;
+}
+__device__ __forceinline__ Spot64 lane_spot(const Spot64& s, int src)
+{
+    Spot64 r;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) t[i] = u[i] = xc[i];
-    uint64_t ok = 0;
-    const int rows = span >> 4;
-    for (int r = 0; r < rows; ++r) {
-#pragma unroll
-        for (int it = 0; it < 16; ++it) {
-#pragma unroll
-            for (int i = 0; i < 3; ++i) u[i] = row_shift1(u[i], t[i]);
-#pragma unroll
-            for (int i = 0; i < 3; ++i) t[i] = __builtin_fmaf(nell, dir[i], u[i]);
-        }
-        // rows 0..r of every span are final: done once each particle has a step it cannot take
-        ok = __ballot(allowed && offset_holds(t, r2));
-        const uint64_t done_rows = r == 3 ? ~0ull : (1ull << (16 * (r + 1))) - 1;
-        bool all = true;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (q < g) all = all && (~ok & (done_rows << (q << sh))) != 0;
-        if (all || r == rows - 1) break;
-        float c[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) c[i] = __shfl(t[i], lane - 1);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) u[i] = j == 16 * (r + 1) ? c[i] : u[i];
+    for (int i = 0; i < 3; ++i) {
+        r.x[i] = __shfl(s.x[i], src);
+        r.xc[i] = __shfl(s.xc[i], src);
     }
-    const uint64_t in_cap = __ballot(allowed);
-    const uint64_t span_mask = span == 64 ? ~0ull : (1ull << span) - 1;
+    return r;
+}
+__device__ __forceinline__ Walk<float> lane_walk(const Walk<float>& w, int) { return w; }
+__device__ __forceinline__ Walk<double> lane_walk(const Walk<double>& w, int src)
+{
+    Walk<double> r;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (q >= g) break;
-        const int b = q << sh;
-        const uint64_t bad = (~ok >> b) & span_mask;
-        const int f = bad ? __ffsll((unsigned long long)bad) - 1 : span;   // steps taken
-        const bool hold = f < span && ((in_cap >> (b + f)) & 1ull);
-        float nx[3];
+    for (int i = 0; i < 3; ++i) r.c[i] = __shfl(w.c[i], src);
+    return r;
+}
+// The step (ell, dir) from spot u, as diffusive_substep takes it, and whether a spot is in the ball.
+__device__ __forceinline__ Spot32 step_from(const Spot32& u, float ell, const float* dir)
+{
+    Spot32 t;
+    offset_try(u.o, ell, dir, t.o);
+    return t;
+}
+__device__ __forceinline__ Spot64 step_from(const Spot64& u, double ell, const double* dir)
+{
+    Spot64 t = u;
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
-            nx[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(f > 0 ? t[i] : xc[i]), f > 0 ? b + f - 1 : b));
-        float hd[3] = {0.f, 0.f, 0.f}, hl = 0.f;
-        if (hold) {
-            hl = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ell), b + f));
+    for (int i = 0; i < 3; ++i) kahan_add(t.x[i], t.xc[i], ell * dir[i]);
+    return t;
+}
+__device__ __forceinline__ bool spot_holds(const Spot32& t, const Walk<float>&, float r2) { return offset_holds(t.o, r2); }
+__device__ __forceinline__ bool spot_holds(const Spot64& t, const Walk<double>& wk, double r2)
+{
+    double q[3];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) hd[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dir[i]), b + f));
-        }
-        if (lane == home[q]) {      // a particle's lane may lie in another particle's span
-#pragma unroll
-            for (int i = 0; i < 3; ++i) p.xc[i] = nx[i];
-            p.e += (uint32_t)f;
-            if (hold) {
-#pragma unroll
-                for (int i = 0; i < 3; ++i) p.d[i] = hd[i];
-                p.r2 = hl;
-                p.e += 1u;
-                held = true;
-            }
-        }
-    }
+    for (int i = 0; i < 3; ++i) q[i] = t.x[i] - wk.c[i];
+    return fma(q[2], q[2], fma(q[1], q[1], q[0] * q[0])) < r2;
+}
+__device__ __forceinline__ float any_draw(float lam_l2, uint4 w, bool odd, float* d)
+{
+    return diffusive_draw32(lam_l2, w, odd, d);
+}
+__device__ __forceinline__ double any_draw(double lam_l2, uint4 w, bool odd, double* d)
+{
+    uint32_t k[3];
+    diffusive_codes(w, odd, k);
+    return diffusive_draw(lam_l2, k, d);
 }
 
-template <typename R>
-__device__ __forceinline__ Term step(const SegDev<R>& s, const TabDev<R>& tb, uint32_t k0, uint32_t k1, uint32_t pid,
-                                     uint32_t cap, Particle<R>& p)
+// The spots that consecutive steps of a walker reach: lane j of its span of 2^sh lanes holds step j
+// (ell, dir), all of them the spot `at` before the first.  T_j is step j from T_{j-1}, in the order and
+// with the operations of the step-by-step walk, so every T_j is the value that computes: the chain moves
+// one lane a round, in 16-lane rows (DPP).  In spans shorter than a row the first lane of each is
+// switched off, so that its neighbour keeps T_0; in spans of several rows each row's last spot seeds the
+// next row, and the chain ends early once every walker of the wave has a step that leaves its ball.
+template <typename R, typename S>
+__device__ __forceinline__ S chain_steps(const S& at, R ell, const R* dir, int sh, int j, bool allowed, bool alive,
+                                         const Walk<R>& wk, R r2)
 {
-    return p.st == ST_BALLISTIC ? step_mode<R, ST_BALLISTIC>(s, tb, k0, k1, pid, cap, p)
-                                : step_mode<R, ST_DIFFUSIVE>(s, tb, k0, k1, pid, cap, p);
+    S u = at, t;
+    if (sh < 4) {                      // at least two lanes a walker
+        t = step_from(at, ell, dir);
+        u = row_shift1(u, t);
+        if (j != 0)
+            for (int it = 1; it < (1 << sh); ++it) {
+                t = step_from(u, ell, dir);
+                u = row_shift1(u, t);
+            }
+        return t;
+    }
+    t = at;
+    const int rows = 1 << (sh - 4), row = j >> 4;
+    for (int r = 0; r < rows; ++r) {
+#pragma unroll 4
+        for (int it = 0; it < 16; ++it) {
+            u = row_shift1(u, t);
+            t = step_from(u, ell, dir);
+        }
+        if (r + 1 == rows) break;
+        // walkers whose steps so far all stay in the ball: those go on
+        const bool out = alive && row <= r && !(allowed && spot_holds(t, wk, r2));
+        const uint64_t left = __ballot(out);
+        const uint64_t mine = sh == 6 ? left : (left >> ((__lane_id() >> 5) * 32)) & 0xFFFFFFFFull;
+        if (__ballot(alive && mine == 0) == 0) break;
+        const S c = lane_spot(t, (int)__lane_id() - 1);
+        if (j == 16 * (r + 1)) u = c;
+    }
+    return t;
 }
 
 template <typename R>

@@ -52,27 +52,28 @@ struct SegHost {
     double cost;          // relative expected work per particle (ticket ordering)
 };
 
-// A thermalised atom handed from the ballistic to the diffusive phase (48 B).
-struct alignas(16) ThermRec {
-    float x[3], xc[3];          // compensated position (chamber frame)
-    float E;                    // energy at thermalisation (reported in the record)
-    uint32_t pid;               // particle index within its segment
+// A thermalised atom handed from the ballistic to the diffusive phase (FP32 48 B, FP64 80 B).
+template <typename R> struct alignas(16) ThermRec {
+    R x[3], xc[3];              // compensated position (chamber frame)
+    R E;                        // energy at thermalisation (reported in the record)
+    R lam;                      // the segment's lam_th ln 2 and Philox counter word: the two
+    uint32_t cfgcat;            // numbers of the segment a diffusive step needs
+    uint32_t pid;               // particle index within its segment (~0: empty slot)
     uint32_t seg;               // segment
     uint32_t e;                 // events taken so far
-    uint32_t lam_bits;          // the segment's lam_th ln 2 (float bits) and Philox counter word: the
-    uint32_t cfgcat;            // two numbers of the segment a diffusive step needs
 };
-static_assert(sizeof(ThermRec) == 48, "ThermRec layout");
+static_assert(sizeof(ThermRec<float>) == 48, "ThermRec layout");
+static_assert(sizeof(ThermRec<double>) == 80, "ThermRec layout");
 
-// Launch arguments of the two batched FP32 transport kernels (one round = one chunk of the
+// Launch arguments of the two transport kernels of a precision (one round = one chunk of the
 // ticket space: the ballistic phase of every ticket, then the diffusive phase of the atoms
 // it thermalised).
-struct TransportArgs {
-    const SegDev<float>* segs;
-    TabDev<float> tab;
+template <typename R> struct TransportArgs {
+    const SegDev<R>* segs;
+    TabDev<R> tab;
     const uint64_t* tfirst;     // [n_seg + 1] first ticket of each position in ticket order
     const uint32_t* torder;     // [n_seg] segment at each position
-    ThermRec* queue;            // thermalised atoms of the round (capacity >= tickets of a round)
+    ThermRec<R>* queue;         // thermalised atoms of the round (capacity >= tickets of a round)
     uint64_t* qstate;           // [QS_TICKETS] ballistic ticket counter, [QS_QUEUE] queue length,
                                 // [QS_DIFFUSIVE] diffusive ticket counter
     unsigned long long* counts;
@@ -81,8 +82,8 @@ struct TransportArgs {
     unsigned long long* arr_E;  // arrival energy histograms [n_seg][SPX_ARRIVAL_E_BINS] (nullable)
     unsigned long long* arr_A;  // arrival angle histograms [n_seg][SPX_ARRIVAL_A_BINS] (nullable with arr_E)
     unsigned long long* esum;   // per tally bin: arrival energies in units of 2^-24 eV (nullable with arr_E)
-    const float* e_edges;       // [SPX_ARRIVAL_E_BINS + 1] energy edges, eV
-    const float* c_edges;       // [SPX_ARRIVAL_A_BINS + 1] cos(k deg)
+    const R* e_edges;           // [SPX_ARRIVAL_E_BINS + 1] energy edges, eV
+    const R* c_edges;           // [SPX_ARRIVAL_A_BINS + 1] cos(k deg)
     uint64_t tbase;             // first ticket of the round
     uint64_t total;             // tickets of the round
     uint32_t k0, k1;            // Philox key (seed words)
@@ -112,6 +113,8 @@ struct Outputs {
 };
 
 constexpr uint64_t ROUND_MAX = 1ull << 28;   // tickets per round: a 12.9 GB queue of thermalised atoms
+// FP64 rounds: 1.3 GB of queue; where that much is not free, half the round, down to the smallest
+constexpr uint64_t ROUND_MAX64 = 1ull << 24, ROUND_MIN64 = 1ull << 16;
 constexpr uint64_t QUEUE_CHUNK = 64;         // queue slots a wave reserves per atomic
 // exactly one lane per slot: a hand-over of up to 64 atoms continues into at most one fresh
 // run, and a wave marks its unused reserved slots one per lane
@@ -136,7 +139,12 @@ constexpr int DEFER_MIN = 8;                  // default: held diffusive steps t
 // sweep: 34.5 / 3.46 / 85.7 ms at 64, 33.9 / 3.37 / 84.0 at 128, 34.1 / 3.46 / 84.4 at 192, 35.9 /
 // 3.82 / 88.4 at 400.
 constexpr int WALK_IDLE = 128;
-constexpr int COOP_MAX = 8;                   // drained waves with at most this many live lanes walk cooperatively
+// The same for the FP64 walk, whose rounds cost as much as a test pass: 9e6 atoms at 0.5 / 0 / 2 Pa took
+// 62.2 ms at 96 idle rounds, 60.4 at 64.
+constexpr int WALK_IDLE64 = 64;
+// Refill thresholds of the FP64 phases (four cathodes, 2.3e6 atoms: 4.95 ms with the ballistic phase
+// refilled at 16 dead lanes, 4.66 at 24, 6.1 at 8; the diffusive phase differs by 1 % between 2 and 8).
+constexpr int REFILL64 = 2, REFILL_BALLISTIC64 = 24;
 constexpr size_t LDS_TALLY_MAX = 49152;      // bytes: up to 12288 bins
 constexpr size_t LDS_ARRIVALS_MAX = 4096;     // bytes: arrival histograms of up to 6 segments
 
@@ -195,7 +203,7 @@ struct Shape {
 // Queue of thermalised atoms and ticket counters a run works in: the plan's own allocation, or
 // caller-independent static scratch.  Rounds hold at most round_max tickets.
 struct QueueMem {
-    ThermRec* queue = nullptr;
+    void* queue = nullptr;       // ThermRec<R> of the plan's precision
     uint64_t cap = 0;            // slots
     uint64_t* qstate = nullptr;  // QSTATE_WORDS words: the round's counters
     uint64_t round_max = ROUND_MAX;
@@ -228,8 +236,10 @@ struct spx_plan {
     spx::RtNode<double>* d_rt64 = nullptr;
     uint64_t* d_tfirst = nullptr;
     uint32_t* d_torder = nullptr;
-    spx::ThermRec* d_queue = nullptr;       // thermalised atoms of a round (FP32 plans)
-    uint64_t queue_cap = 0;
+    unsigned char* d_queue = nullptr;       // thermalised atoms of a round (ThermRec of the precision)
+    uint64_t queue_cap = 0;                 // slots
+    uint64_t round_max = spx::ROUND_MAX;    // tickets per round, at most
+    spx::Shape shape64;                     // launch of the FP64 kernels
     uint64_t* d_qstate = nullptr;           // ticket counters and queue length
     std::vector<hipEvent_t> phase_events;   // recorded in the graph: round start, ballistic end, diffusive end
     uint64_t* d_bin_off = nullptr;          // [n_seg + 1]
@@ -257,10 +267,12 @@ using Plan = spx_plan;
 int build_tables(Plan* P);
 // events (nullable, not while capturing): 3 per round, recorded at the round's start, after
 // its ballistic phase and after its diffusive phase.
-// The launches of one batched FP32 run over tickets [0, total) of `tfirst` in rounds of at most
+// The launches of one run over tickets [0, total) of `tfirst` in rounds of at most
 // q.round_max tickets: zero the outputs, per round reset / ballistic / diffusive, normalise.
-int build_transport32(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tfirst, uint64_t total,
-                      const Shape& sh, const QueueMem& q, LaunchSink& sink);
+// R: the plan's precision.
+template <typename R>
+int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tfirst, uint64_t total,
+                    const Shape& sh, const QueueMem& q, LaunchSink& sink);
 // A sink that launches on `st`; with `events` (3 per round, not while capturing) it records one
 // before each ballistic kernel, one after it and one after the diffusive kernel.
 struct StreamSink : LaunchSink {
@@ -273,8 +285,9 @@ struct StreamSink : LaunchSink {
 uint64_t rounds_of(uint64_t total, uint64_t round_max = ROUND_MAX);
 // The plan's current launch geometry and thresholds.
 Shape plan_shape(const Plan* P);
-int launch_transport64(Plan* P, uint64_t seed, const Outputs& o, hipStream_t st);
-// Arrival bin edges in double (as the comparator uses them); the batched path rounds them to float.
+// Launch geometry of the FP64 kernels of a plan.
+int shape_transport64(Plan* P);
+// Arrival bin edges in double (as the FP64 path uses them); the FP32 path rounds them to float.
 void arrival_edges(double* e_edges, double* c_edges);
 // resident blocks per CU of the ballistic and of the diffusive kernel at this block size
 int occupancy_transport32(const Plan* P, int threads, int* bpc_ballistic, int* bpc_diffusive);

@@ -1,11 +1,11 @@
-// transport.hip -- the two transport paths and their tally kernels.
+// transport.hip -- the transport kernels of both precisions and their tallies.
 //
-// Batched FP32 path: every (configuration, cathode) segment of a plan runs in rounds of
-// at most ROUND_MAX tickets, each round as two persistent launches.  k_ballistic32 takes
-// every ticket of the round from its launch through its ballistic flights and collisions;
-// an atom that ends on a surface (or escapes) is finished there, an atom that thermalises
-// is handed over to a queue in HBM (48 B, with the two numbers of its segment a step needs).  k_diffusive32 then runs the diffusive walks of
-// the queued atoms.  Each lane holds one atom in registers; when lanes die, the wave claims
+// Every (configuration, cathode) segment of a plan runs in rounds of at most ROUND_MAX (FP64:
+// ROUND_MAX64) tickets, each round as two persistent launches.  The ballistic kernel takes
+// every ticket of the round from its launch through its flights and collisions; an atom that
+// ends on a surface (or escapes) is finished there, an atom that thermalises is handed over to
+// a queue in HBM (48 B, in FP64 80 B, with the two numbers of its segment a step needs).  The
+// diffusive kernel then runs the walks of the queued atoms.  Each lane holds one atom in registers; when lanes die, the wave claims
 // a run of tickets with a single atomic (ballot + mbcnt prefix gives each dead lane its
 // ticket).  Splitting the history at thermalisation keeps every lane of a wave in the same
 // kind of event: new atoms (ballistic) and walkers (diffusive) never share a wave.  The
@@ -14,8 +14,10 @@
 // to a per-block LDS tally (or 64-bit global atomics when it does not fit); per-segment
 // counters are accumulated in registers while a lane stays in one segment.
 //
-// Plain FP64 path (k_transport64): one thread per particle runs the whole history;
-// one launch per segment.  It is the comparator for the batched path.
+// The kernels are written once for R = float and R = double.  FP32 walks add their steps to an offset
+// from the centre of a clearance ball, FP64 walks to the compensated position itself, and in both a
+// step is tested against the surfaces only where it leaves the ball, so that FP64 outcomes are those of
+// testing every step, bit for bit.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -66,11 +68,12 @@ constexpr int ARR_BINS = SPX_ARRIVAL_E_BINS + SPX_ARRIVAL_A_BINS;
 
 // Arrival tallies of one deposit: energy and angle histograms of its segment, energy sum of
 // its tally bin.
-__device__ __forceinline__ void tally_arrival(const TransportArgs& a, const BlockTally& bt, int seg, uint64_t bin,
+template <typename R>
+__device__ __forceinline__ void tally_arrival(const TransportArgs<R>& a, const BlockTally& bt, int seg, uint64_t bin,
                                               double E, double cos_in)
 {
-    const int be = energy_bin(a.e_edges, (float)E);
-    const int ba = angle_bin(a.c_edges, (float)cos_in);
+    const int be = energy_bin(a.e_edges, (R)E);
+    const int ba = angle_bin(a.c_edges, (R)cos_in);
     if (a.lds_arrivals) {
         atomicAdd(&bt.larr[seg * ARR_BINS + be], 1u);
         atomicAdd(&bt.larr[seg * ARR_BINS + SPX_ARRIVAL_E_BINS + ba], 1u);
@@ -81,7 +84,8 @@ __device__ __forceinline__ void tally_arrival(const TransportArgs& a, const Bloc
     atomicAdd(&a.esum[bin], energy_units(E));
 }
 
-__device__ __forceinline__ void flush_acc(const TransportArgs& a, const BlockTally& bt, LaneAcc& acc)
+template <typename R>
+__device__ __forceinline__ void flush_acc(const TransportArgs<R>& a, const BlockTally& bt, LaneAcc& acc)
 {
     if (acc.seg < 0) return;
     if (a.lds_counters) {
@@ -96,9 +100,9 @@ __device__ __forceinline__ void flush_acc(const TransportArgs& a, const BlockTal
 }
 
 // End of a history: counters, tally, optional record; the lane becomes free.
-template <bool ARR>
-__device__ __forceinline__ void terminate(const TransportArgs& a, const BlockTally& bt, const SegDev<float>& s,
-                                          uint32_t pid, Particle<float>& p, const Term& t, LaneAcc& acc)
+template <bool ARR, typename R>
+__device__ __forceinline__ void terminate(const TransportArgs<R>& a, const BlockTally& bt, const SegDev<R>& s,
+                                          uint32_t pid, Particle<R>& p, const Term& t, LaneAcc& acc)
 {
     // static indices only: the counters stay in registers
     acc.c[C_DEPOSITED] += (t.state == HIT_DEPOSITED) ? 1u : 0u;
@@ -107,6 +111,10 @@ __device__ __forceinline__ void terminate(const TransportArgs& a, const BlockTal
     acc.c[C_COLLISIONS] += p.ncoll;
     acc.c[C_DIFFUSIVE] += p.ndiff;
     acc.c[C_THERMALIZED] += (p.st == ST_DIFFUSIVE) ? 1u : 0u;
+    // the FP64 path counts every diffusive step: those that ended in the gas and the last one
+    // (unless the history stopped at the event cap); the FP32 path counts at the test
+    if (std::is_same<R, double>::value)
+        acc.c[C_TESTED] += p.ndiff + ((p.st == ST_DIFFUSIVE && t.state != HIT_ESCAPED) ? 1u : 0u);
     if (t.state == HIT_DEPOSITED) {
         const uint64_t b = s.bin_off + (uint64_t)t.bin;
         if (a.lds_tally) atomicAdd(&bt.ltally[b], 1u);
@@ -167,7 +175,8 @@ __device__ __forceinline__ uint64_t claim(Tickets& T, uint64_t* counter, uint64_
     return (((dead >> lane) & 1ull) && rank < take) ? base + rank : ~0ull;
 }
 
-__device__ __forceinline__ void lds_setup(const TransportArgs& a, BlockTally& bt, unsigned long long* lds)
+template <typename R>
+__device__ __forceinline__ void lds_setup(const TransportArgs<R>& a, BlockTally& bt, unsigned long long* lds)
 {
     bt.lcnt = lds;
     bt.ltally = (uint32_t*)(lds + (a.lds_counters ? (size_t)a.n_seg * N_COUNTERS : 0));
@@ -181,7 +190,8 @@ __device__ __forceinline__ void lds_setup(const TransportArgs& a, BlockTally& bt
     __syncthreads();
 }
 
-__device__ __forceinline__ void lds_flush(const TransportArgs& a, const BlockTally& bt, LaneAcc& acc)
+template <typename R>
+__device__ __forceinline__ void lds_flush(const TransportArgs<R>& a, const BlockTally& bt, LaneAcc& acc)
 {
     flush_acc(a, bt, acc);
     __syncthreads();
@@ -211,8 +221,9 @@ struct QRun {
 // Lanes whose atom thermalised in the last flight hand it to the diffusive queue and become
 // free.  Slots come from the wave's run (a hand-over may continue into a fresh run).  Their
 // collisions are counted here; thermalisation itself is counted when the walk ends.
-__device__ __forceinline__ void hand_over(const TransportArgs& a, const SegDev<float>& S, uint32_t pid, int seg,
-                                          Particle<float>& p, LaneAcc& acc, QRun& Q, int lane)
+template <typename R>
+__device__ __forceinline__ void hand_over(const TransportArgs<R>& a, const SegDev<R>& S, uint32_t pid, int seg,
+                                          Particle<R>& p, LaneAcc& acc, QRun& Q, int lane)
 {
     const uint64_t T = __ballot(p.st == ST_DIFFUSIVE);
     if (T == 0) return;
@@ -227,7 +238,7 @@ __device__ __forceinline__ void hand_over(const TransportArgs& a, const SegDev<f
     if (p.st == ST_DIFFUSIVE) {
         const uint64_t rank = lanes_below(T);
         const uint64_t slot = rank < rem ? Q.q + rank : fresh + (rank - rem);   // < queue capacity
-        ThermRec r;
+        ThermRec<R> r;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             r.x[i] = p.x[i];
@@ -237,7 +248,7 @@ __device__ __forceinline__ void hand_over(const TransportArgs& a, const SegDev<f
         r.pid = pid;
         r.seg = (uint32_t)seg;
         r.e = p.e;
-        r.lam_bits = __float_as_uint(S.lam_l2);
+        r.lam = S.lam_l2;
         r.cfgcat = S.cfgcat;
         a.queue[slot] = r;
         acc.c[C_COLLISIONS] += p.ncoll;
@@ -252,7 +263,8 @@ __device__ __forceinline__ void hand_over(const TransportArgs& a, const SegDev<f
 }
 
 // Mark the wave's unused reserved slots as empty (pid ~0).
-__device__ __forceinline__ void close_run(const TransportArgs& a, const QRun& Q, int lane)
+template <typename R>
+__device__ __forceinline__ void close_run(const TransportArgs<R>& a, const QRun& Q, int lane)
 {
     if (Q.q + (uint64_t)lane < Q.q_end) a.queue[Q.q + lane].pid = 0xFFFFFFFFu;
 }
@@ -263,23 +275,27 @@ __device__ __forceinline__ void close_run(const TransportArgs& a, const QRun& Q,
 // phase, as state | bin << 2.
 constexpr int ST_ENDED = 3;
 
-__device__ __forceinline__ void mark_ended(Particle<float>& p, const Term& t)
+__device__ __forceinline__ float pack_end(float, uint32_t bits) { return __uint_as_float(bits); }
+__device__ __forceinline__ double pack_end(double, uint32_t bits) { return __hiloint2double(0, (int)bits); }
+__device__ __forceinline__ uint32_t end_bits(float r2) { return __float_as_uint(r2); }
+__device__ __forceinline__ uint32_t end_bits(double r2) { return (uint32_t)__double2loint(r2); }
+template <typename R> __device__ __forceinline__ void mark_ended(Particle<R>& p, const Term& t)
 {
     p.st = ST_ENDED;
-    p.r2 = __uint_as_float((uint32_t)t.state | ((uint32_t)(t.bin < 0 ? 0 : t.bin) << 2));
+    p.r2 = pack_end((R)0, (uint32_t)t.state | ((uint32_t)(t.bin < 0 ? 0 : t.bin) << 2));
 }
 
 // Settle the wave's ended histories (counters, tally, record) and queue its thermalised atoms.
 // The incidence cosine of a deposit is recomputed from its direction, with the operations of
 // hit_term.
-template <bool ARR>
-__device__ __forceinline__ void settle_ballistic(const TransportArgs& a, const BlockTally& bt,
-                                                 const SegDev<float>* __restrict__ segs, uint32_t pid, int seg,
-                                                 Particle<float>& p, LaneAcc& acc, QRun& Q, int lane)
+template <bool ARR, typename R>
+__device__ __forceinline__ void settle_ballistic(const TransportArgs<R>& a, const BlockTally& bt,
+                                                 const SegDev<R>* __restrict__ segs, uint32_t pid, int seg,
+                                                 Particle<R>& p, LaneAcc& acc, QRun& Q, int lane)
 {
     if (__ballot(p.st == ST_ENDED) != 0 && p.st == ST_ENDED) {
-        const SegDev<float>& s = segs[seg];
-        const uint32_t bits = __float_as_uint(p.r2);
+        const SegDev<R>& s = segs[seg];
+        const uint32_t bits = end_bits(p.r2);
         Term t;
         t.state = (int)(bits & 3u);
         t.bin = t.state == HIT_DEPOSITED ? (int)(bits >> 2) : -1;
@@ -289,32 +305,36 @@ __device__ __forceinline__ void settle_ballistic(const TransportArgs& a, const B
     if (__ballot(p.st == ST_DIFFUSIVE) != 0) hand_over(a, segs[seg], pid, seg, p, acc, Q, lane);
 }
 
-// Ballistic flights of the lanes in segment S (uniform: its constants stay in scalar
+// Ballistic flights of the lanes in `mine`, all of segment S (uniform: its constants stay in scalar
 // registers) until the wave should refill (lanes that ended, thermalised or are free count) or
-// has no ballistic lane left.
-__device__ __forceinline__ void ballistic_loop(const TransportArgs& a, const SegDev<float>& S, uint32_t pid,
-                                               Particle<float>& p, bool drained)
+// none of them flies.
+template <typename R>
+__device__ __forceinline__ void ballistic_loop(const TransportArgs<R>& a, const SegDev<R>* S, uint32_t pid,
+                                               Particle<R>& p, bool mine, bool drained)
 {
     for (;;) {
-        if (p.st == ST_BALLISTIC) {
-            const Term t = step_mode<float, ST_BALLISTIC>(S, a.tab, a.k0, a.k1, pid, a.cap, p);
+        // the FP64 constants do not fit the scalar registers: read again for every flight (an empty
+        // asm hides that the pointer is the same), not kept across flights in spilled vector registers
+        if (std::is_same<R, double>::value) asm volatile("" : "+s"(S));
+        if (mine && p.st == ST_BALLISTIC) {
+            const Term t = step_mode(*S, a.tab, a.k0, a.k1, pid, a.cap, p);
             if (t.state != HIT_NONE) mark_ended(p, t);
         }
-        if (__ballot(p.st == ST_BALLISTIC) == 0) break;
+        if (__ballot(mine && p.st == ST_BALLISTIC) == 0) break;
         if (!drained && __popcll(__ballot(p.st != ST_BALLISTIC)) >= a.refill_ballistic) break;
     }
 }
 
 // Histories of lanes at the event cap (rare) escape, ended one segment at a time.
-template <bool ARR>
-__device__ __forceinline__ void escape_capped(const TransportArgs& a, const BlockTally& bt,
-                                              const SegDev<float>* __restrict__ segs, int seg, uint32_t pid,
-                                              Particle<float>& p, LaneAcc& acc, bool capped)
+template <bool ARR, typename R>
+__device__ __forceinline__ void escape_capped(const TransportArgs<R>& a, const BlockTally& bt,
+                                              const SegDev<R>* __restrict__ segs, int seg, uint32_t pid,
+                                              Particle<R>& p, LaneAcc& acc, bool capped)
 {
-    for (uint64_t R = __ballot(capped); R != 0;) {
-        const int sL = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)R) - 1);
+    for (uint64_t C = __ballot(capped); C != 0;) {
+        const int sL = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)C) - 1);
         const bool mine = capped && seg == sL;
-        R &= ~__ballot(mine);
+        C &= ~__ballot(mine);
         if (mine) {
             capped = false;
             p.ndiff = p.e - p.ndiff;
@@ -325,25 +345,25 @@ __device__ __forceinline__ void escape_capped(const TransportArgs& a, const Bloc
 
 // The held steps of the wave (mask H != 0), tested together: with the geometry read once for
 // the wave when they share a segment (the common case), else each lane reading its own.
-template <bool ARR>
-__device__ __forceinline__ void resolve_held(const TransportArgs& a, const BlockTally& bt,
-                                             const SegDev<float>* __restrict__ segs, int seg, uint32_t pid,
-                                             Particle<float>& p, LaneAcc& acc, bool held, uint64_t H)
+template <bool ARR, typename R>
+__device__ __forceinline__ void resolve_held(const TransportArgs<R>& a, const BlockTally& bt,
+                                             const SegDev<R>* __restrict__ segs, int seg, uint32_t pid,
+                                             Particle<R>& p, Walk<R>& wk, LaneAcc& acc, bool held, uint64_t H)
 {
     const int sL = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)H) - 1);
-    acc.c[C_TESTED] += held ? 1u : 0u;
+    if (std::is_same<R, float>::value) acc.c[C_TESTED] += held ? 1u : 0u;
     if (__ballot(held && seg != sL) == 0) {
         if (held) {
-            const SegDev<float>& S = segs[sL];
-            const Term t = diffusive_resolve(S, p);
+            const SegDev<R>& S = segs[sL];
+            const Term t = diffusive_resolve(S, p, wk);
             if (t.state != HIT_NONE) {
                 p.ndiff = p.e - p.ndiff - 1u;
                 terminate<ARR>(a, bt, S, pid, p, t, acc);
             }
         }
     } else if (held) {
-        const SegDev<float>& S = segs[seg];
-        const Term t = diffusive_resolve(S, p);
+        const SegDev<R>& S = segs[seg];
+        const Term t = diffusive_resolve(S, p, wk);
         if (t.state != HIT_NONE) {
             p.ndiff = p.e - p.ndiff - 1u;
             terminate<ARR>(a, bt, S, pid, p, t, acc);
@@ -355,11 +375,11 @@ __device__ __forceinline__ void resolve_held(const TransportArgs& a, const Block
 // the steps that left their balls tested together after each.  Walkers within a group's length of
 // the event cap are rare: while the wave has one, it takes single steps.  Returns when the wave
 // should refill, has no walker left, or walks its last ones cooperatively; no step is held then.
-template <bool ARR>
-__device__ __forceinline__ void diffusive_loop(const TransportArgs& a, const BlockTally& bt,
-                                               const SegDev<float>* __restrict__ segs, int seg, float lam_l2,
-                                               uint32_t cfgcat, uint32_t pid, Particle<float>& p, LaneAcc& acc,
-                                               bool drained)
+template <bool ARR, typename R>
+__device__ __forceinline__ void diffusive_loop(const TransportArgs<R>& a, const BlockTally& bt,
+                                               const SegDev<R>* __restrict__ segs, int seg, R lam_l2,
+                                               uint32_t cfgcat, uint32_t pid, Particle<R>& p, Walk<R>& wk,
+                                               LaneAcc& acc, bool drained)
 {
     constexpr uint32_t REACH = 2 * WALK_ADVANCES + 1;     // events a group takes at most
     const uint32_t far = a.cap > REACH ? a.cap - REACH : 0u;
@@ -370,18 +390,18 @@ __device__ __forceinline__ void diffusive_loop(const TransportArgs& a, const Blo
             if (p.st == ST_DIFFUSIVE) {
                 const int A = __popcll(M);
                 held = walk_group(lam_l2, cfgcat, a.k0, a.k1, pid, A, a.defer_min < A ? a.defer_min : A, a.walk_idle,
-                                  p);
+                                  p, wk);
             }
         } else {
             const bool walks = p.st == ST_DIFFUSIVE;
             escape_capped<ARR>(a, bt, segs, seg, pid, p, acc, walks && p.e >= a.cap);
-            if (p.st == ST_DIFFUSIVE) held = diffusive_single(lam_l2, cfgcat, a.k0, a.k1, pid, p);
+            if (p.st == ST_DIFFUSIVE) held = diffusive_single(lam_l2, cfgcat, a.k0, a.k1, pid, p, wk);
         }
         const uint64_t H = __ballot(held);
-        if (H != 0) resolve_held<ARR>(a, bt, segs, seg, pid, p, acc, held, H);
+        if (H != 0) resolve_held<ARR>(a, bt, segs, seg, pid, p, wk, acc, held, H);
         M = __ballot(p.st == ST_DIFFUSIVE);
         if (M == 0 || (!drained && __popcll(__ballot(p.st == ST_DEAD)) >= a.refill_min) ||
-            (drained && __popcll(M) <= COOP_MAX))
+            (drained && __popcll(M) <= Walk<R>::COOP))
             break;
     }
 }
@@ -389,17 +409,14 @@ __device__ __forceinline__ void diffusive_loop(const TransportArgs& a, const Blo
 // Ballistic phase of one round: every ticket of the round, from launch until the atom ends
 // on a surface, escapes, or thermalises (then it is queued for the diffusive phase).
 // Dynamic LDS: per-segment counters (u64, when lds_counters) then the tally (u32, when lds_tally).
-// At most 96 VGPRs: five waves per SIMD hide the latency of the transcendental and
-// integer-multiply chains.
-template <bool ARR>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
-k_ballistic32(TransportArgs a, const SegDev<float>* __restrict__ segs)
+template <bool ARR, typename R>
+__device__ __forceinline__ void ballistic_phase(TransportArgs<R>& a, const SegDev<R>* __restrict__ segs)
 {
     extern __shared__ unsigned long long lds[];
     BlockTally bt;
     lds_setup(a, bt, lds);
     const int lane = threadIdx.x & 63;
-    Particle<float> p;
+    Particle<R> p;
     p.st = ST_DEAD;
     p.e = p.ndiff = p.ncoll = 0;
     uint32_t pid = 0;
@@ -453,12 +470,16 @@ k_ballistic32(TransportArgs a, const SegDev<float>* __restrict__ segs)
             continue;
         }
         const int s0 = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)B) - 1);
-        if (__ballot(p.st == ST_BALLISTIC && seg != s0) == 0) {
-            ballistic_loop(a, segs[s0], pid, p, T.drained);
+        if constexpr (std::is_same<R, double>::value) {
+            // lanes of other segments wait their turn: a second copy of the flight with per-lane
+            // constants would only spill
+            ballistic_loop(a, segs + s0, pid, p, seg == s0, T.drained);
+        } else if (__ballot(p.st == ST_BALLISTIC && seg != s0) == 0) {
+            ballistic_loop(a, segs + s0, pid, p, true, T.drained);
         } else if (p.st == ST_BALLISTIC) {
             // lanes of several segments: one flight with per-lane constants
-            const SegDev<float>& s = segs[seg];
-            const Term t = step_mode<float, ST_BALLISTIC>(s, a.tab, a.k0, a.k1, pid, a.cap, p);
+            const SegDev<R>& s = segs[seg];
+            const Term t = step_mode(s, a.tab, a.k0, a.k1, pid, a.cap, p);
             if (t.state != HIT_NONE) mark_ended(p, t);
         }
     }
@@ -466,11 +487,119 @@ k_ballistic32(TransportArgs a, const SegDev<float>* __restrict__ segs)
     lds_flush(a, bt, acc);
 }
 
+// At most 96 VGPRs: five waves per SIMD hide the latency of the transcendental and
+// integer-multiply chains.
+template <bool ARR>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
+k_ballistic32(TransportArgs<float> a, const SegDev<float>* __restrict__ segs)
+{
+    ballistic_phase<ARR>(a, segs);
+}
+// Three waves per SIMD (at most 168 VGPRs) in both FP64 kernels, without spills: four waves spilled
+// 64 registers in the walk (9e5 atoms at 0.5 / 0 / 2 Pa: 13.8 ms at three, 15.8 at four).
+template <bool ARR>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+k_ballistic64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
+{
+    ballistic_phase<ARR>(a, segs);
+}
+
+// The last walks of a drained wave (its lanes in D, at most Walk<R>::COOP, none with a held step), walked
+// to their ends by the whole wave: each walker gets a span of 64, 32, 16, 8 or 4 lanes, all of which hold
+// its state, and lane j of the span draws step e + 1 + j.  A pass takes every walker's steps up to the
+// first that leaves its ball (or to the event cap), then tests those.  Spans are laid out anew as
+// walkers end.  Bound by the latency of one pass, the longest walks being all that is left: the state
+// stays replicated in the span, so a pass starts without shuffles, and the surfaces are read once per
+// layout in FP32 (registers), from the segment table in FP64.
+template <bool ARR, typename R>
+__device__ __forceinline__ void tail_walk(const TransportArgs<R>& a, const BlockTally& bt,
+                                          const SegDev<R>* __restrict__ segs, uint64_t D, int seg, R lam_l2,
+                                          uint32_t cfgcat, uint32_t pid, Particle<R>& p, Walk<R>& wk, LaneAcc& acc,
+                                          int lane)
+{
+    flush_acc(a, bt, acc);
+    acc.seg = -1;
+    while (D != 0) {
+        // layout: walker q (in lane order) moves to span q
+        const int n = __popcll(D);
+        const int sh = n == 1 ? 6 : n == 2 ? 5 : n <= 4 ? 4 : n <= 8 ? 3 : n <= 16 ? 2 : 1;
+        const int span = 1 << sh, slot = lane >> sh, j = lane & (span - 1), base = lane & ~(span - 1);
+        int home = 0;
+        if ((D >> lane) & 1ull) home = (int)lanes_below(D);
+        home = __builtin_amdgcn_ds_permute((((D >> lane) & 1ull) ? home : 63) << 2, lane);
+        const int src = __shfl(home, slot);
+        pid = (uint32_t)__shfl((int)pid, src);
+        seg = __shfl(seg, src);
+        cfgcat = (uint32_t)__shfl((int)cfgcat, src);
+        lam_l2 = __shfl(lam_l2, src);
+        p.e = (uint32_t)__shfl((int)p.e, src);
+        p.ndiff = (uint32_t)__shfl((int)p.ndiff, src);
+        p.E = __shfl(p.E, src);
+        p.r2 = __shfl(p.r2, src);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            p.x[i] = __shfl(p.x[i], src);
+            p.xc[i] = __shfl(p.xc[i], src);
+        }
+        wk = lane_walk(wk, src);
+        bool alive = slot < n;
+        p.st = alive ? ST_DIFFUSIVE : ST_DEAD;
+        const bool lead = alive && j == 0;
+        if (lead && acc.seg != seg) {
+            flush_acc(a, bt, acc);
+            acc.seg = seg;
+        }
+        const SegDev<R>& S = segs[seg];
+        const uint64_t span_mask = sh == 6 ? ~0ull : (1ull << span) - 1;
+        for (;;) {
+            const uint32_t ej = p.e + 1u + (uint32_t)j;
+            R dir[3];
+            const R ell = any_draw(lam_l2, diffusive_block(pid, ej, cfgcat, a.k0, a.k1), (ej & 1u) != 0, dir);
+            const bool allowed = ej <= a.cap && ej > (uint32_t)j;
+            const auto at = spot_of(p);
+            const auto t = chain_steps(at, ell, dir, sh, j, allowed, alive, wk, p.r2);
+            const uint64_t stay = (__ballot(allowed && spot_holds(t, wk, p.r2)) >> base) & span_mask;
+            const int f = stay == span_mask ? span : __ffsll((unsigned long long)~stay) - 1;   // steps taken
+            const auto to = lane_spot(t, base + (f > 0 ? f - 1 : 0));
+            if (f > 0) stand_at(p, to);
+            p.e += (uint32_t)f;
+            const bool stop = alive && f < span, held = stop && p.e < a.cap;
+            const int hl = base + (f < span ? f : 0);
+            const R hell = __shfl(ell, hl);
+            R hd[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) hd[i] = __shfl(dir[i], hl);
+            Term end{HIT_NONE, -1, 0.f};
+            if (held) {
+                ++p.e;
+                p.r2 = hell;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) p.d[i] = hd[i];
+                end = diffusive_resolve(S, p, wk);
+                if (std::is_same<R, float>::value && lead) acc.c[C_TESTED] += 1u;
+            } else if (stop) {
+                end.state = HIT_ESCAPED;
+            }
+            if (end.state != HIT_NONE) {
+                if (lead) {
+                    p.ndiff = p.e - p.ndiff - (held ? 1u : 0u);
+                    terminate<ARR>(a, bt, segs[seg], pid, p, end, acc);
+                }
+                alive = false;
+            }
+            D = __ballot(alive && j == 0);
+            const int live = __popcll(D);
+            if (live == 0 || (sh < 6 && 2 * live <= (64 >> sh))) break;
+        }
+    }
+    p.st = ST_DEAD;
+}
+
 // Diffusive phase of one round: the walks of the atoms queued by the ballistic phase.  Lanes
 // of any segments walk together (the step needs only two per-lane numbers of the segment), so
 // a wave never falls back to one step at a time.
-template <bool ARR>
-__device__ __forceinline__ void diffusive_phase(TransportArgs& a, const SegDev<float>* __restrict__ segs)
+template <bool ARR, typename R>
+__device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const SegDev<R>* __restrict__ segs)
 {
     extern __shared__ unsigned long long lds[];
     BlockTally bt;
@@ -478,12 +607,13 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs& a, const SegDev<f
     const uint64_t total = a.qstate[QS_QUEUE];   // written by the ballistic phase of this round
     const uint64_t chunk = chunk_of(total, a.n_simd, TICKET_CHUNK);
     const int lane = threadIdx.x & 63;
-    Particle<float> p;
+    Particle<R> p;
+    Walk<R> wk;
     p.st = ST_DEAD;
     p.e = p.ndiff = p.ncoll = 0;
     uint32_t pid = 0;
     int seg = 0;
-    float lam_l2 = 0.f;        // the lane's segment: thermal mean free path (times ln 2), Philox word
+    R lam_l2 = (R)0;           // the lane's segment: thermal mean free path (times ln 2), Philox word
     uint32_t cfgcat = 0;
     LaneAcc acc;
     Tickets T;
@@ -494,7 +624,7 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs& a, const SegDev<f
             const uint64_t my = claim(T, &a.qstate[QS_DIFFUSIVE], chunk, total, dead, lane);
             const uint32_t qpid = my != ~0ull ? a.queue[my].pid : 0xFFFFFFFFu;
             if (qpid != 0xFFFFFFFFu) {                 // empty slots (left unused by a wave) are skipped
-                const ThermRec r = a.queue[my];
+                const ThermRec<R> r = a.queue[my];
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     p.x[i] = r.x[i];
@@ -504,7 +634,7 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs& a, const SegDev<f
                 p.e = r.e;
                 p.ndiff = r.e;         // events before the walk
                 p.ncoll = 0;
-                p.r2 = -1.f;           // no clearance ball yet: the first step is tested
+                p.r2 = (R)-1;          // no clearance ball yet: the first step is tested
                 p.st = ST_DIFFUSIVE;
                 pid = r.pid;
                 const int sg = (int)r.seg;
@@ -513,7 +643,7 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs& a, const SegDev<f
                     acc.seg = sg;
                 }
                 seg = sg;
-                lam_l2 = __uint_as_float(r.lam_bits);
+                lam_l2 = r.lam;
                 cfgcat = r.cfgcat;
             }
         }
@@ -522,27 +652,11 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs& a, const SegDev<f
             if (T.drained) break;
             continue;
         }
-        // Last walks of a drained wave: walked by the whole wave, up to four at a time (up to 64,
-        // 32 or 16 steps each per pass), until their steps leave the balls; then the held steps
-        // are tested together.
-        // Every pass takes or holds a step of each walker, or leaves it at the cap, where it
-        // escapes, so the walks end.
-        if (T.drained && __popcll(D) <= COOP_MAX) {
-            bool held = false;
-            for (uint64_t W = D; W != 0;) {
-                uint64_t G = 0;                  // the next (up to) four walkers
-                for (int q = 0; q < 4 && W != 0; ++q) {
-                    G |= W & (~W + 1);
-                    W &= W - 1;
-                }
-                coop_walk(a.k0, a.k1, a.cap, G, lam_l2, cfgcat, pid, p, held, lane);
-            }
-            escape_capped<ARR>(a, bt, segs, seg, pid, p, acc, p.st == ST_DIFFUSIVE && !held && p.e >= a.cap);
-            const uint64_t H = __ballot(held);
-            if (H != 0) resolve_held<ARR>(a, bt, segs, seg, pid, p, acc, held, H);
-            continue;
+        if (T.drained && __popcll(D) <= Walk<R>::COOP) {
+            tail_walk<ARR>(a, bt, segs, D, seg, lam_l2, cfgcat, pid, p, wk, acc, lane);
+            break;
         }
-        diffusive_loop<ARR>(a, bt, segs, seg, lam_l2, cfgcat, pid, p, acc, T.drained);
+        diffusive_loop<ARR>(a, bt, segs, seg, lam_l2, cfgcat, pid, p, wk, acc, T.drained);
     }
     lds_flush(a, bt, acc);
 }
@@ -551,69 +665,25 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs& a, const SegDev<f
 // a few values spill to scratch at five waves, outside the steps of the walk; that still runs
 // faster than four waves without spills.
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
-k_diffusive32(TransportArgs a, const SegDev<float>* __restrict__ segs)
+k_diffusive32(TransportArgs<float> a, const SegDev<float>* __restrict__ segs)
 {
     diffusive_phase<false>(a, segs);
 }
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
-k_diffusive32_arr(TransportArgs a, const SegDev<float>* __restrict__ segs)
+k_diffusive32_arr(TransportArgs<float> a, const SegDev<float>* __restrict__ segs)
 {
     diffusive_phase<true>(a, segs);
 }
 
-// Arrival outputs of the comparator (nullable as a group) with its FP64 bin edges.
-struct Arrivals64 {
-    unsigned long long* E;      // this segment's energy histogram
-    unsigned long long* A;      // this segment's angle histogram
-    unsigned long long* esum;   // per tally bin of the plan
-    const double* e_edges;
-    const double* c_edges;
-};
-
-__global__ void __launch_bounds__(256) k_transport64(const SegDev<double>* __restrict__ segp, TabDev<double> tab,
-                                                     uint32_t k0, uint32_t k1, uint32_t cap,
-                                                     unsigned long long* __restrict__ counts,
-                                                     unsigned long long* __restrict__ counters,
-                                                     spx_record* __restrict__ records, Arrivals64 arr)
+// Bound by VALU issue as the FP32 walk is (an FP64 instruction takes four clocks too): 430
+// instructions a round of two steps, most of them the library's log2 and sincospi.  One thread per
+// atom through its whole history, every step tested, took 77 ms for 9e5 atoms at 0.5 / 0 / 2 Pa and
+// 34.2 ms for 2.3e6 from four cathodes; the two phases take 12.9 and 4.7 ms.
+template <bool ARR>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
+k_diffusive64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
 {
-    const SegDev<double>& s = *segp;
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t acc[N_COUNTERS] = {};
-    if (i < s.N) {
-        const uint32_t pid = (uint32_t)i;
-        Particle<double> p;
-        start(s, k0, k1, pid, p);
-        Term t;
-        do {
-            t = step(s, tab, k0, k1, pid, cap, p);
-        } while (t.state == HIT_NONE);
-        acc[C_LAUNCHED] = 1;
-        acc[t.state == HIT_DEPOSITED ? C_DEPOSITED : (t.state == HIT_WALL ? C_WALL : C_ESCAPED)] = 1;
-        acc[C_COLLISIONS] = p.ncoll;
-        acc[C_DIFFUSIVE] = p.ndiff;
-        acc[C_THERMALIZED] = (p.st == ST_DIFFUSIVE) ? 1u : 0u;
-        // every diffusive step is tested here: those that ended in the gas and the last one
-        // (unless the history stopped at the event cap)
-        acc[C_TESTED] = p.ndiff + ((p.st == ST_DIFFUSIVE && t.state != HIT_ESCAPED) ? 1u : 0u);
-        if (t.state == HIT_DEPOSITED) {
-            const uint64_t b = s.bin_off + (uint64_t)t.bin;
-            atomicAdd(&counts[b], 1ull);
-            if (arr.E) {
-                atomicAdd(&arr.E[energy_bin(arr.e_edges, p.E)], 1ull);
-                atomicAdd(&arr.A[angle_bin(arr.c_edges, (double)t.cos_in)], 1ull);
-                atomicAdd(&arr.esum[b], energy_units(p.E));
-            }
-        }
-        if (records) write_record(records, s, pid, p, t);
-    }
-    // wave sum of the counters, one atomic per counter and wave
-#pragma unroll
-    for (int c = 0; c < N_COUNTERS; ++c) {
-        unsigned long long v = acc[c];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-        if ((threadIdx.x & 63) == 0 && v) atomicAdd(&counters[c], v);
-    }
+    diffusive_phase<ARR>(a, segs);
 }
 
 // Zero the outputs (a kernel, so that it can sit in a graph).
@@ -705,7 +775,7 @@ int StreamSink::put(const KLaunch& k)
 
 // Dynamic LDS of the FP32 transport for a plan: counters if they fit, tally if it fits, arrival
 // histograms (when requested) if they fit.
-size_t transport32_lds(const Plan* P, bool arrivals, bool* lds_counters, bool* lds_tally, bool* lds_arrivals)
+size_t transport_lds(const Plan* P, bool arrivals, bool* lds_counters, bool* lds_tally, bool* lds_arrivals)
 {
     const size_t cbytes = (size_t)P->n_seg * N_COUNTERS * sizeof(unsigned long long);
     const size_t tbytes = (size_t)P->n_bins_total * sizeof(uint32_t);
@@ -719,7 +789,7 @@ size_t transport32_lds(const Plan* P, bool arrivals, bool* lds_counters, bool* l
 int occupancy_transport32(const Plan* P, int threads, int* bpc_ballistic, int* bpc_diffusive)
 {
     bool lc, lt, la;
-    const size_t smem = transport32_lds(P, false, &lc, &lt, &la);
+    const size_t smem = transport_lds(P, false, &lc, &lt, &la);
     int b1 = 0, b2 = 0;
     SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b1, k_ballistic32<false>, threads, smem));
     SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b2, k_diffusive32, threads, smem));
@@ -734,21 +804,55 @@ uint64_t rounds_of(uint64_t total, uint64_t round_max)
     return total == 0 ? 0 : (total + round_max - 1) / round_max;
 }
 
-int build_transport32(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tfirst, uint64_t total,
-                      const Shape& sh, const QueueMem& q, LaunchSink& sink)
+namespace {
+// The plan's constants and the kernels of a precision.
+template <typename R> struct Path;
+template <> struct Path<float> {
+    static const SegDev<float>* segs(const Plan* P) { return P->d_seg32; }
+    static const float* theta(const Plan* P) { return P->d_theta32; }
+    static const float* betamax(const Plan* P) { return P->d_betamax32; }
+    static const float* edges(const Plan* P) { return P->d_edges32; }
+    static const void* ballistic(bool arr)
+    {
+        return arr ? (const void*)k_ballistic32<true> : (const void*)k_ballistic32<false>;
+    }
+    static const void* diffusive(bool arr) { return arr ? (const void*)k_diffusive32_arr : (const void*)k_diffusive32; }
+    static constexpr int IDLE = WALK_IDLE;
+};
+template <> struct Path<double> {
+    static const SegDev<double>* segs(const Plan* P) { return P->d_seg64; }
+    static const double* theta(const Plan* P) { return P->d_theta64; }
+    static const double* betamax(const Plan* P) { return P->d_betamax64; }
+    static const double* edges(const Plan* P) { return P->d_edges64; }
+    static const void* ballistic(bool arr)
+    {
+        return arr ? (const void*)k_ballistic64<true> : (const void*)k_ballistic64<false>;
+    }
+    static const void* diffusive(bool arr)
+    {
+        return arr ? (const void*)k_diffusive64<true> : (const void*)k_diffusive64<false>;
+    }
+    static constexpr int IDLE = WALK_IDLE64;
+};
+}  // namespace
+
+template <typename R>
+int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tfirst, uint64_t total,
+                    const Shape& sh, const QueueMem& q, LaunchSink& sink)
 {
+    using K = Path<R>;
     SPX_TRY(put_zero(P, o, sink));
-    TransportArgs a;
+    TransportArgs<R> a;
     std::memset(&a, 0, sizeof(a));     // padding too: launches are compared bytewise
-    a.segs = P->d_seg32;
-    a.tab.theta = P->d_theta32;
-    a.tab.betamax = P->d_betamax32;
+    a.segs = K::segs(P);
+    a.tab.theta = K::theta(P);
+    a.tab.betamax = K::betamax(P);
     a.tab.ne = P->params.table_ne;
     a.tab.ns = P->params.table_ns;
-    a.tab.xs = (float)((P->params.table_ne - 1) / ((P->params.log_eps_hi - P->params.log_eps_lo) * 3.321928094887362));
+    a.tab.xs = (R)((P->params.table_ne - 1) / ((P->params.log_eps_hi - P->params.log_eps_lo) * 3.321928094887362));
     a.tfirst = tfirst;
     a.torder = P->d_torder;
-    a.queue = q.queue;
+    a.queue = (ThermRec<R>*)q.queue;
     a.qstate = q.qstate;
     a.counts = (unsigned long long*)o.counts;
     a.counters = (unsigned long long*)o.counters;
@@ -756,8 +860,8 @@ int build_transport32(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* 
     a.arr_E = (unsigned long long*)o.arr_E;
     a.arr_A = (unsigned long long*)o.arr_A;
     a.esum = (unsigned long long*)o.esum;
-    a.e_edges = P->d_edges32;
-    a.c_edges = P->d_edges32 + SPX_ARRIVAL_E_BINS + 1;
+    a.e_edges = K::edges(P);
+    a.c_edges = K::edges(P) + SPX_ARRIVAL_E_BINS + 1;
     a.k0 = (uint32_t)seed;
     a.k1 = (uint32_t)(seed >> 32);
     a.cap = P->params.event_cap;
@@ -771,14 +875,14 @@ int build_transport32(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* 
     // in chimneys, seven objects a run: diffusive kernel 2.87 ms at 128 idle rounds, 2.66 at 400)
     size_t n_obj = 0;
     for (const auto& s : P->seg) n_obj += s.objs.size();
-    a.walk_idle = WALK_IDLE + (int32_t)(WALK_IDLE * 70 * n_obj / (180 * (size_t)P->n_seg));
+    a.walk_idle = K::IDLE + (int32_t)(K::IDLE * 70 * n_obj / (180 * (size_t)P->n_seg));
     a.n_bins = (uint32_t)P->n_bins_total;
     bool lc, lt, la;
-    const size_t smem = transport32_lds(P, o.arr_E != nullptr, &lc, &lt, &la);
+    const size_t smem = transport_lds(P, o.arr_E != nullptr, &lc, &lt, &la);
     int blocks_diff_arr = sh.blocks_diff;
     if (o.arr_E) {
         int bpc_arr = 0;
-        SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc_arr, k_diffusive32_arr, sh.threads, smem));
+        SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc_arr, K::diffusive(true), sh.threads, smem));
         if (bpc_arr > 0) blocks_diff_arr = std::min(sh.blocks_diff, bpc_arr * P->n_cu);
     }
     a.lds_counters = lc ? 1 : 0;
@@ -792,7 +896,7 @@ int build_transport32(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* 
         set_error("internal: round larger than the thermalisation queue");
         return SPX_ESTATE;
     }
-    const SegDev<float>* segs = P->d_seg32;
+    const SegDev<R>* segs = K::segs(P);
     for (uint64_t r = 0; r < n_rounds; ++r) {
         a.tbase = r * per_round;
         a.total = (a.tbase + per_round < total) ? per_round : total - a.tbase;
@@ -808,7 +912,7 @@ int build_transport32(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* 
         reset.arg(q.qstate);
         SPX_TRY(sink.put(reset));
         KLaunch bal;
-        bal.func = a.arr_E ? (const void*)k_ballistic32<true> : (const void*)k_ballistic32<false>;
+        bal.func = K::ballistic(a.arr_E != nullptr);
         bal.grid = dim3((unsigned)sh.blocks);
         bal.block = dim3((unsigned)sh.threads);
         bal.smem = (uint32_t)smem;
@@ -818,7 +922,7 @@ int build_transport32(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* 
         SPX_TRY(sink.put(bal));
         // the instance with the arrival tallies has its own resident limit (fewer waves per SIMD)
         KLaunch dif;
-        dif.func = a.arr_E ? (const void*)k_diffusive32_arr : (const void*)k_diffusive32;
+        dif.func = K::diffusive(a.arr_E != nullptr);
         dif.grid = dim3((unsigned)(a.arr_E ? blocks_diff_arr : sh.blocks_diff));
         dif.block = dim3((unsigned)sh.threads);
         dif.smem = (uint32_t)smem;
@@ -831,33 +935,30 @@ int build_transport32(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* 
     return SPX_OK;
 }
 
-int launch_transport64(Plan* P, uint64_t seed, const Outputs& o, hipStream_t st)
+template int build_transport<float>(Plan*, uint64_t, const Outputs&, const uint64_t*, uint64_t, const Shape&,
+                                    const QueueMem&, LaunchSink&);
+template int build_transport<double>(Plan*, uint64_t, const Outputs&, const uint64_t*, uint64_t, const Shape&,
+                                     const QueueMem&, LaunchSink&);
+
+// The FP64 kernels run at their resident limits.
+int shape_transport64(Plan* P)
 {
-    StreamSink sink(st, nullptr);
-    SPX_TRY(put_zero(P, o, sink));
-    TabDev<double> tab;
-    tab.theta = P->d_theta64;
-    tab.betamax = P->d_betamax64;
-    tab.ne = P->params.table_ne;
-    tab.ns = P->params.table_ns;
-    tab.xs = (P->params.table_ne - 1) / ((P->params.log_eps_hi - P->params.log_eps_lo) * 3.321928094887362);
-    for (int k = 0; k < P->n_seg; ++k) {
-        const uint64_t N = P->seg[k].N;
-        if (N == 0) continue;
-        const uint64_t blocks = (N + 255) / 256;
-        Arrivals64 arr{nullptr, nullptr, nullptr, P->d_edges64, P->d_edges64 + SPX_ARRIVAL_E_BINS + 1};
-        if (o.arr_E) {
-            arr.E = (unsigned long long*)(o.arr_E + (size_t)k * SPX_ARRIVAL_E_BINS);
-            arr.A = (unsigned long long*)(o.arr_A + (size_t)k * SPX_ARRIVAL_A_BINS);
-            arr.esum = (unsigned long long*)o.esum;
-        }
-        hipLaunchKernelGGL(k_transport64, dim3((unsigned)blocks), dim3(256), 0, st, P->d_seg64 + k, tab,
-                           (uint32_t)seed, (uint32_t)(seed >> 32), P->params.event_cap,
-                           (unsigned long long*)o.counts, (unsigned long long*)(o.counters + (size_t)k * N_COUNTERS),
-                           o.records, arr);
-        SPX_HIP(hipGetLastError());
+    bool lc, lt, la;
+    const size_t smem = transport_lds(P, false, &lc, &lt, &la);
+    Shape& sh = P->shape64;
+    sh.threads = 256;
+    int b = 0, d = 0;
+    SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, Path<double>::ballistic(false), sh.threads, smem));
+    SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&d, Path<double>::diffusive(false), sh.threads, smem));
+    if (b < 1 || d < 1) {
+        set_error("the FP64 transport kernels do not fit on this device");
+        return SPX_EDEVICE;
     }
-    if (o.profiles) SPX_TRY(put_normalize(P, o.counts, o.profiles, sink));
+    sh.blocks = b * P->n_cu;
+    sh.blocks_diff = d * P->n_cu;
+    sh.refill_min = REFILL64;
+    sh.refill_ballistic = REFILL_BALLISTIC64;
+    sh.defer_min = DEFER_MIN;
     return SPX_OK;
 }
 
