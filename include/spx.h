@@ -332,6 +332,19 @@ int spx_comp_backward(const float* d_f, const float* d_a, const float* d_b, cons
                       float* d_gf, float* d_ga, float* d_gb, float* d_gP, float* d_gM, float* d_grho,
                       float* d_gfref, int32_t B, int32_t J, int32_t K, void* stream);
 
+/* spx_comp_backward in one pass over d_gc, with scratch of the caller: d_scratch float[n_scratch],
+ * n_scratch at least spx_comp_backward_scratch(B, J, K), device memory no other work on another
+ * stream uses meanwhile.  Same outputs (the sums over areas and powers in another fixed order).
+ * SPX_EINVAL also for a smaller scratch and where spx_comp_backward_scratch is 0. */
+int spx_comp_backward_with(const float* d_f, const float* d_a, const float* d_b, const float* d_P,
+                           const float* d_M, const float* d_rho, const float* d_fref, const float* d_gc,
+                           float* d_gf, float* d_ga, float* d_gb, float* d_gP, float* d_gM, float* d_grho,
+                           float* d_gfref, float* d_scratch, uint64_t n_scratch, int32_t B, int32_t J, int32_t K,
+                           void* stream);
+/* Floats of scratch spx_comp_backward_with needs; 0 where it does not apply (K > 8, J > 1536 or
+ * invalid sizes): use spx_comp_backward there. */
+uint64_t spx_comp_backward_scratch(int32_t B, int32_t J, int32_t K);
+
 /* Squared Euclidean distance of compositions summed over areas (Results, d_e):
  * d_loss[b] = sum_{j,k} (c[b,j,k] - ct[b or 0,j,k])^2; ct has B_t = 1 or B rows.
  * If d_gc is non-NULL it also receives d loss_total / d c scaled by d_gloss[b]

@@ -35,6 +35,11 @@ def _stream(stream=None):
     return ctypes.c_void_p(s.cuda_stream)
 
 
+def _torch_stream(stream) -> bool:
+    """Whether torch can order its own work and memory on `stream` (None: the current stream)."""
+    return stream is None or isinstance(stream, _torch().cuda.Stream)
+
+
 def _ptr(t) -> ctypes.c_void_p:
     return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
 
@@ -334,9 +339,17 @@ def comp_backward(f, a, b, P, M, rho, fref, gc, stream=None):
     K, J = f.shape
     B = P.shape[0]
     g = {k: torch.empty_like(v) for k, v in dict(f=f, a=a, b=b, P=P, M=M, rho=rho, fref=fref).items()}
-    check(lib().spx_comp_backward(_ptr(f), _ptr(a), _ptr(b), _ptr(P), _ptr(M), _ptr(rho), _ptr(fref), _ptr(gc),
-                                  _ptr(g["f"]), _ptr(g["a"]), _ptr(g["b"]), _ptr(g["P"]), _ptr(g["M"]),
-                                  _ptr(g["rho"]), _ptr(g["fref"]), B, J, K, _stream(stream)), "spx_comp_backward")
+    ins = [_ptr(t) for t in (f, a, b, P, M, rho, fref, gc)]
+    outs = [_ptr(g[k]) for k in ("f", "a", "b", "P", "M", "rho", "fref")]
+    n = lib().spx_comp_backward_scratch(B, J, K) if _torch_stream(stream) else 0
+    if n:
+        scratch = torch.empty(n, dtype=torch.float32, device=f.device)
+        if stream is not None:
+            scratch.record_stream(stream)      # given back here, still in use there
+        check(lib().spx_comp_backward_with(*ins, *outs, _ptr(scratch), n, B, J, K, _stream(stream)),
+              "spx_comp_backward_with")
+    else:
+        check(lib().spx_comp_backward(*ins, *outs, B, J, K, _stream(stream)), "spx_comp_backward")
     return g
 
 
@@ -366,13 +379,17 @@ def _f64(t):
 def sweep_composition(f, a, b, P, M, rho, stream=None):
     """at.% [T, J, K] (float32) of the T libraries of a sweep: f [T, K, J] float64 area values
     (each library normalised by the mean of its own areas); a, b, P, M, rho [K]."""
+    return _sweep_composition(f, a, b, P, M, rho, stream)
+
+
+def _sweep_composition(f, a, b, P, M, rho, stream=None, out=None):
     torch = _torch()
     f = _f64(f)
     dev = f.device
     a, b, P, M, rho = (_f64(torch.as_tensor(np.asarray(v, dtype=np.float64), device=dev)) if not
                        isinstance(v, torch.Tensor) else _f64(v) for v in (a, b, P, M, rho))
     T, K, J = f.shape
-    c = torch.empty(T, J, K, dtype=torch.float32, device=dev)
+    c = torch.empty(T, J, K, dtype=torch.float32, device=dev) if out is None else out
     check(lib().spx_sweep_composition(_ptr(f), _ptr(a), _ptr(b), _ptr(P), _ptr(M), _ptr(rho), _ptr(c), T, J, K,
                                       _stream(stream)), "spx_sweep_composition")
     return c
@@ -426,13 +443,21 @@ def invert_sweep(plan, out, x, comp, measured, centres=None, half_width: float =
     cen = area_centres() if centres is None else centres
     prof = out["profiles"][:plan.n_segments * nv * nu].view(plan.n_segments, nv, nu)
     f = area_gather(prof, grid, cen, half_width, stream).view(T, K, -1)
-    c = sweep_composition(f, *comp, stream=stream)
-    meas = _f32(measured).reshape(1, c.shape[1], K)
+    J = f.shape[2]
+    # a row more than the sweep: the measured library, so that one launch finds every covered area
+    libs = torch.empty(T + 1, J, K, dtype=torch.float32, device=f.device)
+    c = _sweep_composition(f, *comp, stream=stream, out=libs[:T])
+    meas = _f32(measured).reshape(1, J, K)
     loss = comp_sqdist(c, meas, stream=stream)
     res = dict(f=f, c=c, loss=loss, x_min_de=sweep_fit(x, loss, FIT_MIN, stream=stream))
     if K == 3:
-        area = hull_area(c, stream)
-        area_m = hull_area(meas, stream)
+        if _torch_stream(stream):
+            with torch.cuda.stream(stream):        # None: the current stream
+                libs[T:].copy_(meas)
+            areas = hull_area(libs, stream)
+            area, area_m = areas[:T], areas[T:]
+        else:
+            area, area_m = hull_area(c, stream), hull_area(meas, stream)
         res.update(area=area, area_measured=area_m,
                    x_match_area=sweep_fit(x, area, FIT_MATCH, target=area_m, stream=stream))
     return res

@@ -106,6 +106,8 @@ SIGNATURES = {
     "spx_area_gather": (ctypes.c_int, [_vp, _i32, _i32, _i32, _dbl, _dbl, _vp, _i32, _dbl, _vp, _vp]),
     "spx_comp_forward": (ctypes.c_int, [_vp] * 8 + [_i32, _i32, _i32, _vp]),
     "spx_comp_backward": (ctypes.c_int, [_vp] * 15 + [_i32, _i32, _i32, _vp]),
+    "spx_comp_backward_with": (ctypes.c_int, [_vp] * 16 + [_u64, _i32, _i32, _i32, _vp]),
+    "spx_comp_backward_scratch": (_u64, [_i32, _i32, _i32]),
     "spx_comp_sqdist": (ctypes.c_int, [_vp, _vp, _i32, _vp, _vp, _vp, _i32, _i32, _i32, _vp]),
     "spx_sweep_composition": (ctypes.c_int, [_vp] * 7 + [_i32, _i32, _i32, _vp]),
     "spx_hull_area": (ctypes.c_int, [_vp, _i32, _i32, _vp, _vp]),
