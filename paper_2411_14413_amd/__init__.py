@@ -24,15 +24,27 @@ __all__ = ["Plan", "philox", "area_centres", "area_gather", "comp_forward", "com
            "ESCAPED", "SpxError", "version", "arrival_edges"]
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
-def _stream(stream=None):
+def _stream(stream=None) -> int:
+    """Address of `stream`, or of torch's current stream (asked for without making a Stream object,
+    which took 5 us of every call)."""
+    if stream is not None:
+        return stream.cuda_stream
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _torch_stream(stream) -> bool:
@@ -40,8 +52,8 @@ def _torch_stream(stream) -> bool:
     return stream is None or isinstance(stream, _torch().cuda.Stream)
 
 
-def _ptr(t) -> ctypes.c_void_p:
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+def _ptr(t):
+    return t.data_ptr() if t is not None else None
 
 
 def version() -> int:
@@ -319,53 +331,58 @@ def area_gather(profiles, grid, centres, half_width: float = 2.25, stream=None):
 
 
 def _f32(t):
-    return t.detach().contiguous().float() if t.dtype != _torch().float32 else t.detach().contiguous()
+    """t as the kernels read it (only its memory is used): itself where it is contiguous float32."""
+    if t.dtype is _torch().float32 and t.is_contiguous():
+        return t
+    return t.detach().contiguous().float()
 
 
 def comp_forward(f, a, b, P, M, rho, fref, stream=None):
-    torch = _torch()
     f, a, b, P, M, rho, fref = (_f32(x) for x in (f, a, b, P, M, rho, fref))
     K, J = f.shape
     B = P.shape[0]
-    c = torch.empty(B, J, K, dtype=torch.float32, device=f.device)
+    c = f.new_empty((B, J, K))
     check(lib().spx_comp_forward(_ptr(f), _ptr(a), _ptr(b), _ptr(P), _ptr(M), _ptr(rho), _ptr(fref), _ptr(c), B, J,
                                  K, _stream(stream)), "spx_comp_forward")
     return c
 
 
 def comp_backward(f, a, b, P, M, rho, fref, gc, stream=None):
-    torch = _torch()
     f, a, b, P, M, rho, fref, gc = (_f32(x) for x in (f, a, b, P, M, rho, fref, gc))
     K, J = f.shape
     B = P.shape[0]
-    g = {k: torch.empty_like(v) for k, v in dict(f=f, a=a, b=b, P=P, M=M, rho=rho, fref=fref).items()}
-    ins = [_ptr(t) for t in (f, a, b, P, M, rho, fref, gc)]
-    outs = [_ptr(g[k]) for k in ("f", "a", "b", "P", "M", "rho", "fref")]
+    ins = (f, a, b, P, M, rho, fref)
+    outs = [t.new_empty(t.shape) for t in ins]
+    ptrs = [t.data_ptr() for t in ins] + [gc.data_ptr()] + [t.data_ptr() for t in outs]
     n = lib().spx_comp_backward_scratch(B, J, K) if _torch_stream(stream) else 0
     if n:
-        scratch = torch.empty(n, dtype=torch.float32, device=f.device)
+        scratch = f.new_empty((n,))
         if stream is not None:
             scratch.record_stream(stream)      # given back here, still in use there
-        check(lib().spx_comp_backward_with(*ins, *outs, _ptr(scratch), n, B, J, K, _stream(stream)),
+        check(lib().spx_comp_backward_with(*ptrs, scratch.data_ptr(), n, B, J, K, _stream(stream)),
               "spx_comp_backward_with")
     else:
-        check(lib().spx_comp_backward(*ins, *outs, B, J, K, _stream(stream)), "spx_comp_backward")
-    return g
+        check(lib().spx_comp_backward(*ptrs, B, J, K, _stream(stream)), "spx_comp_backward")
+    return dict(zip(("f", "a", "b", "P", "M", "rho", "fref"), outs))
 
 
 def comp_sqdist(c, ct, gloss=None, want_grad: bool = False, stream=None):
     """Per-row squared Euclidean distance sum_{j,k} (c - ct)^2 and optionally 2 (c - ct) gloss."""
-    torch = _torch()
+    loss, gc = _sqdist(c, ct, gloss, True, want_grad, stream)
+    return (loss, gc) if want_grad else loss
+
+
+def _sqdist(c, ct, gloss, want_loss: bool, want_grad: bool, stream=None):
     c, ct = _f32(c), _f32(ct)
     if ct.dim() == 2:
         ct = ct.unsqueeze(0)
     B, J, K = c.shape
-    loss = torch.empty(B, dtype=torch.float32, device=c.device)
-    gc = torch.empty_like(c) if want_grad else None
+    loss = c.new_empty((B,)) if want_loss else None
+    gc = c.new_empty((B, J, K)) if want_grad else None
     gl = _f32(gloss) if gloss is not None else None
     check(lib().spx_comp_sqdist(_ptr(c), _ptr(ct), ct.shape[0], _ptr(gl), _ptr(loss), _ptr(gc), B, J, K,
                                 _stream(stream)), "spx_comp_sqdist")
-    return (loss, gc) if want_grad else loss
+    return loss, gc
 
 
 # -- inversion over a sweep (Results, cathode-tilt study) --------------------------------------
@@ -495,7 +512,7 @@ def _autograd_classes():
         @staticmethod
         def backward(ctx, gloss):
             c, ct = ctx.saved_tensors
-            _, gc = comp_sqdist(c, ct, gloss=gloss, want_grad=True)
+            _, gc = _sqdist(c, ct, gloss, False, True)
             return gc.to(c.dtype), None
 
     return CompositionMap, SquaredDistance
