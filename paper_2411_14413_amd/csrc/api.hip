@@ -437,6 +437,7 @@ static int create(const spx_config* cfgs, int n_cfgs, const spx_params* prm, Pla
         s.first_rec = first;
         P->h_bin_off.push_back(boff);
         P->h_first.push_back(first);
+        P->has_objects = P->has_objects || !s.objs.empty();
         boff += (uint64_t)s.nu * s.nv;
         first += s.N;
     }

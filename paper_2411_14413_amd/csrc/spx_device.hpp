@@ -353,47 +353,14 @@ __device__ __forceinline__ R lambda_m(const SegDev<R>& s, const TabDev<R>& tb, R
     return m_div(v, nsig * g);
 }
 
-struct HitF {
-    int state;     // HIT_NONE / HIT_DEPOSITED / HIT_WALL
-};
-
-// Nearest surface with 0 < t <= ell; exact ties keep substrate, then cathode, then the
-// absorbing objects in order, then chamber.  Planes use the precomputed n.c, u.c, v.c:
-// t = (n.c - n.x)/(n.d), q.u = u.x + t u.d - u.c.  The fixed surfaces are written without
-// branches (every candidate computed, then selected) so that they form one basic block: a
-// wave runs them once whatever its lanes need, and the loads of the surface constants can be
-// scheduled early; the objects follow in a loop uniform over the segment.  A direction
-// parallel to a plane gives a reciprocal of zero, hence t = inf or NaN, which fails t > 0 as
-// intended.
+// The least of `best` and the distances along d to the objects k0, k0 + dk, ..., both faces: a plane
+// crossing inside the disc or rectangle; for a tube the smaller positive root of |w_perp + t d_perp| =
+// radius whose axial coordinate lies in [0, len].
 template <typename R>
-__device__ __forceinline__ HitF hit_test(const SegDev<R>& s, const R* x, const R* d, R ell, R& t_hit, R& qu_hit,
-                                         R& qv_hit, bool first)
+__device__ __forceinline__ R objects_hit(const SegDev<R>& s, const R* x, const R* d, R best, int k0, int dk)
 {
     const R inf = m_inf<R>();
-    // substrate plate: the front face (moving against its normal) deposits
-    const R dn = dot3(d, s.sub_n);
-    const R ts = (s.sub_nc - dot3(x, s.sub_n)) * m_rcp(dn);
-    const R qu = dot3(x, s.sub_u) + ts * dot3(d, s.sub_u) - s.sub_uc;
-    const R qv = dot3(x, s.sub_v) + ts * dot3(d, s.sub_v) - s.sub_vc;
-    const bool in_s = (s.shape == 0) ? (fabs(qu) <= s.half_u && fabs(qv) <= s.half_v) : (qu * qu + qv * qv <= s.sub_R2);
-    const bool hit_s = (ts > (R)0) && in_s;
-    R best = hit_s ? ts : inf;
-    int state = hit_s ? (dn < (R)0 ? HIT_DEPOSITED : HIT_WALL) : HIT_NONE;
-    qu_hit = qu;
-    qv_hit = qv;
-    // emitting cathode disc (both faces absorb).  The first flight starts on the target
-    // plane and a line meets a plane once, so on that flight the target is not tested.
-    const R dc = dot3(d, s.cat_n);
-    const R tcat = (s.cat_nc - dot3(x, s.cat_n)) * m_rcp(dc);
-    const R cu = dot3(x, s.cat_u) + tcat * dot3(d, s.cat_u) - s.cat_uc;
-    const R cv = dot3(x, s.cat_v) + tcat * dot3(d, s.cat_v) - s.cat_vc;
-    const bool hit_c = !first && (tcat > (R)0) && (tcat < best) && (cu * cu + cv * cv <= s.cat_R2);
-    best = hit_c ? tcat : best;
-    state = hit_c ? HIT_WALL : state;
-    // absorbing objects (both faces): a plane crossing inside the disc or rectangle; for a tube
-    // the smaller positive root of |w_perp + t d_perp| = radius whose axial coordinate lies
-    // in [0, len]
-    for (int k = 0; k < s.n_obj; ++k) {
+    for (int k = k0; k < s.n_obj; k += dk) {
         const ObjDev<R>& o = s.obj[k];
         R to = inf;
         if (o.kind != 2) {
@@ -418,10 +385,128 @@ __device__ __forceinline__ HitF hit_test(const SegDev<R>& s, const R* x, const R
                 else if (t2 > (R)0 && z2 >= (R)0 && z2 <= o.len) to = t2;
             }
         }
-        const bool hit_o = to < best;
-        best = hit_o ? to : best;
-        state = hit_o ? HIT_WALL : state;
+        best = to < best ? to : best;
     }
+    return best;
+}
+
+// The least of `best` and the squared distances from x to the objects k0, k0 + dk, ...
+template <typename R>
+__device__ __forceinline__ R objects_clear2(const SegDev<R>& s, const R* x, R best, int k0, int dk)
+{
+    for (int k = k0; k < s.n_obj; k += dk) {
+        const ObjDev<R>& o = s.obj[k];
+        R d2;
+        if (o.kind != 2) {
+            const R ho = dot3(x, o.n) - o.nc;
+            const R ou = dot3(x, o.u) - o.uc, ov = dot3(x, o.v) - o.vc;
+            R e2;
+            if (o.kind == 0) {
+                const R er = fmax(m_sqrt(ou * ou + ov * ov) - o.hu, (R)0);
+                e2 = er * er;
+            } else {
+                const R eu = fmax(fabs(ou) - o.hu, (R)0), ev = fmax(fabs(ov) - o.hv, (R)0);
+                e2 = eu * eu + ev * ev;
+            }
+            d2 = ho * ho + e2;
+        } else {
+            // open cylinder: radial distance to the wall, plus the axial overhang past a rim
+            const R w[3] = {x[0] - o.c[0], x[1] - o.c[1], x[2] - o.c[2]};
+            const R wa = dot3(w, o.n);
+            const R rp = m_sqrt(fmax(dot3(w, w) - wa * wa, (R)0));
+            const R dr = rp - o.hu;
+            const R off = fmax(fmax(-wa, wa - o.len), (R)0);
+            d2 = dr * dr + off * off;
+        }
+        best = fmin(best, d2);
+    }
+    return best;
+}
+
+// Who goes over the absorbing objects of a test: nobody (a plan without objects has kernels without the
+// loops, and more registers), the lane itself, or the 2^sh lanes of its span, which hold the same x and d
+// (lane j takes objects j, j + 2^sh, ...; the least of all is the same value in any order, and an
+// object's hit wins over another's only in t, never in state).
+struct NoObjects {
+    __device__ __forceinline__ NoObjects(int = 0, int = 0) {}
+    template <typename R> __device__ __forceinline__ R hit(const SegDev<R>&, const R*, const R*, R best) const
+    {
+        return best;
+    }
+    template <typename R> __device__ __forceinline__ R clear2(const SegDev<R>&, const R*, R best) const { return best; }
+};
+struct OwnObjects {
+    template <typename R> __device__ __forceinline__ R hit(const SegDev<R>& s, const R* x, const R* d, R best) const
+    {
+        return objects_hit(s, x, d, best, 0, 1);
+    }
+    template <typename R> __device__ __forceinline__ R clear2(const SegDev<R>& s, const R* x, R best) const
+    {
+        return objects_clear2(s, x, best, 0, 1);
+    }
+};
+struct SpanObjects {
+    int sh, j;
+    __device__ __forceinline__ SpanObjects(int sh_, int j_) : sh(sh_), j(j_) {}
+    template <typename R> __device__ __forceinline__ R hit(const SegDev<R>& s, const R* x, const R* d, R best) const
+    {
+        if (s.n_obj == 0) return best;
+        best = objects_hit(s, x, d, best, j, 1 << sh);
+        for (int o = 1; o < (1 << sh); o <<= 1) {
+            const R u = __shfl_xor(best, o);
+            best = u < best ? u : best;
+        }
+        return best;
+    }
+    template <typename R> __device__ __forceinline__ R clear2(const SegDev<R>& s, const R* x, R best) const
+    {
+        if (s.n_obj == 0) return best;
+        best = objects_clear2(s, x, best, j, 1 << sh);
+        for (int o = 1; o < (1 << sh); o <<= 1) best = fmin(best, __shfl_xor(best, o));
+        return best;
+    }
+};
+
+struct HitF {
+    int state;     // HIT_NONE / HIT_DEPOSITED / HIT_WALL
+};
+
+// Nearest surface with 0 < t <= ell; exact ties keep substrate, then cathode, then the
+// absorbing objects in order, then chamber.  Planes use the precomputed n.c, u.c, v.c:
+// t = (n.c - n.x)/(n.d), q.u = u.x + t u.d - u.c.  The fixed surfaces are written without
+// branches (every candidate computed, then selected) so that they form one basic block: a
+// wave runs them once whatever its lanes need, and the loads of the surface constants can be
+// scheduled early; the objects follow in a loop uniform over the segment.  A direction
+// parallel to a plane gives a reciprocal of zero, hence t = inf or NaN, which fails t > 0 as
+// intended.
+template <typename R, typename O>
+__device__ __forceinline__ HitF hit_test(const SegDev<R>& s, const R* x, const R* d, R ell, R& t_hit, R& qu_hit,
+                                         R& qv_hit, bool first, const O& objects)
+{
+    const R inf = m_inf<R>();
+    // substrate plate: the front face (moving against its normal) deposits
+    const R dn = dot3(d, s.sub_n);
+    const R ts = (s.sub_nc - dot3(x, s.sub_n)) * m_rcp(dn);
+    const R qu = dot3(x, s.sub_u) + ts * dot3(d, s.sub_u) - s.sub_uc;
+    const R qv = dot3(x, s.sub_v) + ts * dot3(d, s.sub_v) - s.sub_vc;
+    const bool in_s = (s.shape == 0) ? (fabs(qu) <= s.half_u && fabs(qv) <= s.half_v) : (qu * qu + qv * qv <= s.sub_R2);
+    const bool hit_s = (ts > (R)0) && in_s;
+    R best = hit_s ? ts : inf;
+    int state = hit_s ? (dn < (R)0 ? HIT_DEPOSITED : HIT_WALL) : HIT_NONE;
+    qu_hit = qu;
+    qv_hit = qv;
+    // emitting cathode disc (both faces absorb).  The first flight starts on the target
+    // plane and a line meets a plane once, so on that flight the target is not tested.
+    const R dc = dot3(d, s.cat_n);
+    const R tcat = (s.cat_nc - dot3(x, s.cat_n)) * m_rcp(dc);
+    const R cu = dot3(x, s.cat_u) + tcat * dot3(d, s.cat_u) - s.cat_uc;
+    const R cv = dot3(x, s.cat_v) + tcat * dot3(d, s.cat_v) - s.cat_vc;
+    const bool hit_c = !first && (tcat > (R)0) && (tcat < best) && (cu * cu + cv * cv <= s.cat_R2);
+    best = hit_c ? tcat : best;
+    state = hit_c ? HIT_WALL : state;
+    const R nearest = objects.hit(s, x, d, best);
+    state = nearest < best ? HIT_WALL : state;
+    best = nearest;
     // chamber: cylinder side (stable root of |x + t d|^2 = R^2 in the xy-plane) and caps
     const R a = d[0] * d[0] + d[1] * d[1];
     const R b = x[0] * d[0] + x[1] * d[1];
@@ -447,7 +532,8 @@ __device__ __forceinline__ HitF hit_test(const SegDev<R>& s, const R* x, const R
 // point-to-region distances, tubes as point-to-open-cylinder distances, the chamber side and
 // caps.  A path that stays closer to x than this cannot
 // meet any surface.
-template <typename R> __device__ __forceinline__ R clearance(const SegDev<R>& s, const R* x)
+template <typename R, typename O>
+__device__ __forceinline__ R clearance(const SegDev<R>& s, const R* x, const O& objects)
 {
     const R h = dot3(x, s.sub_n) - s.sub_nc;
     const R qu = dot3(x, s.sub_u) - s.sub_uc, qv = dot3(x, s.sub_v) - s.sub_vc;
@@ -465,32 +551,7 @@ template <typename R> __device__ __forceinline__ R clearance(const SegDev<R>& s,
     const R ec = fmax(m_sqrt(cu * cu + cv * cv) - m_sqrt(s.cat_R2), (R)0);
     const R d_cat2 = hc * hc + ec * ec;
     R dmin2 = fmin(d_sub2, d_cat2);
-    for (int k = 0; k < s.n_obj; ++k) {
-        const ObjDev<R>& o = s.obj[k];
-        R d2;
-        if (o.kind != 2) {
-            const R ho = dot3(x, o.n) - o.nc;
-            const R ou = dot3(x, o.u) - o.uc, ov = dot3(x, o.v) - o.vc;
-            R e2;
-            if (o.kind == 0) {
-                const R er = fmax(m_sqrt(ou * ou + ov * ov) - o.hu, (R)0);
-                e2 = er * er;
-            } else {
-                const R eu = fmax(fabs(ou) - o.hu, (R)0), ev = fmax(fabs(ov) - o.hv, (R)0);
-                e2 = eu * eu + ev * ev;
-            }
-            d2 = ho * ho + e2;
-        } else {
-            // open cylinder: radial distance to the wall, plus the axial overhang past a rim
-            const R w[3] = {x[0] - o.c[0], x[1] - o.c[1], x[2] - o.c[2]};
-            const R wa = dot3(w, o.n);
-            const R rp = m_sqrt(fmax(dot3(w, w) - wa * wa, (R)0));
-            const R dr = rp - o.hu;
-            const R off = fmax(fmax(-wa, wa - o.len), (R)0);
-            d2 = dr * dr + off * off;
-        }
-        dmin2 = fmin(dmin2, d2);
-    }
+    dmin2 = objects.clear2(s, x, dmin2);
     const R side = m_sqrt(s.ch_R2) - m_sqrt(x[0] * x[0] + x[1] * x[1]);
     const R caps = fmin(x[2] - s.zlo, s.zhi - x[2]);
     return fmin(m_sqrt(dmin2), fmin(side, caps));
@@ -645,7 +706,7 @@ __device__ __forceinline__ Term hit_term(const SegDev<R>& s, int state, R qu, R 
 
 // One ballistic flight of a live particle: event number p.e + 1.  Returns the terminal outcome
 // (HIT_NONE if still in the gas; then p.st tells whether the collision thermalised the atom).
-template <typename R>
+template <typename O, typename R>
 __device__ __forceinline__ Term step_mode(const SegDev<R>& s, const TabDev<R>& tb, uint32_t k0, uint32_t k1,
                                           uint32_t pid, uint32_t cap, Particle<R>& p)
 {
@@ -655,7 +716,7 @@ __device__ __forceinline__ Term step_mode(const SegDev<R>& s, const TabDev<R>& t
     const uint4 r = philox4x32_10(make_uint4(pid, e, s.cfgcat, 0u), k0, k1);
     const R ell = s.vacuum ? m_inf<R>() : -lambda_m(s, tb, p.E) * m_log(u01<R>(r.x));
     R t, qu = (R)0, qv = (R)0;
-    const HitF h = hit_test(s, p.x, p.d, ell, t, qu, qv, e == 1u);
+    const HitF h = hit_test(s, p.x, p.d, ell, t, qu, qv, e == 1u, O());
     // one compensated move: to the surface hit, else the whole flight (a wave whose lanes
     // differ runs the move once)
     const bool hit = h.state != HIT_NONE, finite = ell < m_inf<R>();
@@ -904,13 +965,15 @@ __device__ __forceinline__ bool walk_group(R lam_l2, uint32_t cfgcat, uint32_t k
     return held;
 }
 
-__device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& s, Particle<float>& p, Walk<float>&)
+template <typename O>
+__device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& s, Particle<float>& p, Walk<float>&,
+                                                  const O& objects)
 {
     const float dir[3] = {p.d[0], p.d[1], p.d[2]};
     const float ell = p.r2;
     renormalise(p.x, p.xc);
     float th, qu = 0.f, qv = 0.f;
-    const HitF h = hit_test(s, p.x, dir, ell, th, qu, qv, false);
+    const HitF h = hit_test(s, p.x, dir, ell, th, qu, qv, false, objects);
     if (h.state != HIT_NONE) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) kahan_add(p.x[i], p.xc[i], th * dir[i]);
@@ -918,18 +981,20 @@ __device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& s, Partic
     }
     if (!(ell < m_inf<float>())) return Term{HIT_ESCAPED, -1, 0.f};
     compensated_step(p.x, p.xc, ell, dir);
-    const float c = clearance(s, p.x) - CLEAR_MARGIN;
+    const float c = clearance(s, p.x, objects) - CLEAR_MARGIN;
     p.r2 = c > 0.f ? c * c : -1.f;
     return Term{HIT_NONE, -1, 0.f};
 }
 
 // The same in FP64, with the arithmetic of a step that is always tested.
-__device__ __forceinline__ Term diffusive_resolve(const SegDev<double>& s, Particle<double>& p, Walk<double>& wk)
+template <typename O>
+__device__ __forceinline__ Term diffusive_resolve(const SegDev<double>& s, Particle<double>& p, Walk<double>& wk,
+                                                  const O& objects)
 {
     const double dir[3] = {p.d[0], p.d[1], p.d[2]};
     const double ell = p.r2;
     double th, qu = 0.0, qv = 0.0;
-    const HitF h = hit_test(s, p.x, dir, ell, th, qu, qv, false);
+    const HitF h = hit_test(s, p.x, dir, ell, th, qu, qv, false, objects);
     const bool hit = h.state != HIT_NONE;
     if (!hit && !(ell < m_inf<double>())) return Term{HIT_ESCAPED, -1, 0.f};
     const double mv = hit ? th : ell;
@@ -938,7 +1003,7 @@ __device__ __forceinline__ Term diffusive_resolve(const SegDev<double>& s, Parti
     if (hit) return hit_term(s, h.state, qu, qv, dir);
 #pragma unroll
     for (int i = 0; i < 3; ++i) wk.c[i] = p.x[i];
-    const double c = clearance(s, p.x) - (double)CLEAR_MARGIN;
+    const double c = clearance(s, p.x, objects) - (double)CLEAR_MARGIN;
     p.r2 = c > 0.0 ? c * c : -1.0;
     return Term{HIT_NONE, -1, 0.f};
 }

@@ -134,6 +134,10 @@ constexpr uint64_t TICKET_CHUNK_MIN = 8;     // tickets of either phase a wave c
 // counter; the chunk of a round is also kept small enough for every wave to take several
 constexpr uint64_t TICKET_CHUNK_BALLISTIC_MAX = 512;
 constexpr int DEFER_MIN = 8;                  // default: held diffusive steps that trigger a wave's surface tests
+// Dead lanes a wave refills at, of a plan that is not tuned: four cathodes 6.13 ms (6.35 at 8 and 8, 6.12
+// at 8 and 24), single target 35.8 (36.7, 36.9), half the 64-chamber sweep 93.5 (95.9, 95.2), 2.3e6
+// atoms from four cathodes 1.29 (1.32, 1.28).
+constexpr int REFILL = 4, REFILL_BALLISTIC = 16;
 // Idle rounds of held lanes (summed over the lanes) that one pass of the surface tests is worth
 // without absorbing objects.  Diffusive kernel, single target / four cathodes / half the 64-chamber
 // sweep: 34.5 / 3.46 / 85.7 ms at 64, 33.9 / 3.37 / 84.0 at 128, 34.1 / 3.46 / 84.4 at 192, 35.9 /
@@ -197,7 +201,8 @@ struct LaunchSink {
 
 // Launch geometry and thresholds of the two persistent transport kernels.
 struct Shape {
-    int blocks = 0, blocks_diff = 0, threads = 256, refill_min = 8, refill_ballistic = 8, defer_min = DEFER_MIN;
+    int blocks = 0, blocks_diff = 0, threads = 256, refill_min = REFILL, refill_ballistic = REFILL_BALLISTIC,
+        defer_min = DEFER_MIN;
 };
 
 // Queue of thermalised atoms and ticket counters a run works in: the plan's own allocation, or
@@ -216,6 +221,7 @@ struct spx_plan {
     spx_params params{};
     std::vector<spx::SegHost> seg;
     int n_seg = 0;
+    bool has_objects = false;               // a segment has absorbing objects
     uint64_t n_bins_total = 0, n_particles_total = 0;
     std::vector<uint64_t> h_bin_off, h_first;
     std::vector<double> h_betamax;          // FP64 beta_max table copy (host)
@@ -246,7 +252,8 @@ struct spx_plan {
     double* d_seg_norm = nullptr;           // [n_seg]
     uint64_t n_tickets = 0;
 
-    int blocks = 0, threads = 256, refill_min = 8, refill_ballistic = 8, defer_min = spx::DEFER_MIN;
+    int blocks = 0, threads = 256, refill_min = spx::REFILL, refill_ballistic = spx::REFILL_BALLISTIC,
+        defer_min = spx::DEFER_MIN;
     int blocks_diff = 0;                    // grid of the diffusive kernel: blocks, capped at its resident limit
     int max_blocks_per_cu = 0, n_cu = 0;
 

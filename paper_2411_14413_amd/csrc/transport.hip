@@ -53,7 +53,9 @@ __device__ __forceinline__ void write_record(spx_record* rec, const SegDev<R>& s
 
 // Per-lane bookkeeping of the batched kernel: counters of the lane's current segment,
 // flushed to the block's LDS counters (or HBM) when the lane moves to another segment.
-struct LaneAcc {
+// WALKS: of the diffusive phase, where every history that ends had thermalised, so that this counter
+// is the sum of the endings and needs no register.
+template <bool WALKS> struct LaneAcc {
     int seg = -1;
     uint32_t c[N_COUNTERS] = {};
 };
@@ -84,10 +86,11 @@ __device__ __forceinline__ void tally_arrival(const TransportArgs<R>& a, const B
     atomicAdd(&a.esum[bin], energy_units(E));
 }
 
-template <typename R>
-__device__ __forceinline__ void flush_acc(const TransportArgs<R>& a, const BlockTally& bt, LaneAcc& acc)
+template <typename R, bool WALKS>
+__device__ __forceinline__ void flush_acc(const TransportArgs<R>& a, const BlockTally& bt, LaneAcc<WALKS>& acc)
 {
     if (acc.seg < 0) return;
+    if (WALKS) acc.c[C_THERMALIZED] = acc.c[C_DEPOSITED] + acc.c[C_WALL] + acc.c[C_ESCAPED];
     if (a.lds_counters) {
 #pragma unroll
         for (int i = 0; i < N_COUNTERS; ++i)
@@ -100,21 +103,19 @@ __device__ __forceinline__ void flush_acc(const TransportArgs<R>& a, const Block
 }
 
 // End of a history: counters, tally, optional record; the lane becomes free.
-template <bool ARR, typename R>
+template <bool ARR, typename R, bool WALKS>
 __device__ __forceinline__ void terminate(const TransportArgs<R>& a, const BlockTally& bt, const SegDev<R>& s,
-                                          uint32_t pid, Particle<R>& p, const Term& t, LaneAcc& acc)
+                                          uint32_t pid, Particle<R>& p, const Term& t, LaneAcc<WALKS>& acc)
 {
     // static indices only: the counters stay in registers
     acc.c[C_DEPOSITED] += (t.state == HIT_DEPOSITED) ? 1u : 0u;
     acc.c[C_WALL] += (t.state == HIT_WALL) ? 1u : 0u;
     acc.c[C_ESCAPED] += (t.state == HIT_ESCAPED) ? 1u : 0u;
-    acc.c[C_COLLISIONS] += p.ncoll;
-    acc.c[C_DIFFUSIVE] += p.ndiff;
-    acc.c[C_THERMALIZED] += (p.st == ST_DIFFUSIVE) ? 1u : 0u;
+    if (WALKS) acc.c[C_DIFFUSIVE] += p.ndiff;
+    else acc.c[C_COLLISIONS] += p.ncoll;
     // the FP64 path counts every diffusive step: those that ended in the gas and the last one
     // (unless the history stopped at the event cap); the FP32 path counts at the test
-    if (std::is_same<R, double>::value)
-        acc.c[C_TESTED] += p.ndiff + ((p.st == ST_DIFFUSIVE && t.state != HIT_ESCAPED) ? 1u : 0u);
+    if (WALKS && std::is_same<R, double>::value) acc.c[C_TESTED] += p.ndiff + (t.state != HIT_ESCAPED ? 1u : 0u);
     if (t.state == HIT_DEPOSITED) {
         const uint64_t b = s.bin_off + (uint64_t)t.bin;
         if (a.lds_tally) atomicAdd(&bt.ltally[b], 1u);
@@ -143,6 +144,13 @@ __device__ __forceinline__ uint64_t lanes_below(uint64_t m)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// Lane 0's value, in scalar registers (the whole wave is here).
+__device__ __forceinline__ uint64_t first_lane(uint64_t v)
+{
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
 // Wave-private run of tickets [tk, tk_end), claimed CHUNK at a time from a global counter with
 // one atomic, so that refills rarely touch the counter.
 struct Tickets {
@@ -152,13 +160,14 @@ struct Tickets {
 
 // Tickets for the dead lanes `dead` of the wave: consecutive tickets of the wave's run in lane
 // order.  Returns this lane's ticket, or ~0 when it gets none.
+template <bool SCALAR>
 __device__ __forceinline__ uint64_t claim(Tickets& T, uint64_t* counter, uint64_t chunk, uint64_t total, uint64_t dead,
                                           int lane)
 {
     if (T.tk == T.tk_end) {
         unsigned long long base = 0;
         if (lane == 0) base = atomicAdd((unsigned long long*)counter, (unsigned long long)chunk);
-        base = __shfl(base, 0);
+        base = SCALAR ? first_lane(base) : __shfl(base, 0);
         if (base >= total) {
             T.drained = true;
             return ~0ull;
@@ -190,8 +199,8 @@ __device__ __forceinline__ void lds_setup(const TransportArgs<R>& a, BlockTally&
     __syncthreads();
 }
 
-template <typename R>
-__device__ __forceinline__ void lds_flush(const TransportArgs<R>& a, const BlockTally& bt, LaneAcc& acc)
+template <typename R, bool WALKS>
+__device__ __forceinline__ void lds_flush(const TransportArgs<R>& a, const BlockTally& bt, LaneAcc<WALKS>& acc)
 {
     flush_acc(a, bt, acc);
     __syncthreads();
@@ -223,7 +232,7 @@ struct QRun {
 // collisions are counted here; thermalisation itself is counted when the walk ends.
 template <typename R>
 __device__ __forceinline__ void hand_over(const TransportArgs<R>& a, const SegDev<R>& S, uint32_t pid, int seg,
-                                          Particle<R>& p, LaneAcc& acc, QRun& Q, int lane)
+                                          Particle<R>& p, LaneAcc<false>& acc, QRun& Q, int lane)
 {
     const uint64_t T = __ballot(p.st == ST_DIFFUSIVE);
     if (T == 0) return;
@@ -233,7 +242,7 @@ __device__ __forceinline__ void hand_over(const TransportArgs<R>& a, const SegDe
     if (rem < n) {
         unsigned long long b = 0;
         if (lane == 0) b = atomicAdd((unsigned long long*)&a.qstate[QS_QUEUE], (unsigned long long)QUEUE_CHUNK);
-        fresh = __shfl(b, 0);
+        fresh = first_lane(b);
     }
     if (p.st == ST_DIFFUSIVE) {
         const uint64_t rank = lanes_below(T);
@@ -291,7 +300,7 @@ template <typename R> __device__ __forceinline__ void mark_ended(Particle<R>& p,
 template <bool ARR, typename R>
 __device__ __forceinline__ void settle_ballistic(const TransportArgs<R>& a, const BlockTally& bt,
                                                  const SegDev<R>* __restrict__ segs, uint32_t pid, int seg,
-                                                 Particle<R>& p, LaneAcc& acc, QRun& Q, int lane)
+                                                 Particle<R>& p, LaneAcc<false>& acc, QRun& Q, int lane)
 {
     if (__ballot(p.st == ST_ENDED) != 0 && p.st == ST_ENDED) {
         const SegDev<R>& s = segs[seg];
@@ -308,7 +317,7 @@ __device__ __forceinline__ void settle_ballistic(const TransportArgs<R>& a, cons
 // Ballistic flights of the lanes in `mine`, all of segment S (uniform: its constants stay in scalar
 // registers) until the wave should refill (lanes that ended, thermalised or are free count) or
 // none of them flies.
-template <typename R>
+template <typename O, typename R>
 __device__ __forceinline__ void ballistic_loop(const TransportArgs<R>& a, const SegDev<R>* S, uint32_t pid,
                                                Particle<R>& p, bool mine, bool drained)
 {
@@ -317,7 +326,7 @@ __device__ __forceinline__ void ballistic_loop(const TransportArgs<R>& a, const 
         // asm hides that the pointer is the same), not kept across flights in spilled vector registers
         if (std::is_same<R, double>::value) asm volatile("" : "+s"(S));
         if (mine && p.st == ST_BALLISTIC) {
-            const Term t = step_mode(*S, a.tab, a.k0, a.k1, pid, a.cap, p);
+            const Term t = step_mode<O>(*S, a.tab, a.k0, a.k1, pid, a.cap, p);
             if (t.state != HIT_NONE) mark_ended(p, t);
         }
         if (__ballot(mine && p.st == ST_BALLISTIC) == 0) break;
@@ -329,7 +338,7 @@ __device__ __forceinline__ void ballistic_loop(const TransportArgs<R>& a, const 
 template <bool ARR, typename R>
 __device__ __forceinline__ void escape_capped(const TransportArgs<R>& a, const BlockTally& bt,
                                               const SegDev<R>* __restrict__ segs, int seg, uint32_t pid,
-                                              Particle<R>& p, LaneAcc& acc, bool capped)
+                                              Particle<R>& p, LaneAcc<true>& acc, bool capped)
 {
     for (uint64_t C = __ballot(capped); C != 0;) {
         const int sL = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)C) - 1);
@@ -345,17 +354,17 @@ __device__ __forceinline__ void escape_capped(const TransportArgs<R>& a, const B
 
 // The held steps of the wave (mask H != 0), tested together: with the geometry read once for
 // the wave when they share a segment (the common case), else each lane reading its own.
-template <bool ARR, typename R>
+template <bool ARR, bool OBJ, typename R>
 __device__ __forceinline__ void resolve_held(const TransportArgs<R>& a, const BlockTally& bt,
                                              const SegDev<R>* __restrict__ segs, int seg, uint32_t pid,
-                                             Particle<R>& p, Walk<R>& wk, LaneAcc& acc, bool held, uint64_t H)
+                                             Particle<R>& p, Walk<R>& wk, LaneAcc<true>& acc, bool held, uint64_t H)
 {
     const int sL = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)H) - 1);
     if (std::is_same<R, float>::value) acc.c[C_TESTED] += held ? 1u : 0u;
     if (__ballot(held && seg != sL) == 0) {
         if (held) {
             const SegDev<R>& S = segs[sL];
-            const Term t = diffusive_resolve(S, p, wk);
+            const Term t = diffusive_resolve(S, p, wk, std::conditional_t<OBJ, OwnObjects, NoObjects>());
             if (t.state != HIT_NONE) {
                 p.ndiff = p.e - p.ndiff - 1u;
                 terminate<ARR>(a, bt, S, pid, p, t, acc);
@@ -363,7 +372,7 @@ __device__ __forceinline__ void resolve_held(const TransportArgs<R>& a, const Bl
         }
     } else if (held) {
         const SegDev<R>& S = segs[seg];
-        const Term t = diffusive_resolve(S, p, wk);
+        const Term t = diffusive_resolve(S, p, wk, std::conditional_t<OBJ, OwnObjects, NoObjects>());
         if (t.state != HIT_NONE) {
             p.ndiff = p.e - p.ndiff - 1u;
             terminate<ARR>(a, bt, S, pid, p, t, acc);
@@ -375,11 +384,11 @@ __device__ __forceinline__ void resolve_held(const TransportArgs<R>& a, const Bl
 // the steps that left their balls tested together after each.  Walkers within a group's length of
 // the event cap are rare: while the wave has one, it takes single steps.  Returns when the wave
 // should refill, has no walker left, or walks its last ones cooperatively; no step is held then.
-template <bool ARR, typename R>
+template <bool ARR, bool OBJ, typename R>
 __device__ __forceinline__ void diffusive_loop(const TransportArgs<R>& a, const BlockTally& bt,
                                                const SegDev<R>* __restrict__ segs, int seg, R lam_l2,
                                                uint32_t cfgcat, uint32_t pid, Particle<R>& p, Walk<R>& wk,
-                                               LaneAcc& acc, bool drained)
+                                               LaneAcc<true>& acc, bool drained)
 {
     constexpr uint32_t REACH = 2 * WALK_ADVANCES + 1;     // events a group takes at most
     const uint32_t far = a.cap > REACH ? a.cap - REACH : 0u;
@@ -398,7 +407,7 @@ __device__ __forceinline__ void diffusive_loop(const TransportArgs<R>& a, const 
             if (p.st == ST_DIFFUSIVE) held = diffusive_single(lam_l2, cfgcat, a.k0, a.k1, pid, p, wk);
         }
         const uint64_t H = __ballot(held);
-        if (H != 0) resolve_held<ARR>(a, bt, segs, seg, pid, p, wk, acc, held, H);
+        if (H != 0) resolve_held<ARR, OBJ>(a, bt, segs, seg, pid, p, wk, acc, held, H);
         M = __ballot(p.st == ST_DIFFUSIVE);
         if (M == 0 || (!drained && __popcll(__ballot(p.st == ST_DEAD)) >= a.refill_min) ||
             (drained && __popcll(M) <= Walk<R>::COOP))
@@ -409,9 +418,10 @@ __device__ __forceinline__ void diffusive_loop(const TransportArgs<R>& a, const 
 // Ballistic phase of one round: every ticket of the round, from launch until the atom ends
 // on a surface, escapes, or thermalises (then it is queued for the diffusive phase).
 // Dynamic LDS: per-segment counters (u64, when lds_counters) then the tally (u32, when lds_tally).
-template <bool ARR, typename R>
+template <bool ARR, bool OBJ, typename R>
 __device__ __forceinline__ void ballistic_phase(TransportArgs<R>& a, const SegDev<R>* __restrict__ segs)
 {
+    using O = std::conditional_t<OBJ, OwnObjects, NoObjects>;
     extern __shared__ unsigned long long lds[];
     BlockTally bt;
     lds_setup(a, bt, lds);
@@ -421,7 +431,7 @@ __device__ __forceinline__ void ballistic_phase(TransportArgs<R>& a, const SegDe
     p.e = p.ndiff = p.ncoll = 0;
     uint32_t pid = 0;
     int seg = 0;
-    LaneAcc acc;
+    LaneAcc<false> acc;
     Tickets T;
     QRun Q;
     int cur_pos = 0, last_pos = 0;        // wave-uniform current position in ticket order ...
@@ -431,7 +441,7 @@ __device__ __forceinline__ void ballistic_phase(TransportArgs<R>& a, const SegDe
         const uint64_t dead = __ballot(p.st == ST_DEAD);
         const int n_dead = __popcll(dead);
         if (!T.drained && n_dead > 0 && (n_dead >= a.refill_ballistic || n_dead == 64)) {
-            const uint64_t my = claim(T, &a.qstate[QS_TICKETS], a.chunk_ballistic, a.total, dead, lane);
+            const uint64_t my = claim<true>(T, &a.qstate[QS_TICKETS], a.chunk_ballistic, a.total, dead, lane);
             if (my != ~0ull) {
                 const uint64_t g = a.tbase + my;
                 // the ticket's position in ticket order: the wave's current one (tickets of a
@@ -473,13 +483,13 @@ __device__ __forceinline__ void ballistic_phase(TransportArgs<R>& a, const SegDe
         if constexpr (std::is_same<R, double>::value) {
             // lanes of other segments wait their turn: a second copy of the flight with per-lane
             // constants would only spill
-            ballistic_loop(a, segs + s0, pid, p, seg == s0, T.drained);
+            ballistic_loop<O>(a, segs + s0, pid, p, seg == s0, T.drained);
         } else if (__ballot(p.st == ST_BALLISTIC && seg != s0) == 0) {
-            ballistic_loop(a, segs + s0, pid, p, true, T.drained);
+            ballistic_loop<O>(a, segs + s0, pid, p, true, T.drained);
         } else if (p.st == ST_BALLISTIC) {
             // lanes of several segments: one flight with per-lane constants
             const SegDev<R>& s = segs[seg];
-            const Term t = step_mode(s, a.tab, a.k0, a.k1, pid, a.cap, p);
+            const Term t = step_mode<O>(s, a.tab, a.k0, a.k1, pid, a.cap, p);
             if (t.state != HIT_NONE) mark_ended(p, t);
         }
     }
@@ -487,21 +497,23 @@ __device__ __forceinline__ void ballistic_phase(TransportArgs<R>& a, const SegDe
     lds_flush(a, bt, acc);
 }
 
-// At most 96 VGPRs: five waves per SIMD hide the latency of the transcendental and
-// integer-multiply chains.
-template <bool ARR>
+// At most 96 VGPRs: five waves per SIMD or more hide the latency of the transcendental and
+// integer-multiply chains.  73 are used without absorbing objects (85 with tickets and queue slots in
+// vector registers): six waves per SIMD, four cathodes 3.04 -> 2.95 ms, the 64-chamber sweep's half 14.1
+// -> 13.5; asked for seven (72 VGPRs), 2.97 and 13.7.
+template <bool ARR, bool OBJ>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
 k_ballistic32(TransportArgs<float> a, const SegDev<float>* __restrict__ segs)
 {
-    ballistic_phase<ARR>(a, segs);
+    ballistic_phase<ARR, OBJ>(a, segs);
 }
 // Three waves per SIMD (at most 168 VGPRs) in both FP64 kernels, without spills: four waves spilled
 // 64 registers in the walk (9e5 atoms at 0.5 / 0 / 2 Pa: 13.8 ms at three, 15.8 at four).
-template <bool ARR>
+template <bool ARR, bool OBJ>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 k_ballistic64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
 {
-    ballistic_phase<ARR>(a, segs);
+    ballistic_phase<ARR, OBJ>(a, segs);
 }
 
 // The last walks of a drained wave (its lanes in D, at most Walk<R>::COOP, none with a held step), walked
@@ -511,10 +523,10 @@ k_ballistic64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
 // walkers end.  Bound by the latency of one pass, the longest walks being all that is left: the state
 // stays replicated in the span, so a pass starts without shuffles, and the surfaces are read once per
 // layout in FP32 (registers), from the segment table in FP64.
-template <bool ARR, typename R>
+template <bool ARR, bool OBJ, typename R>
 __device__ __forceinline__ void tail_walk(const TransportArgs<R>& a, const BlockTally& bt,
                                           const SegDev<R>* __restrict__ segs, uint64_t D, int seg, R lam_l2,
-                                          uint32_t cfgcat, uint32_t pid, Particle<R>& p, Walk<R>& wk, LaneAcc& acc,
+                                          uint32_t cfgcat, uint32_t pid, Particle<R>& p, Walk<R>& wk, LaneAcc<true>& acc,
                                           int lane)
 {
     flush_acc(a, bt, acc);
@@ -575,7 +587,7 @@ __device__ __forceinline__ void tail_walk(const TransportArgs<R>& a, const Block
                 p.r2 = hell;
 #pragma unroll
                 for (int i = 0; i < 3; ++i) p.d[i] = hd[i];
-                end = diffusive_resolve(S, p, wk);
+                end = diffusive_resolve(S, p, wk, std::conditional_t<OBJ, SpanObjects, NoObjects>(sh, j));
                 if (std::is_same<R, float>::value && lead) acc.c[C_TESTED] += 1u;
             } else if (stop) {
                 end.state = HIT_ESCAPED;
@@ -598,7 +610,7 @@ __device__ __forceinline__ void tail_walk(const TransportArgs<R>& a, const Block
 // Diffusive phase of one round: the walks of the atoms queued by the ballistic phase.  Lanes
 // of any segments walk together (the step needs only two per-lane numbers of the segment), so
 // a wave never falls back to one step at a time.
-template <bool ARR, typename R>
+template <bool ARR, bool OBJ, typename R>
 __device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const SegDev<R>* __restrict__ segs)
 {
     extern __shared__ unsigned long long lds[];
@@ -615,13 +627,13 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const SegDe
     int seg = 0;
     R lam_l2 = (R)0;           // the lane's segment: thermal mean free path (times ln 2), Philox word
     uint32_t cfgcat = 0;
-    LaneAcc acc;
+    LaneAcc<true> acc;
     Tickets T;
     for (;;) {
         const uint64_t dead = __ballot(p.st == ST_DEAD);
         const int n_dead = __popcll(dead);
         if (!T.drained && n_dead > 0 && (n_dead >= a.refill_min || n_dead == 64)) {
-            const uint64_t my = claim(T, &a.qstate[QS_DIFFUSIVE], chunk, total, dead, lane);
+            const uint64_t my = claim<false>(T, &a.qstate[QS_DIFFUSIVE], chunk, total, dead, lane);
             const uint32_t qpid = my != ~0ull ? a.queue[my].pid : 0xFFFFFFFFu;
             if (qpid != 0xFFFFFFFFu) {                 // empty slots (left unused by a wave) are skipped
                 const ThermRec<R> r = a.queue[my];
@@ -653,37 +665,33 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const SegDe
             continue;
         }
         if (T.drained && __popcll(D) <= Walk<R>::COOP) {
-            tail_walk<ARR>(a, bt, segs, D, seg, lam_l2, cfgcat, pid, p, wk, acc, lane);
+            tail_walk<ARR, OBJ>(a, bt, segs, D, seg, lam_l2, cfgcat, pid, p, wk, acc, lane);
             break;
         }
-        diffusive_loop<ARR>(a, bt, segs, seg, lam_l2, cfgcat, pid, p, wk, acc, T.drained);
+        diffusive_loop<ARR, OBJ>(a, bt, segs, seg, lam_l2, cfgcat, pid, p, wk, acc, T.drained);
     }
     lds_flush(a, bt, acc);
 }
 
-// At most 96 VGPRs (five waves per SIMD, as the ballistic phase).  With the arrival tallies
-// a few values spill to scratch at five waves, outside the steps of the walk; that still runs
-// faster than four waves without spills.
+// At most 96 VGPRs: five waves per SIMD.  Without absorbing objects nothing spills (92 VGPRs); with them,
+// or with the arrival tallies, a few values do outside the steps of the walk, which still runs faster
+// than four waves without spills in large runs.
+template <bool ARR, bool OBJ>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
 k_diffusive32(TransportArgs<float> a, const SegDev<float>* __restrict__ segs)
 {
-    diffusive_phase<false>(a, segs);
-}
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
-k_diffusive32_arr(TransportArgs<float> a, const SegDev<float>* __restrict__ segs)
-{
-    diffusive_phase<true>(a, segs);
+    diffusive_phase<ARR, OBJ>(a, segs);
 }
 
 // Bound by VALU issue as the FP32 walk is (an FP64 instruction takes four clocks too): 430
 // instructions a round of two steps, most of them the library's log2 and sincospi.  One thread per
 // atom through its whole history, every step tested, took 77 ms for 9e5 atoms at 0.5 / 0 / 2 Pa and
 // 34.2 ms for 2.3e6 from four cathodes; the two phases take 12.9 and 4.7 ms.
-template <bool ARR>
+template <bool ARR, bool OBJ>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 k_diffusive64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
 {
-    diffusive_phase<ARR>(a, segs);
+    diffusive_phase<ARR, OBJ>(a, segs);
 }
 
 // Zero the outputs (a kernel, so that it can sit in a graph).
@@ -786,13 +794,41 @@ size_t transport_lds(const Plan* P, bool arrivals, bool* lds_counters, bool* lds
     return (*lds_counters ? cbytes : 0) + (*lds_tally ? tbytes : 0) + (*lds_arrivals ? abytes : 0);
 }
 
+namespace {
+// The instance of a kernel template <arrival tallies, absorbing objects>.
+#define SPX_INSTANCE(kernel, arr, obj)                                                          \
+    ((arr) ? ((obj) ? (const void*)kernel<true, true> : (const void*)kernel<true, false>)       \
+           : ((obj) ? (const void*)kernel<false, true> : (const void*)kernel<false, false>))
+
+// The plan's constants and the kernels of a precision.
+template <typename R> struct Path;
+template <> struct Path<float> {
+    static const SegDev<float>* segs(const Plan* P) { return P->d_seg32; }
+    static const float* theta(const Plan* P) { return P->d_theta32; }
+    static const float* betamax(const Plan* P) { return P->d_betamax32; }
+    static const float* edges(const Plan* P) { return P->d_edges32; }
+    static const void* ballistic(const Plan* P, bool arr) { return SPX_INSTANCE(k_ballistic32, arr, P->has_objects); }
+    static const void* diffusive(const Plan* P, bool arr) { return SPX_INSTANCE(k_diffusive32, arr, P->has_objects); }
+    static constexpr int IDLE = WALK_IDLE;
+};
+template <> struct Path<double> {
+    static const SegDev<double>* segs(const Plan* P) { return P->d_seg64; }
+    static const double* theta(const Plan* P) { return P->d_theta64; }
+    static const double* betamax(const Plan* P) { return P->d_betamax64; }
+    static const double* edges(const Plan* P) { return P->d_edges64; }
+    static const void* ballistic(const Plan* P, bool arr) { return SPX_INSTANCE(k_ballistic64, arr, P->has_objects); }
+    static const void* diffusive(const Plan* P, bool arr) { return SPX_INSTANCE(k_diffusive64, arr, P->has_objects); }
+    static constexpr int IDLE = WALK_IDLE64;
+};
+}  // namespace
+
 int occupancy_transport32(const Plan* P, int threads, int* bpc_ballistic, int* bpc_diffusive)
 {
     bool lc, lt, la;
     const size_t smem = transport_lds(P, false, &lc, &lt, &la);
     int b1 = 0, b2 = 0;
-    SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b1, k_ballistic32<false>, threads, smem));
-    SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b2, k_diffusive32, threads, smem));
+    SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b1, Path<float>::ballistic(P, false), threads, smem));
+    SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b2, Path<float>::diffusive(P, false), threads, smem));
     *bpc_ballistic = b1;
     *bpc_diffusive = b2;
     return SPX_OK;
@@ -804,37 +840,19 @@ uint64_t rounds_of(uint64_t total, uint64_t round_max)
     return total == 0 ? 0 : (total + round_max - 1) / round_max;
 }
 
-namespace {
-// The plan's constants and the kernels of a precision.
-template <typename R> struct Path;
-template <> struct Path<float> {
-    static const SegDev<float>* segs(const Plan* P) { return P->d_seg32; }
-    static const float* theta(const Plan* P) { return P->d_theta32; }
-    static const float* betamax(const Plan* P) { return P->d_betamax32; }
-    static const float* edges(const Plan* P) { return P->d_edges32; }
-    static const void* ballistic(bool arr)
-    {
-        return arr ? (const void*)k_ballistic32<true> : (const void*)k_ballistic32<false>;
-    }
-    static const void* diffusive(bool arr) { return arr ? (const void*)k_diffusive32_arr : (const void*)k_diffusive32; }
-    static constexpr int IDLE = WALK_IDLE;
-};
-template <> struct Path<double> {
-    static const SegDev<double>* segs(const Plan* P) { return P->d_seg64; }
-    static const double* theta(const Plan* P) { return P->d_theta64; }
-    static const double* betamax(const Plan* P) { return P->d_betamax64; }
-    static const double* edges(const Plan* P) { return P->d_edges64; }
-    static const void* ballistic(bool arr)
-    {
-        return arr ? (const void*)k_ballistic64<true> : (const void*)k_ballistic64<false>;
-    }
-    static const void* diffusive(bool arr)
-    {
-        return arr ? (const void*)k_diffusive64<true> : (const void*)k_diffusive64<false>;
-    }
-    static constexpr int IDLE = WALK_IDLE64;
-};
-}  // namespace
+// Blocks of a round of `total` tickets, out of `blocks`: a wave of a small run costs more to start and end
+// (its block clears and flushes the LDS tally) than its share of the work, and histories step faster
+// with fewer waves on their SIMD.  Waves per SIMD by tickets per lane of one wave per SIMD; ballistic
+// + diffusive kernel at 1, 2, 3, 4, 5 of them: 1e4 atoms 0.26, 0.28, 0.31, 0.34, 0.36 ms; 1e5 (1.5 tickets)
+// 0.42, 0.45, 0.49, 0.51, 0.53; 2e5, four cathodes (3.1) 0.56, 0.51, 0.55, 0.57, 0.60; 1e6 (15) 1.23,
+// 0.95, 0.89, 0.91, 0.92; 2.3e6 (35) 2.34, 1.50, 1.34, 1.31, 1.36.
+static int blocks_of(uint64_t total, int blocks, int threads, int n_simd)
+{
+    const uint64_t per_lane = total / ((uint64_t)n_simd * 64);
+    if (per_lane >= 64) return blocks;
+    const int w = 1 + (per_lane >= 2) + (per_lane >= 8) + (per_lane >= 24);
+    return std::min(blocks, (w * n_simd * 64 + threads - 1) / threads);
+}
 
 template <typename R>
 int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tfirst, uint64_t total,
@@ -882,7 +900,7 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
     int blocks_diff_arr = sh.blocks_diff;
     if (o.arr_E) {
         int bpc_arr = 0;
-        SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc_arr, K::diffusive(true), sh.threads, smem));
+        SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&bpc_arr, K::diffusive(P, true), sh.threads, smem));
         if (bpc_arr > 0) blocks_diff_arr = std::min(sh.blocks_diff, bpc_arr * P->n_cu);
     }
     a.lds_counters = lc ? 1 : 0;
@@ -890,8 +908,10 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
     a.lds_arrivals = la ? 1 : 0;
     const uint64_t n_rounds = rounds_of(total, q.round_max);
     const uint64_t per_round = n_rounds ? (total + n_rounds - 1) / n_rounds : 0;
+    const int blocks = blocks_of(per_round, sh.blocks, sh.threads, a.n_simd);
+    const int blocks_diff = blocks_of(per_round, a.arr_E ? blocks_diff_arr : sh.blocks_diff, sh.threads, a.n_simd);
     // every queue slot a round can reserve: its atoms plus at most one unused run per wave
-    const uint64_t waves = (uint64_t)sh.blocks * (uint64_t)((sh.threads + 63) / 64);
+    const uint64_t waves = (uint64_t)blocks * (uint64_t)((sh.threads + 63) / 64);
     if (n_rounds && per_round + waves * QUEUE_CHUNK > q.cap) {
         set_error("internal: round larger than the thermalisation queue");
         return SPX_ESTATE;
@@ -912,8 +932,8 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
         reset.arg(q.qstate);
         SPX_TRY(sink.put(reset));
         KLaunch bal;
-        bal.func = K::ballistic(a.arr_E != nullptr);
-        bal.grid = dim3((unsigned)sh.blocks);
+        bal.func = K::ballistic(P, a.arr_E != nullptr);
+        bal.grid = dim3((unsigned)blocks);
         bal.block = dim3((unsigned)sh.threads);
         bal.smem = (uint32_t)smem;
         bal.phase = 1;
@@ -922,8 +942,8 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
         SPX_TRY(sink.put(bal));
         // the instance with the arrival tallies has its own resident limit (fewer waves per SIMD)
         KLaunch dif;
-        dif.func = K::diffusive(a.arr_E != nullptr);
-        dif.grid = dim3((unsigned)(a.arr_E ? blocks_diff_arr : sh.blocks_diff));
+        dif.func = K::diffusive(P, a.arr_E != nullptr);
+        dif.grid = dim3((unsigned)blocks_diff);
         dif.block = dim3((unsigned)sh.threads);
         dif.smem = (uint32_t)smem;
         dif.phase = 2;
@@ -948,8 +968,8 @@ int shape_transport64(Plan* P)
     Shape& sh = P->shape64;
     sh.threads = 256;
     int b = 0, d = 0;
-    SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, Path<double>::ballistic(false), sh.threads, smem));
-    SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&d, Path<double>::diffusive(false), sh.threads, smem));
+    SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, Path<double>::ballistic(P, false), sh.threads, smem));
+    SPX_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&d, Path<double>::diffusive(P, false), sh.threads, smem));
     if (b < 1 || d < 1) {
         set_error("the FP64 transport kernels do not fit on this device");
         return SPX_EDEVICE;
