@@ -359,18 +359,8 @@ __device__ __forceinline__ void resolve_held(const TransportArgs<R>& a, const Bl
                                              const SegDev<R>* __restrict__ segs, int seg, uint32_t pid,
                                              Particle<R>& p, Walk<R>& wk, LaneAcc<true>& acc, bool held, uint64_t H)
 {
-    const int sL = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)H) - 1);
     if (std::is_same<R, float>::value) acc.c[C_TESTED] += held ? 1u : 0u;
-    if (__ballot(held && seg != sL) == 0) {
-        if (held) {
-            const SegDev<R>& S = segs[sL];
-            const Term t = diffusive_resolve(S, p, wk, std::conditional_t<OBJ, OwnObjects, NoObjects>());
-            if (t.state != HIT_NONE) {
-                p.ndiff = p.e - p.ndiff - 1u;
-                terminate<ARR>(a, bt, S, pid, p, t, acc);
-            }
-        }
-    } else if (held) {
+    if (held) {
         const SegDev<R>& S = segs[seg];
         const Term t = diffusive_resolve(S, p, wk, std::conditional_t<OBJ, OwnObjects, NoObjects>());
         if (t.state != HIT_NONE) {
