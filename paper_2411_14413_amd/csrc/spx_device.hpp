@@ -356,8 +356,8 @@ __device__ __forceinline__ R lambda_m(const SegDev<R>& s, const TabDev<R>& tb, R
 // The least of `best` and the distances along d to the objects k0, k0 + dk, ..., both faces: a plane
 // crossing inside the disc or rectangle; for a tube the smaller positive root of |w_perp + t d_perp| =
 // radius whose axial coordinate lies in [0, len].
-template <typename R>
-__device__ __forceinline__ R objects_hit(const SegDev<R>& s, const R* x, const R* d, R best, int k0, int dk)
+template <typename G, typename R>
+__device__ __forceinline__ R objects_hit(const G& s, const R* x, const R* d, R best, int k0, int dk)
 {
     const R inf = m_inf<R>();
     for (int k = k0; k < s.n_obj; k += dk) {
@@ -391,8 +391,8 @@ __device__ __forceinline__ R objects_hit(const SegDev<R>& s, const R* x, const R
 }
 
 // The least of `best` and the squared distances from x to the objects k0, k0 + dk, ...
-template <typename R>
-__device__ __forceinline__ R objects_clear2(const SegDev<R>& s, const R* x, R best, int k0, int dk)
+template <typename G, typename R>
+__device__ __forceinline__ R objects_clear2(const G& s, const R* x, R best, int k0, int dk)
 {
     for (int k = k0; k < s.n_obj; k += dk) {
         const ObjDev<R>& o = s.obj[k];
@@ -429,18 +429,18 @@ __device__ __forceinline__ R objects_clear2(const SegDev<R>& s, const R* x, R be
 // object's hit wins over another's only in t, never in state).
 struct NoObjects {
     __device__ __forceinline__ NoObjects(int = 0, int = 0) {}
-    template <typename R> __device__ __forceinline__ R hit(const SegDev<R>&, const R*, const R*, R best) const
+    template <typename G, typename R> __device__ __forceinline__ R hit(const G&, const R*, const R*, R best) const
     {
         return best;
     }
-    template <typename R> __device__ __forceinline__ R clear2(const SegDev<R>&, const R*, R best) const { return best; }
+    template <typename G, typename R> __device__ __forceinline__ R clear2(const G&, const R*, R best) const { return best; }
 };
 struct OwnObjects {
-    template <typename R> __device__ __forceinline__ R hit(const SegDev<R>& s, const R* x, const R* d, R best) const
+    template <typename G, typename R> __device__ __forceinline__ R hit(const G& s, const R* x, const R* d, R best) const
     {
         return objects_hit(s, x, d, best, 0, 1);
     }
-    template <typename R> __device__ __forceinline__ R clear2(const SegDev<R>& s, const R* x, R best) const
+    template <typename G, typename R> __device__ __forceinline__ R clear2(const G& s, const R* x, R best) const
     {
         return objects_clear2(s, x, best, 0, 1);
     }
@@ -448,7 +448,7 @@ struct OwnObjects {
 struct SpanObjects {
     int sh, j;
     __device__ __forceinline__ SpanObjects(int sh_, int j_) : sh(sh_), j(j_) {}
-    template <typename R> __device__ __forceinline__ R hit(const SegDev<R>& s, const R* x, const R* d, R best) const
+    template <typename G, typename R> __device__ __forceinline__ R hit(const G& s, const R* x, const R* d, R best) const
     {
         if (s.n_obj == 0) return best;
         best = objects_hit(s, x, d, best, j, 1 << sh);
@@ -458,7 +458,7 @@ struct SpanObjects {
         }
         return best;
     }
-    template <typename R> __device__ __forceinline__ R clear2(const SegDev<R>& s, const R* x, R best) const
+    template <typename G, typename R> __device__ __forceinline__ R clear2(const G& s, const R* x, R best) const
     {
         if (s.n_obj == 0) return best;
         best = objects_clear2(s, x, best, j, 1 << sh);
@@ -466,6 +466,47 @@ struct SpanObjects {
         return best;
     }
 };
+
+// What the surface test and the clearance read of a segment, as values: read together, they cost one wait
+// where reads spread through the test cost several, and the tail of a run (one test per pass) keeps them
+// for many passes.  1e5 atoms of one cathode 431 -> 380 us, four cathodes 6.14 -> 5.96 ms, the 64-chamber
+// sweep's half 92.4 -> 91.8.  FP64 values would take twice the registers, and beside the code of the
+// absorbing objects they spill (four cathodes in chimneys, 2.3e7 atoms: 5.97 ms from the table, 6.24 as values), so
+// GeoOf takes the table there.
+template <typename R> struct SegGeo {
+    R sub_n[3], sub_u[3], sub_v[3], sub_nc, sub_uc, sub_vc, half_u, half_v, sub_R2;
+    R cat_n[3], cat_u[3], cat_v[3], cat_nc, cat_uc, cat_vc, cat_R2;
+    R ch_R2, zlo, zhi;
+    int32_t shape;
+    __device__ __forceinline__ explicit SegGeo(const SegDev<R>& s)
+    {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            sub_n[i] = s.sub_n[i];
+            sub_u[i] = s.sub_u[i];
+            sub_v[i] = s.sub_v[i];
+            cat_n[i] = s.cat_n[i];
+            cat_u[i] = s.cat_u[i];
+            cat_v[i] = s.cat_v[i];
+        }
+        sub_nc = s.sub_nc;
+        sub_uc = s.sub_uc;
+        sub_vc = s.sub_vc;
+        half_u = s.half_u;
+        half_v = s.half_v;
+        sub_R2 = s.sub_R2;
+        cat_nc = s.cat_nc;
+        cat_uc = s.cat_uc;
+        cat_vc = s.cat_vc;
+        cat_R2 = s.cat_R2;
+        ch_R2 = s.ch_R2;
+        zlo = s.zlo;
+        zhi = s.zhi;
+        shape = s.shape;
+    }
+};
+template <bool OBJ, typename R>
+using GeoOf = std::conditional_t<std::is_same<R, float>::value && !OBJ, const SegGeo<R>, const SegDev<R>&>;
 
 struct HitF {
     int state;     // HIT_NONE / HIT_DEPOSITED / HIT_WALL
@@ -479,8 +520,8 @@ struct HitF {
 // scheduled early; the objects follow in a loop uniform over the segment.  A direction
 // parallel to a plane gives a reciprocal of zero, hence t = inf or NaN, which fails t > 0 as
 // intended.
-template <typename R, typename O>
-__device__ __forceinline__ HitF hit_test(const SegDev<R>& s, const R* x, const R* d, R ell, R& t_hit, R& qu_hit,
+template <typename G, typename R, typename O>
+__device__ __forceinline__ HitF hit_test(const G& s, const R* x, const R* d, R ell, R& t_hit, R& qu_hit,
                                          R& qv_hit, bool first, const O& objects)
 {
     const R inf = m_inf<R>();
@@ -532,8 +573,8 @@ __device__ __forceinline__ HitF hit_test(const SegDev<R>& s, const R* x, const R
 // point-to-region distances, tubes as point-to-open-cylinder distances, the chamber side and
 // caps.  A path that stays closer to x than this cannot
 // meet any surface.
-template <typename R, typename O>
-__device__ __forceinline__ R clearance(const SegDev<R>& s, const R* x, const O& objects)
+template <typename G, typename R, typename O>
+__device__ __forceinline__ R clearance(const G& s, const R* x, const O& objects)
 {
     const R h = dot3(x, s.sub_n) - s.sub_nc;
     const R qu = dot3(x, s.sub_u) - s.sub_uc, qv = dot3(x, s.sub_v) - s.sub_vc;
@@ -965,8 +1006,8 @@ __device__ __forceinline__ bool walk_group(R lam_l2, uint32_t cfgcat, uint32_t k
     return held;
 }
 
-template <typename O>
-__device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& s, Particle<float>& p, Walk<float>&,
+template <typename G, typename O>
+__device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& sd, const G& s, Particle<float>& p, Walk<float>&,
                                                   const O& objects)
 {
     const float dir[3] = {p.d[0], p.d[1], p.d[2]};
@@ -977,7 +1018,7 @@ __device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& s, Partic
     if (h.state != HIT_NONE) {
 #pragma unroll
         for (int i = 0; i < 3; ++i) kahan_add(p.x[i], p.xc[i], th * dir[i]);
-        return hit_term(s, h.state, qu, qv, dir);
+        return hit_term(sd, h.state, qu, qv, dir);
     }
     if (!(ell < m_inf<float>())) return Term{HIT_ESCAPED, -1, 0.f};
     compensated_step(p.x, p.xc, ell, dir);
@@ -987,8 +1028,8 @@ __device__ __forceinline__ Term diffusive_resolve(const SegDev<float>& s, Partic
 }
 
 // The same in FP64, with the arithmetic of a step that is always tested.
-template <typename O>
-__device__ __forceinline__ Term diffusive_resolve(const SegDev<double>& s, Particle<double>& p, Walk<double>& wk,
+template <typename G, typename O>
+__device__ __forceinline__ Term diffusive_resolve(const SegDev<double>& s, const G&, Particle<double>& p, Walk<double>& wk,
                                                   const O& objects)
 {
     const double dir[3] = {p.d[0], p.d[1], p.d[2]};

@@ -152,16 +152,19 @@ __device__ __forceinline__ uint64_t first_lane(uint64_t v)
 }
 
 // Wave-private run of tickets [tk, tk_end), claimed CHUNK at a time from a global counter with
-// one atomic, so that refills rarely touch the counter.
+// one atomic, so that refills rarely touch the counter.  A round's tickets and queue slots fit 32 bits
+// (at most 2^28 of them).
 struct Tickets {
-    uint64_t tk = 0, tk_end = 0;
+    uint32_t tk = 0, tk_end = 0;
     bool drained = false;     // wave-uniform: the ticket space is exhausted
 };
+constexpr uint32_t NO_TICKET = ~0u;
+static_assert(ROUND_MAX + QUEUE_SLACK_WAVES * QUEUE_CHUNK < NO_TICKET, "tickets of a round fit 32 bits");
 
 // Tickets for the dead lanes `dead` of the wave: consecutive tickets of the wave's run in lane
-// order.  Returns this lane's ticket, or ~0 when it gets none.
+// order.  Returns this lane's ticket, or NO_TICKET when it gets none.
 template <bool SCALAR>
-__device__ __forceinline__ uint64_t claim(Tickets& T, uint64_t* counter, uint64_t chunk, uint64_t total, uint64_t dead,
+__device__ __forceinline__ uint32_t claim(Tickets& T, uint64_t* counter, uint32_t chunk, uint32_t total, uint64_t dead,
                                           int lane)
 {
     if (T.tk == T.tk_end) {
@@ -170,18 +173,18 @@ __device__ __forceinline__ uint64_t claim(Tickets& T, uint64_t* counter, uint64_
         base = SCALAR ? first_lane(base) : __shfl(base, 0);
         if (base >= total) {
             T.drained = true;
-            return ~0ull;
+            return NO_TICKET;
         }
-        T.tk = base;
-        T.tk_end = (base + chunk < total) ? base + chunk : total;
+        T.tk = (uint32_t)base;
+        T.tk_end = total - T.tk > chunk ? T.tk + chunk : total;
     }
-    const uint64_t n_dead = (uint64_t)__popcll(dead);
-    const uint64_t avail = T.tk_end - T.tk;
-    const uint64_t take = avail < n_dead ? avail : n_dead;
-    const uint64_t base = T.tk;
+    const uint32_t n_dead = (uint32_t)__popcll(dead);
+    const uint32_t avail = T.tk_end - T.tk;
+    const uint32_t take = avail < n_dead ? avail : n_dead;
+    const uint32_t base = T.tk;
     T.tk += take;
-    const uint64_t rank = lanes_below(dead);
-    return (((dead >> lane) & 1ull) && rank < take) ? base + rank : ~0ull;
+    const uint32_t rank = (uint32_t)lanes_below(dead);
+    return (((dead >> lane) & 1ull) && rank < take) ? base + rank : NO_TICKET;
 }
 
 template <typename R>
@@ -362,7 +365,8 @@ __device__ __forceinline__ void resolve_held(const TransportArgs<R>& a, const Bl
     if (std::is_same<R, float>::value) acc.c[C_TESTED] += held ? 1u : 0u;
     if (held) {
         const SegDev<R>& S = segs[seg];
-        const Term t = diffusive_resolve(S, p, wk, std::conditional_t<OBJ, OwnObjects, NoObjects>());
+        GeoOf<OBJ, R> geo(S);
+        const Term t = diffusive_resolve(S, geo, p, wk, std::conditional_t<OBJ, OwnObjects, NoObjects>());
         if (t.state != HIT_NONE) {
             p.ndiff = p.e - p.ndiff - 1u;
             terminate<ARR>(a, bt, S, pid, p, t, acc);
@@ -431,8 +435,8 @@ __device__ __forceinline__ void ballistic_phase(TransportArgs<R>& a, const SegDe
         const uint64_t dead = __ballot(p.st == ST_DEAD);
         const int n_dead = __popcll(dead);
         if (!T.drained && n_dead > 0 && (n_dead >= a.refill_ballistic || n_dead == 64)) {
-            const uint64_t my = claim<true>(T, &a.qstate[QS_TICKETS], a.chunk_ballistic, a.total, dead, lane);
-            if (my != ~0ull) {
+            const uint32_t my = claim<true>(T, &a.qstate[QS_TICKETS], a.chunk_ballistic, (uint32_t)a.total, dead, lane);
+            if (my != NO_TICKET) {
                 const uint64_t g = a.tbase + my;
                 // the ticket's position in ticket order: the wave's current one (tickets of a
                 // run are consecutive, segments long), else a binary search of the prefix table
@@ -457,7 +461,7 @@ __device__ __forceinline__ void ballistic_phase(TransportArgs<R>& a, const SegDe
                 acc.c[C_LAUNCHED] += 1;
             }
             // the position of the wave's last new ticket becomes the current one
-            const uint64_t got = __ballot(my != ~0ull);
+            const uint64_t got = __ballot(my != NO_TICKET);
             if (got != 0) {
                 cur_pos = __builtin_amdgcn_readlane(last_pos, 63 - __clzll((long long)got));
                 cur_lo = a.tfirst[cur_pos];
@@ -512,7 +516,7 @@ k_ballistic64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
 // first that leaves its ball (or to the event cap), then tests those.  Spans are laid out anew as
 // walkers end.  Bound by the latency of one pass, the longest walks being all that is left: the state
 // stays replicated in the span, so a pass starts without shuffles, and the surfaces are read once per
-// layout in FP32 (registers), from the segment table in FP64.
+// layout (GeoOf).
 template <bool ARR, bool OBJ, typename R>
 __device__ __forceinline__ void tail_walk(const TransportArgs<R>& a, const BlockTally& bt,
                                           const SegDev<R>* __restrict__ segs, uint64_t D, int seg, R lam_l2,
@@ -552,6 +556,7 @@ __device__ __forceinline__ void tail_walk(const TransportArgs<R>& a, const Block
             acc.seg = seg;
         }
         const SegDev<R>& S = segs[seg];
+        GeoOf<OBJ, R> geo(S);
         const uint64_t span_mask = sh == 6 ? ~0ull : (1ull << span) - 1;
         for (;;) {
             const uint32_t ej = p.e + 1u + (uint32_t)j;
@@ -577,7 +582,7 @@ __device__ __forceinline__ void tail_walk(const TransportArgs<R>& a, const Block
                 p.r2 = hell;
 #pragma unroll
                 for (int i = 0; i < 3; ++i) p.d[i] = hd[i];
-                end = diffusive_resolve(S, p, wk, std::conditional_t<OBJ, SpanObjects, NoObjects>(sh, j));
+                end = diffusive_resolve(S, geo, p, wk, std::conditional_t<OBJ, SpanObjects, NoObjects>(sh, j));
                 if (std::is_same<R, float>::value && lead) acc.c[C_TESTED] += 1u;
             } else if (stop) {
                 end.state = HIT_ESCAPED;
@@ -606,8 +611,8 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const SegDe
     extern __shared__ unsigned long long lds[];
     BlockTally bt;
     lds_setup(a, bt, lds);
-    const uint64_t total = a.qstate[QS_QUEUE];   // written by the ballistic phase of this round
-    const uint64_t chunk = chunk_of(total, a.n_simd, TICKET_CHUNK);
+    const uint32_t total = (uint32_t)a.qstate[QS_QUEUE];   // written by the ballistic phase of this round
+    const uint32_t chunk = (uint32_t)chunk_of(total, a.n_simd, TICKET_CHUNK);
     const int lane = threadIdx.x & 63;
     Particle<R> p;
     Walk<R> wk;
@@ -623,8 +628,8 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const SegDe
         const uint64_t dead = __ballot(p.st == ST_DEAD);
         const int n_dead = __popcll(dead);
         if (!T.drained && n_dead > 0 && (n_dead >= a.refill_min || n_dead == 64)) {
-            const uint64_t my = claim<false>(T, &a.qstate[QS_DIFFUSIVE], chunk, total, dead, lane);
-            const uint32_t qpid = my != ~0ull ? a.queue[my].pid : 0xFFFFFFFFu;
+            const uint32_t my = claim<false>(T, &a.qstate[QS_DIFFUSIVE], chunk, total, dead, lane);
+            const uint32_t qpid = my != NO_TICKET ? a.queue[my].pid : 0xFFFFFFFFu;
             if (qpid != 0xFFFFFFFFu) {                 // empty slots (left unused by a wave) are skipped
                 const ThermRec<R> r = a.queue[my];
 #pragma unroll
@@ -663,9 +668,8 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const SegDe
     lds_flush(a, bt, acc);
 }
 
-// At most 96 VGPRs: five waves per SIMD.  Without absorbing objects nothing spills (92 VGPRs); with them,
-// or with the arrival tallies, a few values do outside the steps of the walk, which still runs faster
-// than four waves without spills in large runs.
+// At most 96 VGPRs: five waves per SIMD.  The few spills (8 to 25 registers) lie outside the steps of the
+// walk; four waves without them were slower in large runs.
 template <bool ARR, bool OBJ>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
 k_diffusive32(TransportArgs<float> a, const SegDev<float>* __restrict__ segs)
