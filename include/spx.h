@@ -204,10 +204,11 @@ typedef struct spx_plan spx_plan;
  * negative depths, zero weight), E_max <= 0, masses <= 0, an emission law negative somewhere on
  * [0, 90 deg] or with zero integral, non-unit or non-orthogonal axes, an object of unknown kind,
  * with non-positive sizes or outside the chamber, more than 32 absorbing objects in one run,
- * more than 2^24 configurations.  Device memory: the tables, the segment constants and, for
- * FP32 plans, a queue of thermalised atoms of 48 B per ticket of a round (the particles run in
- * equal rounds of at most 2^28 tickets, so at most ~12.9 GB); SPX_ENOMEM if an allocation
- * fails.  *out is set only on success. */
+ * more than 2^24 configurations.  Device memory: the tables, the segment constants and a queue
+ * of thermalised atoms of 48 B (FP64 plans: 80 B) per ticket of a round.  The particles run in
+ * equal rounds of at most 2^28 tickets, so at most ~12.9 GB; FP64 plans of at most 2^24 (1.3 GB),
+ * where that is not free of half as many, down to 2^16.  SPX_ENOMEM if an allocation fails.
+ * *out is set only on success. */
 int spx_plan_create(const spx_config* h_cfgs, int32_t n_cfgs, const spx_params* h_params, spx_plan** out);
 
 /* Sizes of spx_run's outputs: total tally bins over all segments, counters
@@ -224,8 +225,9 @@ int spx_plan_layout(const spx_plan* plan, uint64_t* h_bin_off, uint64_t* h_first
  *   d_counters  uint64[n_counters]    SPX_C_* per segment (overwritten)
  *   d_profiles  double[n_bins_total]  counts / (N_seg * bin area), mm^-2 per launched atom; nullable
  *   d_records   spx_record[n_particles_total]; nullable
- * precision 32 runs the whole plan as one persistent launch (replayed from a HIP
- * graph built on the first run and updated in place for new seeds and buffers);
+ * Runs that fill the device for long take a kernel for each phase, others both phases in one.
+ * precision 32 replays a HIP graph built on the first run and updated in place for new seeds
+ * and buffers;
  * precision 64 enqueues the same two phases in FP64 (every position, energy and decision in
  * double) on `stream`, without a graph.  Asynchronous. */
 int spx_run(spx_plan* plan, uint64_t seed, uint64_t* d_counts, uint64_t* d_counters,
@@ -251,9 +253,9 @@ int spx_run_ex(spx_plan* plan, uint64_t seed, const spx_outputs* out, void* stre
  * static device array of the library (64 MiB per device, held from the library's load until
  * the process ends) instead of the plan's memory, and are enqueued on `stream` directly (no
  * graph).  Outputs as spx_run_ex (caller-owned, overwritten), bit-identical to its results.
- * The particles run in rounds of at most (64 MiB - 1 KiB) / 48 B - (queue slots the launch
- * shape's waves may leave unused: 64 per wave) tickets, so any plan size runs, in more rounds
- * than spx_run uses.  Every call on one GPU shares that GPU's array: calls that overlap on one
+ * The particles run in rounds of at most (64 MiB - 1 KiB) / 48 B tickets (less, where each phase
+ * has its kernel, the queue slots the launch shape's waves may leave unused: 64 per wave), so any
+ * plan size runs, in more rounds than spx_run uses.  Every call on one GPU shares that GPU's array: calls that overlap on one
  * GPU (another stream, another host thread, another plan) race and corrupt each other's
  * results, so order them.  SPX_EINVAL for precision 64 plans, missing outputs, and a launch
  * shape whose unused-slot slack alone exceeds the array; SPX_EDEVICE if the array's device
@@ -278,7 +280,9 @@ int spx_autotune(spx_plan* plan, void* stream);
  * (both), the diffusive phase's refill threshold (a wave refills its dead lanes once at least
  * this many are dead), the ballistic phase's, and the diffusive phase's deferral threshold (a
  * wave tests the steps that left their clearance balls once at least this many lanes hold
- * one and their wait is worth a test pass; default 8).  Any pointer may be NULL. */
+ * one and their wait is worth a test pass; default 8).  Short runs launch fewer blocks, or both
+ * phases in one kernel of its own geometry (not where blocks * threads are less than a wave per
+ * SIMD), with the same thresholds.  Any pointer may be NULL. */
 int spx_get_launch(const spx_plan* plan, int32_t* blocks, int32_t* threads, int32_t* refill_min,
                    int32_t* refill_ballistic, int32_t* defer_min);
 /* Override them: threads a multiple of 64 in [64, 1024], thresholds in [1, 64]; blocks <= 0
@@ -287,8 +291,8 @@ int spx_set_launch(spx_plan* plan, int32_t blocks, int32_t threads, int32_t refi
                    int32_t defer_min);
 
 /* Device time [ms] of the two phases of the last FP32 spx_run of this plan, summed over its
- * rounds (HIP events recorded between the kernels; waits for that run to finish).
- * SPX_ESTATE before the first FP32 run. */
+ * rounds (HIP events recorded between the kernels; waits for that run to finish).  Where both
+ * phases run in one kernel, its time, split as sampled waves' times in them.  SPX_ESTATE before the first FP32 run. */
 int spx_phase_times(spx_plan* plan, float* ms_ballistic, float* ms_diffusive);
 
 /* Copy the FP64 scattering table to the host: h_theta[ne * ns] (row i = log10 eps node),

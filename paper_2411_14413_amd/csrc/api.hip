@@ -716,7 +716,7 @@ static int build_graph(Plan* P, const std::vector<KLaunch>& L)
         return SPX_OK;
     };
     for (const KLaunch& k : L) {
-        if (k.phase == 1) {
+        if (k.phase & 1) {
             if (round >= n_rounds) {
                 set_error("internal: more rounds in the run than in the plan");
                 return SPX_ESTATE;
@@ -737,8 +737,8 @@ static int build_graph(Plan* P, const std::vector<KLaunch>& L)
         prev = n;
         P->graph_launches.push_back(k);
         P->graph_nodes.push_back(n);
-        if (k.phase == 1) SPX_TRY(chain_event(P->phase_events[3 * round + 1]));
-        if (k.phase == 2) SPX_TRY(chain_event(P->phase_events[3 * round++ + 2]));
+        if (k.phase & 1) SPX_TRY(chain_event(P->phase_events[3 * round + 1]));
+        if (k.phase & 2) SPX_TRY(chain_event(P->phase_events[3 * round++ + 2]));
     }
     if (round != n_rounds) {
         set_error("internal: unexpected number of rounds in the transport graph");
@@ -875,6 +875,7 @@ static int autotune(Plan* P, hipStream_t st)
             sh.refill_min = rmin;
             sh.refill_ballistic = rbal;
             sh.defer_min = defer;
+            sh.whole = false;
             QueueMem q;
             q.queue = P->d_queue;
             q.cap = P->queue_cap;
@@ -1192,6 +1193,17 @@ int spx_phase_times(spx_plan* P, float* ms_ballistic, float* ms_diffusive)
         b += t1;
         d += t2;
     }
+    // both phases in one kernel: its time, split as its waves' times in them
+    for (const KLaunch& k : P->graph_launches)
+        if (k.phase == 3) {
+            uint64_t t[2] = {0, 0};
+            SPX_HIP(hipMemcpyAsync(t, P->d_qstate + QS_TIMES, sizeof(t), hipMemcpyDeviceToHost, P->work_stream));
+            SPX_HIP(hipStreamSynchronize(P->work_stream));
+            const double share = t[0] + t[1] ? (double)t[0] / (double)(t[0] + t[1]) : 0.5;
+            d += (float)((1.0 - share) * b);
+            b = (float)(share * b);
+            break;
+        }
     *ms_ballistic = b;
     *ms_diffusive = d;
     return SPX_OK;

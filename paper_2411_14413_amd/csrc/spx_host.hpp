@@ -94,7 +94,7 @@ template <typename R> struct TransportArgs {
     int32_t refill_ballistic;   // ballistic phase: the same threshold
     int32_t defer_min;          // diffusive phase: held steps a wave's surface tests wait for at least
     int32_t walk_idle;          // diffusive phase: ... and the idle rounds of the lanes that hold them
-    uint32_t chunk_ballistic;   // ballistic phase: tickets a wave claims per atomic
+    uint32_t chunk_ballistic;   // ballistic phase: tickets a wave claims per atomic (whole kernel: tickets of a wave)
     uint32_t n_bins;            // tally bins of the plan
     int32_t lds_counters;       // per-segment counters privatised in LDS
     int32_t lds_tally;          // whole tally privatised in LDS (u32 per bin)
@@ -121,8 +121,9 @@ constexpr uint64_t QUEUE_CHUNK = 64;         // queue slots a wave reserves per 
 static_assert(QUEUE_CHUNK == 64, "queue runs hold one slot per lane of a wave");
 // The round's three counters (ballistic tickets, queue length, diffusive tickets) sit 256 bytes
 // apart: every wave's claims and queue reservations are atomics on them, and on one cache line
-// the two kinds of atomics of the ballistic phase would queue behind each other.
-constexpr uint64_t QS_TICKETS = 0, QS_QUEUE = 32, QS_DIFFUSIVE = 64, QSTATE_WORDS = 96;
+// the two kinds of atomics of the ballistic phase would queue behind each other.  QS_TIMES: ticks that
+// sampled waves of the whole kernel spent in either phase.
+constexpr uint64_t QS_TICKETS = 0, QS_QUEUE = 32, QS_DIFFUSIVE = 64, QS_TIMES = 96, QSTATE_WORDS = 128;
 constexpr uint64_t QUEUE_SLACK_WAVES = 8192;  // waves that may leave slots unused (32 per CU, 256 CUs)
 constexpr size_t LDS_COUNTERS_MAX = 16384;   // bytes: up to 256 segments
 constexpr int RT_MAX_NODES = 256;             // nodes of a measured racetrack profile
@@ -160,7 +161,7 @@ struct KLaunch {
     const void* func = nullptr;
     dim3 grid{1, 1, 1}, block{1, 1, 1};
     uint32_t smem = 0;
-    int phase = 0;              // 1: the ballistic kernel of a round, 2: its diffusive kernel, else 0
+    int phase = 0;              // 1: the ballistic kernel of a round, 2: its diffusive kernel, 3: both in one, else 0
     int n_args = 0;
     uint16_t off[8] = {};
     uint16_t last_size = 0;
@@ -203,6 +204,7 @@ struct LaunchSink {
 struct Shape {
     int blocks = 0, blocks_diff = 0, threads = 256, refill_min = REFILL, refill_ballistic = REFILL_BALLISTIC,
         defer_min = DEFER_MIN;
+    bool whole = true;          // runs of whole_waves() take both phases in one kernel
 };
 
 // Queue of thermalised atoms and ticket counters a run works in: the plan's own allocation, or
@@ -290,6 +292,8 @@ struct StreamSink : LaunchSink {
     int put(const KLaunch& k) override;
 };
 uint64_t rounds_of(uint64_t total, uint64_t round_max = ROUND_MAX);
+// Waves per SIMD of a round of `total` tickets whose two phases run in one kernel; 0: a kernel per phase.
+int whole_waves(const Plan* P, uint64_t total, const Shape& sh, bool fp64);
 // The plan's current launch geometry and thresholds.
 Shape plan_shape(const Plan* P);
 // Launch geometry of the FP64 kernels of a plan.

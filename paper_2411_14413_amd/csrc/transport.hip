@@ -162,12 +162,13 @@ constexpr uint32_t NO_TICKET = ~0u;
 static_assert(ROUND_MAX + QUEUE_SLACK_WAVES * QUEUE_CHUNK < NO_TICKET, "tickets of a round fit 32 bits");
 
 // Tickets for the dead lanes `dead` of the wave: consecutive tickets of the wave's run in lane
-// order.  Returns this lane's ticket, or NO_TICKET when it gets none.
-template <bool SCALAR>
+// order.  Returns this lane's ticket, or NO_TICKET when it gets none.  OWN: the wave has the run it
+// started with and claims no other.
+template <bool OWN, bool SCALAR>
 __device__ __forceinline__ uint32_t claim(Tickets& T, uint64_t* counter, uint32_t chunk, uint32_t total, uint64_t dead,
                                           int lane)
 {
-    if (T.tk == T.tk_end) {
+    if (!OWN && T.tk == T.tk_end) {
         unsigned long long base = 0;
         if (lane == 0) base = atomicAdd((unsigned long long*)counter, (unsigned long long)chunk);
         base = SCALAR ? first_lane(base) : __shfl(base, 0);
@@ -183,36 +184,80 @@ __device__ __forceinline__ uint32_t claim(Tickets& T, uint64_t* counter, uint32_
     const uint32_t take = avail < n_dead ? avail : n_dead;
     const uint32_t base = T.tk;
     T.tk += take;
+    if (OWN) T.drained = T.tk == T.tk_end;
     const uint32_t rank = (uint32_t)lanes_below(dead);
     return (((dead >> lane) & 1ull) && rank < take) ? base + rank : NO_TICKET;
 }
 
+// The queued atoms of the waves of a block (both phases in one kernel), walked by whichever of its waves is
+// free: slots [next, end) of each wave, end 0 until its ballistic phase is over.
+struct BlockQueue {
+    uint32_t* next;
+    uint32_t* end;
+    uint32_t wave, waves;
+};
+
+// Slots for the dead lanes of the wave, as claim: from the list it took from last, its own at first, or the
+// next one that holds any.  Lists that are not there yet are left to their waves: nobody waits.
+__device__ __forceinline__ uint32_t claim_shared(Tickets& T, BlockQueue& B, uint64_t dead, int lane)
+{
+    const uint32_t n_dead = (uint32_t)__popcll(dead);
+    for (uint32_t tried = 0; tried < B.waves; ++tried) {
+        const uint32_t end = (uint32_t)__builtin_amdgcn_readfirstlane(
+            (int)__hip_atomic_load(&B.end[B.wave], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
+        // (an end of 0 has to fail here: next means nothing yet)
+        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(&B.next[B.wave], __ATOMIC_RELAXED,
+                                                                            __HIP_MEMORY_SCOPE_WORKGROUP)) < end) {
+            uint32_t base = 0;
+            if (lane == 0)
+                base = __hip_atomic_fetch_add(&B.next[B.wave], n_dead, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+            if (base < end) {
+                const uint32_t rank = (uint32_t)lanes_below(dead);
+                return ((dead >> lane) & 1ull) && rank < end - base ? base + rank : NO_TICKET;
+            }
+        }
+        B.wave = B.wave + 1 < B.waves ? B.wave + 1 : 0;
+    }
+    T.drained = true;
+    return NO_TICKET;
+}
+
+// Dynamic LDS: per-segment counters (u64, when lds_counters), the tally (u32, when lds_tally), the
+// arrival histograms (u32, when lds_arrivals).
 template <typename R>
 __device__ __forceinline__ void lds_setup(const TransportArgs<R>& a, BlockTally& bt, unsigned long long* lds)
 {
     bt.lcnt = lds;
     bt.ltally = (uint32_t*)(lds + (a.lds_counters ? (size_t)a.n_seg * N_COUNTERS : 0));
     bt.larr = bt.ltally + (a.lds_tally ? a.n_bins : 0u);
-    if (a.lds_counters)
-        for (int i = threadIdx.x; i < a.n_seg * N_COUNTERS; i += blockDim.x) bt.lcnt[i] = 0;
-    if (a.lds_tally)
-        for (uint32_t i = threadIdx.x; i < a.n_bins; i += blockDim.x) bt.ltally[i] = 0;
-    if (a.lds_arrivals)
-        for (int i = threadIdx.x; i < a.n_seg * ARR_BINS; i += blockDim.x) bt.larr[i] = 0;
+    const uint32_t words = (uint32_t)(bt.larr - (uint32_t*)lds) + (a.lds_arrivals ? (uint32_t)(a.n_seg * ARR_BINS) : 0u);
+    for (uint32_t i = threadIdx.x; i < words / 4; i += blockDim.x) ((uint4*)lds)[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (threadIdx.x < (words & 3u)) ((uint32_t*)lds)[(words & ~3u) + threadIdx.x] = 0;
     __syncthreads();
 }
 
-template <typename R, bool WALKS>
-__device__ __forceinline__ void lds_flush(const TransportArgs<R>& a, const BlockTally& bt, LaneAcc<WALKS>& acc)
+template <typename R>
+__device__ __forceinline__ void lds_flush(const TransportArgs<R>& a, const BlockTally& bt)
 {
-    flush_acc(a, bt, acc);
     __syncthreads();
     if (a.lds_counters)
         for (int i = threadIdx.x; i < a.n_seg * N_COUNTERS; i += blockDim.x)
             if (bt.lcnt[i]) atomicAdd(&a.counters[i], bt.lcnt[i]);
-    if (a.lds_tally)
-        for (uint32_t i = threadIdx.x; i < a.n_bins; i += blockDim.x)
-            if (bt.ltally[i]) atomicAdd(&a.counts[i], (unsigned long long)bt.ltally[i]);
+    if (a.lds_tally) {
+        constexpr uint32_t U = 8;       // LDS reads in flight
+        for (uint32_t i0 = threadIdx.x; i0 < a.n_bins; i0 += U * blockDim.x) {
+            uint32_t v[U];
+#pragma unroll
+            for (uint32_t k = 0; k < U; ++k) {
+                const uint32_t i = i0 + k * blockDim.x;
+                v[k] = i < a.n_bins ? bt.ltally[i] : 0u;
+            }
+#pragma unroll
+            for (uint32_t k = 0; k < U; ++k)
+                if (v[k]) atomicAdd(&a.counts[i0 + k * blockDim.x], (unsigned long long)v[k]);
+        }
+    }
     if (a.lds_arrivals)
         for (int i = threadIdx.x; i < a.n_seg * ARR_BINS; i += blockDim.x)
             if (bt.larr[i]) {
@@ -409,25 +454,20 @@ __device__ __forceinline__ void diffusive_loop(const TransportArgs<R>& a, const 
     }
 }
 
-// Ballistic phase of one round: every ticket of the round, from launch until the atom ends
-// on a surface, escapes, or thermalises (then it is queued for the diffusive phase).
-// Dynamic LDS: per-segment counters (u64, when lds_counters) then the tally (u32, when lds_tally).
-template <bool ARR, bool OBJ, typename R>
-__device__ __forceinline__ void ballistic_phase(TransportArgs<R>& a, const SegDev<R>* __restrict__ segs)
+// Ballistic phase: every ticket of the round (WHOLE: of the run T that the wave starts with, its queue slots
+// from Q.q on), from launch until the atom ends on a surface, escapes, or thermalises (then it is queued for the
+// diffusive phase).  Returns the wave's next free slot.
+template <bool ARR, bool OBJ, bool WHOLE, typename R>
+__device__ __forceinline__ uint64_t ballistic_phase(TransportArgs<R>& a, const BlockTally& bt,
+                                                const SegDev<R>* __restrict__ segs, Tickets T, QRun Q, int lane)
 {
     using O = std::conditional_t<OBJ, OwnObjects, NoObjects>;
-    extern __shared__ unsigned long long lds[];
-    BlockTally bt;
-    lds_setup(a, bt, lds);
-    const int lane = threadIdx.x & 63;
     Particle<R> p;
     p.st = ST_DEAD;
     p.e = p.ndiff = p.ncoll = 0;
     uint32_t pid = 0;
     int seg = 0;
     LaneAcc<false> acc;
-    Tickets T;
-    QRun Q;
     int cur_pos = 0, last_pos = 0;        // wave-uniform current position in ticket order ...
     uint64_t cur_lo = 0, cur_hi = 0;      // ... and its ticket range (empty until the first refill)
     for (;;) {
@@ -435,7 +475,8 @@ __device__ __forceinline__ void ballistic_phase(TransportArgs<R>& a, const SegDe
         const uint64_t dead = __ballot(p.st == ST_DEAD);
         const int n_dead = __popcll(dead);
         if (!T.drained && n_dead > 0 && (n_dead >= a.refill_ballistic || n_dead == 64)) {
-            const uint32_t my = claim<true>(T, &a.qstate[QS_TICKETS], a.chunk_ballistic, (uint32_t)a.total, dead, lane);
+            const uint32_t my = claim<WHOLE, true>(T, &a.qstate[QS_TICKETS], a.chunk_ballistic, (uint32_t)a.total,
+                                                   dead, lane);
             if (my != NO_TICKET) {
                 const uint64_t g = a.tbase + my;
                 // the ticket's position in ticket order: the wave's current one (tickets of a
@@ -487,8 +528,19 @@ __device__ __forceinline__ void ballistic_phase(TransportArgs<R>& a, const SegDe
             if (t.state != HIT_NONE) mark_ended(p, t);
         }
     }
-    close_run(a, Q, lane);
-    lds_flush(a, bt, acc);
+    if (!WHOLE) close_run(a, Q, lane);
+    flush_acc(a, bt, acc);
+    return Q.q;
+}
+
+template <bool ARR, bool OBJ, typename R>
+__device__ __forceinline__ void ballistic_kernel(TransportArgs<R>& a, const SegDev<R>* segs)
+{
+    extern __shared__ unsigned long long lds[];
+    BlockTally bt;
+    lds_setup(a, bt, lds);
+    ballistic_phase<ARR, OBJ, false>(a, bt, segs, Tickets(), QRun(), (int)(threadIdx.x & 63));
+    lds_flush(a, bt);
 }
 
 // At most 96 VGPRs: five waves per SIMD or more hide the latency of the transcendental and
@@ -499,7 +551,7 @@ template <bool ARR, bool OBJ>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
 k_ballistic32(TransportArgs<float> a, const SegDev<float>* __restrict__ segs)
 {
-    ballistic_phase<ARR, OBJ>(a, segs);
+    ballistic_kernel<ARR, OBJ>(a, segs);
 }
 // Three waves per SIMD (at most 168 VGPRs) in both FP64 kernels, without spills: four waves spilled
 // 64 registers in the walk (9e5 atoms at 0.5 / 0 / 2 Pa: 13.8 ms at three, 15.8 at four).
@@ -507,7 +559,7 @@ template <bool ARR, bool OBJ>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 k_ballistic64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
 {
-    ballistic_phase<ARR, OBJ>(a, segs);
+    ballistic_kernel<ARR, OBJ>(a, segs);
 }
 
 // The last walks of a drained wave (its lanes in D, at most Walk<R>::COOP, none with a held step), walked
@@ -602,18 +654,14 @@ __device__ __forceinline__ void tail_walk(const TransportArgs<R>& a, const Block
     p.st = ST_DEAD;
 }
 
-// Diffusive phase of one round: the walks of the atoms queued by the ballistic phase.  Lanes
-// of any segments walk together (the step needs only two per-lane numbers of the segment), so
-// a wave never falls back to one step at a time.
-template <bool ARR, bool OBJ, typename R>
-__device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const SegDev<R>* __restrict__ segs)
+// Diffusive phase: the walks of the `total` atoms queued by the ballistic phase of the round (WHOLE: of
+// the wave's own slots T).  Lanes of any segments walk together (the step needs only two per-lane
+// numbers of the segment), so a wave never falls back to one step at a time.
+template <bool ARR, bool OBJ, bool WHOLE, typename R>
+__device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const BlockTally& bt,
+                                                const SegDev<R>* __restrict__ segs, BlockQueue B, uint32_t total,
+                                                uint32_t chunk, int lane)
 {
-    extern __shared__ unsigned long long lds[];
-    BlockTally bt;
-    lds_setup(a, bt, lds);
-    const uint32_t total = (uint32_t)a.qstate[QS_QUEUE];   // written by the ballistic phase of this round
-    const uint32_t chunk = (uint32_t)chunk_of(total, a.n_simd, TICKET_CHUNK);
-    const int lane = threadIdx.x & 63;
     Particle<R> p;
     Walk<R> wk;
     p.st = ST_DEAD;
@@ -628,7 +676,8 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const SegDe
         const uint64_t dead = __ballot(p.st == ST_DEAD);
         const int n_dead = __popcll(dead);
         if (!T.drained && n_dead > 0 && (n_dead >= a.refill_min || n_dead == 64)) {
-            const uint32_t my = claim<false>(T, &a.qstate[QS_DIFFUSIVE], chunk, total, dead, lane);
+            const uint32_t my = WHOLE ? claim_shared(T, B, dead, lane)
+                                      : claim<false, false>(T, &a.qstate[QS_DIFFUSIVE], chunk, total, dead, lane);
             const uint32_t qpid = my != NO_TICKET ? a.queue[my].pid : 0xFFFFFFFFu;
             if (qpid != 0xFFFFFFFFu) {                 // empty slots (left unused by a wave) are skipped
                 const ThermRec<R> r = a.queue[my];
@@ -665,7 +714,20 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const SegDe
         }
         diffusive_loop<ARR, OBJ>(a, bt, segs, seg, lam_l2, cfgcat, pid, p, wk, acc, T.drained);
     }
-    lds_flush(a, bt, acc);
+    flush_acc(a, bt, acc);
+}
+
+template <bool ARR, bool OBJ, typename R>
+__device__ __forceinline__ void diffusive_kernel(TransportArgs<R>& a, const SegDev<R>* segs)
+{
+    extern __shared__ unsigned long long lds[];
+    const uint32_t total = (uint32_t)a.qstate[QS_QUEUE];   // written by the ballistic phase of this round
+    if (total == 0) return;        // (clearing and flushing the LDS of a full grid takes 60 us)
+    BlockTally bt;
+    lds_setup(a, bt, lds);
+    const uint32_t chunk = (uint32_t)chunk_of(total, a.n_simd, TICKET_CHUNK);
+    diffusive_phase<ARR, OBJ, false>(a, bt, segs, BlockQueue(), total, chunk, (int)(threadIdx.x & 63));
+    lds_flush(a, bt);
 }
 
 // At most 96 VGPRs: five waves per SIMD.  The few spills (8 to 25 registers) lie outside the steps of the
@@ -674,7 +736,7 @@ template <bool ARR, bool OBJ>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5)))
 k_diffusive32(TransportArgs<float> a, const SegDev<float>* __restrict__ segs)
 {
-    diffusive_phase<ARR, OBJ>(a, segs);
+    diffusive_kernel<ARR, OBJ>(a, segs);
 }
 
 // Bound by VALU issue as the FP32 walk is (an FP64 instruction takes four clocks too): 430
@@ -685,21 +747,91 @@ template <bool ARR, bool OBJ>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3)))
 k_diffusive64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
 {
-    diffusive_phase<ARR, OBJ>(a, segs);
+    diffusive_kernel<ARR, OBJ>(a, segs);
 }
 
-// Zero the outputs (a kernel, so that it can sit in a graph).
-__global__ void k_zero(unsigned long long* counts, uint64_t n_counts, unsigned long long* counters, uint64_t n_counters)
+// Both phases of a run in one kernel (whole_waves says which): a wave takes a fixed run of chunk_ballistic
+// tickets through the ballistic phase, its thermalised atoms into the run's own queue slots, and then
+// walks those and what is left of its block's.  Such a run is bound by the latency of its longest
+// histories; here no walk waits for the slowest flight of another wave nor for a launch, and no
+// counter is shared between blocks: atomics on one line go at 11 ns each.  1e5 atoms of one cathode 0.372
+// -> 0.288 ms, 1e6 from four 0.84 -> 0.62, 4.6e6 1.80 -> 1.60; without gas 5e6 0.59 -> 0.13; 4.6e6 in rounds of the scratch
+// array 3.70 -> 2.50.
+template <bool ARR, bool OBJ, typename R>
+__device__ __forceinline__ void whole_kernel(TransportArgs<R>& a, const SegDev<R>* segs)
+{
+    extern __shared__ unsigned long long lds[];
+    constexpr int WAVES = 16;          // of a block, at most
+    __shared__ uint32_t next[WAVES], end[WAVES];
+    BlockTally bt;
+    if (threadIdx.x < WAVES) end[threadIdx.x] = 0;
+    lds_setup(a, bt, lds);
+    const int lane = threadIdx.x & 63;
+    const uint64_t t0 = wall_clock64();
+    // the waves of a block take tickets from all over the run
+    const uint32_t own = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t wave = own * gridDim.x + blockIdx.x;
+    const uint32_t total = (uint32_t)a.total;
+    const uint32_t first = wave * a.chunk_ballistic < total ? wave * a.chunk_ballistic : total;
+    Tickets T;
+    T.tk = first;
+    T.tk_end = total - first > a.chunk_ballistic ? first + a.chunk_ballistic : total;
+    T.drained = T.tk == T.tk_end;
+    QRun Q;
+    Q.q = first;
+    Q.q_end = T.tk_end;
+    const uint32_t queued = (uint32_t)ballistic_phase<ARR, OBJ, true>(a, bt, segs, T, Q, lane);
+    const uint64_t t1 = wall_clock64();
+    // publish the wave's records to the block: all lanes' stores, then next, then end
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    if (lane == 0) {
+        __hip_atomic_store(&next[own], first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(&end[own], queued, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __builtin_amdgcn_wave_barrier();
+    diffusive_phase<ARR, OBJ, true>(a, bt, segs, BlockQueue{next, end, own, blockDim.x / 64}, 0u, 0u, lane);
+    if (threadIdx.x == 0 && blockIdx.x % 8 == 0) {
+        atomicAdd((unsigned long long*)&a.qstate[QS_TIMES], (unsigned long long)(t1 - t0));
+        atomicAdd((unsigned long long*)&a.qstate[QS_TIMES + 1], (unsigned long long)(wall_clock64() - t1));
+    }
+    lds_flush(a, bt);
+}
+
+// Four waves per SIMD (FP64: three) fit without spills in the steps.
+template <bool ARR, bool OBJ>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
+k_whole32(TransportArgs<float> a, const SegDev<float>* __restrict__ segs)
+{
+    whole_kernel<ARR, OBJ>(a, segs);
+}
+template <bool ARR, bool OBJ>
+__global__ void __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3)))
+k_whole64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
+{
+    whole_kernel<ARR, OBJ>(a, segs);
+}
+
+// Ranges of words to clear: a run's outputs and a round's counters.
+struct Ranges {
+    uint64_t* p[6] = {};
+    uint64_t n[6] = {};
+    void add(uint64_t* q, uint64_t m)
+    {
+        int i = 0;
+        while (n[i] != 0) ++i;
+        p[i] = q;
+        n[i] = q ? m : 0;
+    }
+};
+
+// (A kernel, so that it can sit in a graph; one for all ranges, a launch costs more than clearing them.)
+__global__ void k_clear(Ranges c)
 {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_counts; i += stride) counts[i] = 0;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_counters; i += stride) counters[i] = 0;
-}
-
-// Reset a round's ticket counters and queue length.
-__global__ void k_round_reset(uint64_t* qstate)
-{
-    for (uint32_t i = threadIdx.x; i < QSTATE_WORDS; i += blockDim.x) qstate[i] = 0;
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < c.n[k]; i += stride) c.p[k][i] = 0;
 }
 
 // profiles = counts / (N_seg * bin area); FP64.
@@ -718,30 +850,16 @@ __global__ void k_normalize(const unsigned long long* __restrict__ counts, const
     }
 }
 
-static int zero_u64(uint64_t* p, uint64_t n, LaunchSink& sink)
+static int put_clear(const Ranges& c, LaunchSink& sink)
 {
-    if (!p || n == 0) return SPX_OK;
+    uint64_t n = 0;
+    for (uint64_t m : c.n) n = std::max(n, m);
     KLaunch k;
-    k.func = (const void*)k_zero;
+    k.func = (const void*)k_clear;
     k.grid = dim3((unsigned)((n + 255) / 256 < 4096 ? (n + 255) / 256 + 1 : 4096));
     k.block = dim3(256);
-    k.arg((unsigned long long*)p);
-    k.arg(n);
-    k.arg((unsigned long long*)nullptr);
-    k.arg((uint64_t)0);
+    k.arg(c);
     return sink.put(k);
-}
-
-static int put_zero(Plan* P, const Outputs& o, LaunchSink& sink)
-{
-    SPX_TRY(zero_u64(o.counts, P->n_bins_total, sink));
-    SPX_TRY(zero_u64(o.counters, (uint64_t)P->n_seg * N_COUNTERS, sink));
-    if (o.arr_E) {
-        SPX_TRY(zero_u64(o.arr_E, (uint64_t)P->n_seg * SPX_ARRIVAL_E_BINS, sink));
-        SPX_TRY(zero_u64(o.arr_A, (uint64_t)P->n_seg * SPX_ARRIVAL_A_BINS, sink));
-        SPX_TRY(zero_u64(o.esum, P->n_bins_total, sink));
-    }
-    return SPX_OK;
 }
 
 static int put_normalize(Plan* P, const uint64_t* d_counts, double* d_profiles, LaunchSink& sink)
@@ -766,12 +884,12 @@ int StreamSink::put(const KLaunch& k)
         set_error("internal: malformed kernel launch");
         return SPX_ESTATE;
     }
-    if (events && k.phase == 1) SPX_HIP(hipEventRecord(events[3 * round], st));
+    if (events && (k.phase & 1)) SPX_HIP(hipEventRecord(events[3 * round], st));
     void* args[8];
     k.pointers(args);
     SPX_HIP(hipLaunchKernel(k.func, k.grid, k.block, args, k.smem, st));
-    if (events && k.phase == 1) SPX_HIP(hipEventRecord(events[3 * round + 1], st));
-    if (events && k.phase == 2) SPX_HIP(hipEventRecord(events[3 * round++ + 2], st));
+    if (events && (k.phase & 1)) SPX_HIP(hipEventRecord(events[3 * round + 1], st));
+    if (events && (k.phase & 2)) SPX_HIP(hipEventRecord(events[3 * round++ + 2], st));
     return SPX_OK;
 }
 
@@ -803,6 +921,7 @@ template <> struct Path<float> {
     static const float* edges(const Plan* P) { return P->d_edges32; }
     static const void* ballistic(const Plan* P, bool arr) { return SPX_INSTANCE(k_ballistic32, arr, P->has_objects); }
     static const void* diffusive(const Plan* P, bool arr) { return SPX_INSTANCE(k_diffusive32, arr, P->has_objects); }
+    static const void* whole(const Plan* P, bool arr) { return SPX_INSTANCE(k_whole32, arr, P->has_objects); }
     static constexpr int IDLE = WALK_IDLE;
 };
 template <> struct Path<double> {
@@ -812,6 +931,7 @@ template <> struct Path<double> {
     static const double* edges(const Plan* P) { return P->d_edges64; }
     static const void* ballistic(const Plan* P, bool arr) { return SPX_INSTANCE(k_ballistic64, arr, P->has_objects); }
     static const void* diffusive(const Plan* P, bool arr) { return SPX_INSTANCE(k_diffusive64, arr, P->has_objects); }
+    static const void* whole(const Plan* P, bool arr) { return SPX_INSTANCE(k_whole64, arr, P->has_objects); }
     static constexpr int IDLE = WALK_IDLE64;
 };
 }  // namespace
@@ -834,7 +954,7 @@ uint64_t rounds_of(uint64_t total, uint64_t round_max)
     return total == 0 ? 0 : (total + round_max - 1) / round_max;
 }
 
-// Blocks of a round of `total` tickets, out of `blocks`: a wave of a small run costs more to start and end
+// Blocks of a round of `total` tickets with a kernel per phase, out of `blocks`: a wave of a small run costs more to start and end
 // (its block clears and flushes the LDS tally) than its share of the work, and histories step faster
 // with fewer waves on their SIMD.  Waves per SIMD by tickets per lane of one wave per SIMD; ballistic
 // + diffusive kernel at 1, 2, 3, 4, 5 of them: 1e4 atoms 0.26, 0.28, 0.31, 0.34, 0.36 ms; 1e5 (1.5 tickets)
@@ -848,12 +968,46 @@ static int blocks_of(uint64_t total, int blocks, int threads, int n_simd)
     return std::min(blocks, (w * n_simd * 64 + threads - 1) / threads);
 }
 
+// Waves per SIMD of a run that takes both phases in one kernel, one block of all of them per CU; 0: two
+// kernels.  A kernel per phase waits twice for its longest histories, but shares the work over the whole
+// device and has more waves resident, which wins in long runs, and earlier where the chambers differ (the
+// waves of a block share walks, blocks do not).  Two kernels / one at 2, 3, 4 waves [ms]: single target
+// at 0.5 Pa, 1e5 atoms (1.5 tickets per lane of one wave per SIMD) 0.372 / 0.288, 0.300, 0.324; 1e6 (15)
+// 0.80 / 0.68, 0.62, 0.64; 5e6 (76) 1.96 / 2.40, 1.92, 1.74; 1e7 3.29 / 4.55, 3.56, 3.15; four cathodes, 7e6
+// 2.38 / 2.97, 2.35, 2.31, 2.3e7 5.95 / 9.2, 7.1, 6.6.  Chambers of 0.1 to 2 Pa: 3e5 atoms 2.96 / 2.32, 2.23,
+// 2.24; 1e6 3.59 / 4.03, 3.73, 3.47; 2e6 4.80 / 6.32, 5.40, 5.08.  FP64 (three waves at most), four
+// cathodes: 2e5 1.19 / 0.96, 0.88; 5e5 2.21 / 1.36, 1.46; 4e6 6.77 / 7.08, 5.30.
+int whole_waves(const Plan* P, uint64_t total, const Shape& sh, bool fp64)
+{
+    const int n_simd = 4 * P->n_cu;
+    if (!sh.whole || total == 0 || (int64_t)std::min(sh.blocks, sh.blocks_diff) * sh.threads < (int64_t)n_simd * 64)
+        return 0;                  // (a grid that the caller made smaller than that stays as it is)
+    double lo = P->seg[0].pressure, hi = lo;
+    for (const auto& s : P->seg) {
+        lo = std::min(lo, s.pressure);
+        hi = std::max(hi, s.pressure);
+    }
+    const uint64_t per_lane = total / ((uint64_t)n_simd * 64);
+    if (per_lane >= (hi > 2.0 * lo ? 16u : 80u)) return 0;
+    if (fp64) return per_lane < 8 ? 2 : 3;
+    return per_lane < 4 ? 2 : per_lane < 20 ? 3 : 4;
+}
+
 template <typename R>
 int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tfirst, uint64_t total,
                     const Shape& sh, const QueueMem& q, LaunchSink& sink)
 {
     using K = Path<R>;
-    SPX_TRY(put_zero(P, o, sink));
+    Ranges clear;
+    clear.add(o.counts, P->n_bins_total);
+    clear.add(o.counters, (uint64_t)P->n_seg * N_COUNTERS);
+    if (o.arr_E) {
+        clear.add(o.arr_E, (uint64_t)P->n_seg * SPX_ARRIVAL_E_BINS);
+        clear.add(o.arr_A, (uint64_t)P->n_seg * SPX_ARRIVAL_A_BINS);
+        clear.add(o.esum, P->n_bins_total);
+    }
+    clear.add(q.qstate, QSTATE_WORDS);     // the first round's
+    SPX_TRY(put_clear(clear, sink));
     TransportArgs<R> a;
     std::memset(&a, 0, sizeof(a));     // padding too: launches are compared bytewise
     a.segs = K::segs(P);
@@ -904,9 +1058,10 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
     const uint64_t per_round = n_rounds ? (total + n_rounds - 1) / n_rounds : 0;
     const int blocks = blocks_of(per_round, sh.blocks, sh.threads, a.n_simd);
     const int blocks_diff = blocks_of(per_round, a.arr_E ? blocks_diff_arr : sh.blocks_diff, sh.threads, a.n_simd);
-    // every queue slot a round can reserve: its atoms plus at most one unused run per wave
+    // every queue slot a round can reserve: its atoms plus, with two kernels, at most one unused run per wave
     const uint64_t waves = (uint64_t)blocks * (uint64_t)((sh.threads + 63) / 64);
-    if (n_rounds && per_round + waves * QUEUE_CHUNK > q.cap) {
+    const int ww = whole_waves(P, per_round, sh, std::is_same<R, double>::value);
+    if (n_rounds && per_round + (ww > 0 ? 0 : waves * QUEUE_CHUNK) > q.cap) {
         set_error("internal: round larger than the thermalisation queue");
         return SPX_ESTATE;
     }
@@ -914,17 +1069,31 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
     for (uint64_t r = 0; r < n_rounds; ++r) {
         a.tbase = r * per_round;
         a.total = (a.tbase + per_round < total) ? per_round : total - a.tbase;
+        if (ww > 0) {
+            const uint64_t grid = std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)P->n_cu, a.total));
+            a.chunk_ballistic = (uint32_t)((a.total + grid * 4 * ww - 1) / (grid * 4 * ww));
+            KLaunch k;
+            k.func = K::whole(P, a.arr_E != nullptr);
+            k.grid = dim3((unsigned)grid);
+            k.block = dim3((unsigned)(256 * ww));
+            k.smem = (uint32_t)smem;
+            k.phase = 3;
+            k.arg(a);
+            k.arg(segs);
+            SPX_TRY(sink.put(k));
+            continue;
+        }
         // the largest power-of-two chunk in [TICKET_CHUNK, TICKET_CHUNK_BALLISTIC_MAX] that
         // still gives every wave about four chunks of the round
         uint64_t cb = TICKET_CHUNK;
         while (2 * cb <= TICKET_CHUNK_BALLISTIC_MAX && 2 * cb * 4 * waves <= a.total) cb *= 2;
         cb = chunk_of(a.total, a.n_simd, cb);
         a.chunk_ballistic = (uint32_t)cb;
-        KLaunch reset;
-        reset.func = (const void*)k_round_reset;
-        reset.block = dim3(64);
-        reset.arg(q.qstate);
-        SPX_TRY(sink.put(reset));
+        if (r > 0) {
+            Ranges c;
+            c.add(q.qstate, QSTATE_WORDS);
+            SPX_TRY(put_clear(c, sink));
+        }
         KLaunch bal;
         bal.func = K::ballistic(P, a.arr_E != nullptr);
         bal.grid = dim3((unsigned)blocks);

@@ -1,0 +1,76 @@
+"""Runs that take both phases in one kernel: sizes at the edges of its waves per SIMD, of its blocks and of
+its range, against the same run as a kernel per phase (which a grid of less than a wave per SIMD
+selects).  A history does not depend on the lane that takes it: every output is equal to the bit."""
+import numpy as np
+import pytest
+
+import sputter_inputs as si
+from parity import say
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2411_14413_amd as spx  # noqa: E402
+
+# one ticket per lane of one wave per SIMD
+LANES = 256 * torch.cuda.get_device_properties(0).multi_processor_count
+KEYS = ("counts", "counters", "records", "profiles", "arrival_energy", "arrival_angle", "energy_sum")
+
+
+def _systems(n):
+    k = lambda f: max(1, int(n * f))     # noqa: E731
+    return {
+        "single": [si.single_ni(0.5, n)],
+        "dense": [si.single_ni(2.0, n)],
+        "pressures": [si.single_ni(0.5, n - 2 * (n // 3)), si.single_ni(0.0, n // 3), si.single_ni(2.0, n // 3)],
+        "chimneys": [si.with_chimneys(si.quaternary(0.8, counts=[k(0.4), k(0.1), k(0.3), k(0.2)]))],
+    }
+
+
+@pytest.mark.parametrize("arrivals", [False, True])
+@pytest.mark.parametrize("system, n", [
+    ("single", 1), ("single", 255), ("single", 4097), ("single", 4 * LANES - 1), ("single", 4 * LANES),
+    ("single", 20 * LANES), ("dense", 3 * LANES + 17), ("pressures", 3), ("pressures", 16 * LANES - 1),
+    ("pressures", 16 * LANES), ("chimneys", 1000), ("chimneys", 5 * LANES)])
+def test_equals_two_kernels(system, n, arrivals):
+    say(f"{system}, {n} atoms, arrivals {arrivals}")
+    plan = spx.Plan(_systems(n)[system], si.Params())
+    outs = [plan.run(seed=77, records=True, arrivals=arrivals)]
+    tb, td = plan.phase_times()
+    assert tb > 0 and td > 0
+    plan.set_launch(LANES // 512, 256, 4, 16, 8)
+    outs.append(plan.run(seed=77, records=True, arrivals=arrivals))
+    torch.cuda.synchronize()
+    for key in KEYS:
+        if key in outs[0] and outs[0][key] is not None:
+            assert torch.equal(outs[0][key], outs[1][key]), key
+    C = outs[0]["counters"]
+    assert C[:, 0].sum().item() == sum(c.n_particles for cfg in _systems(n)[system] for c in cfg.cathodes)
+
+
+@pytest.mark.parametrize("n", [7, 5000, 100001])
+def test_fp64_equals_two_kernels(n):
+    # a particle's history depends on its number, not on how many there are
+    say(f"FP64, {n} atoms")
+    big = 17 * LANES
+    recs = []
+    for k in (n, big):
+        cfg = [si.single_ni(0.5, k), si.single_ni(0.1, 10)]
+        recs.append(spx.records_to_numpy(spx.Plan(cfg, si.Params(), precision=64).run(seed=5, records=True)["records"]))
+    assert np.array_equal(recs[0][:n], recs[1][:n])
+
+
+@pytest.mark.parametrize("n", [1398080, 1398081, 3000000])
+def test_rounds_of_the_scratch_array(n):
+    # 1 398 080 slots: one full round, two, three
+    say(f"{n} atoms from the scratch array")
+    plan = spx.Plan([si.single_ni(0.5, n)], si.Params())
+    ref = plan.run(seed=9, records=True)
+    got = plan.allocate(records=True)
+    plan.run_noalloc_into(9, got)
+    torch.cuda.synchronize()
+    for key in ("counts", "counters", "records", "profiles"):
+        assert torch.equal(got[key].view(-1), ref[key].view(-1)), key
