@@ -93,11 +93,9 @@ extern "C" int spx_run_noalloc(spx_plan* P, uint64_t seed, const spx_outputs* ou
                   " bytes of queue slack, more than the " + std::to_string(SCRATCH_BYTES) + "-byte scratch array holds");
         return SPX_EINVAL;
     }
-    // rounds that take both phases in one kernel reserve no runs: they may fill the queue (4.6e6 atoms of
-    // four cathodes in 4 rounds instead of 5)
-    const uint64_t full = std::min<uint64_t>(ROUND_MAX, q.cap), n = rounds_of(P->n_tickets, full);
-    const bool whole = n > 0 && whole_waves(P, (P->n_tickets + n - 1) / n, sh, false) > 0;
-    q.round_max = whole ? full : std::min<uint64_t>(full, q.cap - slack);
+    // rounds that take both phases in one kernel reserve no runs and may hold more tickets than the queue slots
+    const uint64_t whole = whole_limit(P, sh);
+    q.round_max = whole > 0 ? whole : std::min<uint64_t>(ROUND_MAX, q.cap - slack);
     Outputs o;
     o.counts = out->counts;
     o.counters = out->counters;

@@ -95,6 +95,7 @@ template <typename R> struct TransportArgs {
     int32_t defer_min;          // diffusive phase: held steps a wave's surface tests wait for at least
     int32_t walk_idle;          // diffusive phase: ... and the idle rounds of the lanes that hold them
     uint32_t chunk_ballistic;   // ballistic phase: tickets a wave claims per atomic (whole kernel: tickets of a wave)
+    uint32_t wave_slots;        // whole kernel: queue slots of a wave
     uint32_t n_bins;            // tally bins of the plan
     int32_t lds_counters;       // per-segment counters privatised in LDS
     int32_t lds_tally;          // whole tally privatised in LDS (u32 per bin)
@@ -204,7 +205,7 @@ struct LaunchSink {
 struct Shape {
     int blocks = 0, blocks_diff = 0, threads = 256, refill_min = REFILL, refill_ballistic = REFILL_BALLISTIC,
         defer_min = DEFER_MIN;
-    bool whole = true;          // runs of whole_waves() take both phases in one kernel
+    bool whole = true;          // rounds of up to whole_limit() take both phases in one kernel
 };
 
 // Queue of thermalised atoms and ticket counters a run works in: the plan's own allocation, or
@@ -292,8 +293,8 @@ struct StreamSink : LaunchSink {
     int put(const KLaunch& k) override;
 };
 uint64_t rounds_of(uint64_t total, uint64_t round_max = ROUND_MAX);
-// Waves per SIMD of a round of `total` tickets whose two phases run in one kernel; 0: a kernel per phase.
-int whole_waves(const Plan* P, uint64_t total, const Shape& sh, bool fp64);
+// Tickets of a round that takes both phases in one kernel, at most; 0: rounds take a kernel per phase.
+uint64_t whole_limit(const Plan* P, const Shape& sh);
 // The plan's current launch geometry and thresholds.
 Shape plan_shape(const Plan* P);
 // Launch geometry of the FP64 kernels of a plan.

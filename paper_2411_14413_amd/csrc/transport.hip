@@ -456,9 +456,10 @@ __device__ __forceinline__ void diffusive_loop(const TransportArgs<R>& a, const 
 
 // Ballistic phase: every ticket of the round (WHOLE: of the run T that the wave starts with, its queue slots
 // from Q.q on), from launch until the atom ends on a surface, escapes, or thermalises (then it is queued for the
-// diffusive phase).  Returns the wave's next free slot.
-template <bool ARR, bool OBJ, bool WHOLE, typename R>
-__device__ __forceinline__ uint64_t ballistic_phase(TransportArgs<R>& a, const BlockTally& bt,
+// diffusive phase).  LIMITED: the slots may not hold them all; it ends while the lanes' atoms still fit.
+// Returns the wave's next free slot and its next ticket.
+template <bool ARR, bool OBJ, bool WHOLE, bool LIMITED, typename R>
+__device__ __forceinline__ QRun ballistic_phase(TransportArgs<R>& a, const BlockTally& bt,
                                                 const SegDev<R>* __restrict__ segs, Tickets T, QRun Q, int lane)
 {
     using O = std::conditional_t<OBJ, OwnObjects, NoObjects>;
@@ -474,7 +475,8 @@ __device__ __forceinline__ uint64_t ballistic_phase(TransportArgs<R>& a, const B
         settle_ballistic<ARR>(a, bt, segs, pid, seg, p, acc, Q, lane);
         const uint64_t dead = __ballot(p.st == ST_DEAD);
         const int n_dead = __popcll(dead);
-        if (!T.drained && n_dead > 0 && (n_dead >= a.refill_ballistic || n_dead == 64)) {
+        const bool drained = T.drained || (LIMITED && Q.q_end - Q.q < 64);
+        if (!drained && n_dead > 0 && (n_dead >= a.refill_ballistic || n_dead == 64)) {
             const uint32_t my = claim<WHOLE, true>(T, &a.qstate[QS_TICKETS], a.chunk_ballistic, (uint32_t)a.total,
                                                    dead, lane);
             if (my != NO_TICKET) {
@@ -511,16 +513,16 @@ __device__ __forceinline__ uint64_t ballistic_phase(TransportArgs<R>& a, const B
         }
         const uint64_t B = __ballot(p.st == ST_BALLISTIC);
         if (B == 0) {
-            if (T.drained) break;
+            if (drained) break;
             continue;
         }
         const int s0 = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)B) - 1);
         if constexpr (std::is_same<R, double>::value) {
             // lanes of other segments wait their turn: a second copy of the flight with per-lane
             // constants would only spill
-            ballistic_loop<O>(a, segs + s0, pid, p, seg == s0, T.drained);
+            ballistic_loop<O>(a, segs + s0, pid, p, seg == s0, T.drained || drained);
         } else if (__ballot(p.st == ST_BALLISTIC && seg != s0) == 0) {
-            ballistic_loop<O>(a, segs + s0, pid, p, true, T.drained);
+            ballistic_loop<O>(a, segs + s0, pid, p, true, T.drained || drained);
         } else if (p.st == ST_BALLISTIC) {
             // lanes of several segments: one flight with per-lane constants
             const SegDev<R>& s = segs[seg];
@@ -530,7 +532,7 @@ __device__ __forceinline__ uint64_t ballistic_phase(TransportArgs<R>& a, const B
     }
     if (!WHOLE) close_run(a, Q, lane);
     flush_acc(a, bt, acc);
-    return Q.q;
+    return QRun{Q.q, T.tk};
 }
 
 template <bool ARR, bool OBJ, typename R>
@@ -539,7 +541,7 @@ __device__ __forceinline__ void ballistic_kernel(TransportArgs<R>& a, const SegD
     extern __shared__ unsigned long long lds[];
     BlockTally bt;
     lds_setup(a, bt, lds);
-    ballistic_phase<ARR, OBJ, false>(a, bt, segs, Tickets(), QRun(), (int)(threadIdx.x & 63));
+    ballistic_phase<ARR, OBJ, false, false>(a, bt, segs, Tickets(), QRun(), (int)(threadIdx.x & 63));
     lds_flush(a, bt);
 }
 
@@ -752,12 +754,14 @@ k_diffusive64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
 
 // Both phases of a run in one kernel (whole_waves says which): a wave takes a fixed run of chunk_ballistic
 // tickets through the ballistic phase, its thermalised atoms into the run's own queue slots, and then
-// walks those and what is left of its block's.  Such a run is bound by the latency of its longest
+// walks those and what is left of its block's; where the queue holds fewer slots than that, in several
+// passes, its own walks only.  Such a run is bound by the latency of its longest
 // histories; here no walk waits for the slowest flight of another wave nor for a launch, and no
 // counter is shared between blocks: atomics on one line go at 11 ns each.  1e5 atoms of one cathode 0.372
-// -> 0.288 ms, 1e6 from four 0.84 -> 0.62, 4.6e6 1.80 -> 1.60; without gas 5e6 0.59 -> 0.13; 4.6e6 in rounds of the scratch
-// array 3.70 -> 2.50.
-template <bool ARR, bool OBJ, typename R>
+// -> 0.288 ms, 1e6 from four 0.84 -> 0.62, 4.6e6 1.80 -> 1.60; without gas 5e6 0.59 -> 0.13.  LIMITED: 4.6e6 from the
+// scratch array in one launch 1.77 ms (four rounds 2.50, five of a kernel per phase 3.70); as a run-time
+// switch it cost the instance with objects and arrivals 8 % in spills.
+template <bool ARR, bool OBJ, bool LIMITED, typename R>
 __device__ __forceinline__ void whole_kernel(TransportArgs<R>& a, const SegDev<R>* segs)
 {
     extern __shared__ unsigned long long lds[];
@@ -767,49 +771,55 @@ __device__ __forceinline__ void whole_kernel(TransportArgs<R>& a, const SegDev<R
     if (threadIdx.x < WAVES) end[threadIdx.x] = 0;
     lds_setup(a, bt, lds);
     const int lane = threadIdx.x & 63;
-    const uint64_t t0 = wall_clock64();
     // the waves of a block take tickets from all over the run
     const uint32_t own = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t wave = own * gridDim.x + blockIdx.x;
+    const uint32_t wave = own * gridDim.x + blockIdx.x, slot = wave * a.wave_slots;
     const uint32_t total = (uint32_t)a.total;
-    const uint32_t first = wave * a.chunk_ballistic < total ? wave * a.chunk_ballistic : total;
     Tickets T;
-    T.tk = first;
-    T.tk_end = total - first > a.chunk_ballistic ? first + a.chunk_ballistic : total;
-    T.drained = T.tk == T.tk_end;
-    QRun Q;
-    Q.q = first;
-    Q.q_end = T.tk_end;
-    const uint32_t queued = (uint32_t)ballistic_phase<ARR, OBJ, true>(a, bt, segs, T, Q, lane);
-    const uint64_t t1 = wall_clock64();
-    // publish the wave's records to the block: all lanes' stores, then next, then end
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    if (lane == 0) {
-        __hip_atomic_store(&next[own], first, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        __hip_atomic_store(&end[own], queued, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    T.tk = wave * a.chunk_ballistic < total ? wave * a.chunk_ballistic : total;
+    T.tk_end = total - T.tk > a.chunk_ballistic ? T.tk + a.chunk_ballistic : total;
+    uint64_t times[2] = {0, 0};
+    for (;;) {
+        T.drained = T.tk == T.tk_end;
+        const uint64_t t0 = wall_clock64();
+        const QRun e = ballistic_phase<ARR, OBJ, true, LIMITED>(a, bt, segs, T, QRun{slot, slot + a.wave_slots}, lane);
+        const uint64_t t1 = wall_clock64();
+        // publish the wave's records to the block: all lanes' stores, then next, then end
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        if (lane == 0) {
+            __hip_atomic_store(&next[own], slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __hip_atomic_store(&end[own], (uint32_t)e.q, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        __builtin_amdgcn_wave_barrier();
+        // (slots that are written again are walked by their wave alone)
+        diffusive_phase<ARR, OBJ, true>(a, bt, segs, BlockQueue{next, end, own, LIMITED ? 1u : blockDim.x / 64}, 0u, 0u,
+                                        lane);
+        times[0] += t1 - t0;
+        times[1] += wall_clock64() - t1;
+        if (!LIMITED) break;
+        T.tk = (uint32_t)e.q_end;
+        if (T.tk == T.tk_end) break;
     }
-    __builtin_amdgcn_wave_barrier();
-    diffusive_phase<ARR, OBJ, true>(a, bt, segs, BlockQueue{next, end, own, blockDim.x / 64}, 0u, 0u, lane);
     if (threadIdx.x == 0 && blockIdx.x % 8 == 0) {
-        atomicAdd((unsigned long long*)&a.qstate[QS_TIMES], (unsigned long long)(t1 - t0));
-        atomicAdd((unsigned long long*)&a.qstate[QS_TIMES + 1], (unsigned long long)(wall_clock64() - t1));
+        atomicAdd((unsigned long long*)&a.qstate[QS_TIMES], (unsigned long long)times[0]);
+        atomicAdd((unsigned long long*)&a.qstate[QS_TIMES + 1], (unsigned long long)times[1]);
     }
     lds_flush(a, bt);
 }
 
 // Four waves per SIMD (FP64: three) fit without spills in the steps.
-template <bool ARR, bool OBJ>
+template <bool ARR, bool OBJ, bool LIMITED>
 __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(4)))
 k_whole32(TransportArgs<float> a, const SegDev<float>* __restrict__ segs)
 {
-    whole_kernel<ARR, OBJ>(a, segs);
+    whole_kernel<ARR, OBJ, LIMITED>(a, segs);
 }
 template <bool ARR, bool OBJ>
 __global__ void __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(3)))
 k_whole64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
 {
-    whole_kernel<ARR, OBJ>(a, segs);
+    whole_kernel<ARR, OBJ, false>(a, segs);
 }
 
 // Ranges of words to clear: a run's outputs and a round's counters.
@@ -907,10 +917,12 @@ size_t transport_lds(const Plan* P, bool arrivals, bool* lds_counters, bool* lds
 }
 
 namespace {
-// The instance of a kernel template <arrival tallies, absorbing objects>.
-#define SPX_INSTANCE(kernel, arr, obj)                                                          \
-    ((arr) ? ((obj) ? (const void*)kernel<true, true> : (const void*)kernel<true, false>)       \
-           : ((obj) ? (const void*)kernel<false, true> : (const void*)kernel<false, false>))
+// The instance of a kernel template <arrival tallies, absorbing objects, ...>.
+#define SPX_INSTANCE(kernel, arr, obj, ...)                                                     \
+    ((arr) ? ((obj) ? (const void*)kernel<true, true __VA_OPT__(, ) __VA_ARGS__>                \
+                    : (const void*)kernel<true, false __VA_OPT__(, ) __VA_ARGS__>)              \
+           : ((obj) ? (const void*)kernel<false, true __VA_OPT__(, ) __VA_ARGS__>               \
+                    : (const void*)kernel<false, false __VA_OPT__(, ) __VA_ARGS__>))
 
 // The plan's constants and the kernels of a precision.
 template <typename R> struct Path;
@@ -921,8 +933,13 @@ template <> struct Path<float> {
     static const float* edges(const Plan* P) { return P->d_edges32; }
     static const void* ballistic(const Plan* P, bool arr) { return SPX_INSTANCE(k_ballistic32, arr, P->has_objects); }
     static const void* diffusive(const Plan* P, bool arr) { return SPX_INSTANCE(k_diffusive32, arr, P->has_objects); }
-    static const void* whole(const Plan* P, bool arr) { return SPX_INSTANCE(k_whole32, arr, P->has_objects); }
+    static const void* whole(const Plan* P, bool arr, bool limited)
+    {
+        return limited ? SPX_INSTANCE(k_whole32, arr, P->has_objects, true)
+                       : SPX_INSTANCE(k_whole32, arr, P->has_objects, false);
+    }
     static constexpr int IDLE = WALK_IDLE;
+    static constexpr bool LIMITED = true;
 };
 template <> struct Path<double> {
     static const SegDev<double>* segs(const Plan* P) { return P->d_seg64; }
@@ -931,8 +948,10 @@ template <> struct Path<double> {
     static const double* edges(const Plan* P) { return P->d_edges64; }
     static const void* ballistic(const Plan* P, bool arr) { return SPX_INSTANCE(k_ballistic64, arr, P->has_objects); }
     static const void* diffusive(const Plan* P, bool arr) { return SPX_INSTANCE(k_diffusive64, arr, P->has_objects); }
-    static const void* whole(const Plan* P, bool arr) { return SPX_INSTANCE(k_whole64, arr, P->has_objects); }
+    // (the queue of an FP64 plan holds its rounds)
+    static const void* whole(const Plan* P, bool arr, bool) { return SPX_INSTANCE(k_whole64, arr, P->has_objects); }
     static constexpr int IDLE = WALK_IDLE64;
+    static constexpr bool LIMITED = false;
 };
 }  // namespace
 
@@ -977,18 +996,23 @@ static int blocks_of(uint64_t total, int blocks, int threads, int n_simd)
 // 2.38 / 2.97, 2.35, 2.31, 2.3e7 5.95 / 9.2, 7.1, 6.6.  Chambers of 0.1 to 2 Pa: 3e5 atoms 2.96 / 2.32, 2.23,
 // 2.24; 1e6 3.59 / 4.03, 3.73, 3.47; 2e6 4.80 / 6.32, 5.40, 5.08.  FP64 (three waves at most), four
 // cathodes: 2e5 1.19 / 0.96, 0.88; 5e5 2.21 / 1.36, 1.46; 4e6 6.77 / 7.08, 5.30.
-int whole_waves(const Plan* P, uint64_t total, const Shape& sh, bool fp64)
+uint64_t whole_limit(const Plan* P, const Shape& sh)
 {
-    const int n_simd = 4 * P->n_cu;
-    if (!sh.whole || total == 0 || (int64_t)std::min(sh.blocks, sh.blocks_diff) * sh.threads < (int64_t)n_simd * 64)
+    const uint64_t lanes = 4 * (uint64_t)P->n_cu * 64;
+    if (!sh.whole || (uint64_t)std::min(sh.blocks, sh.blocks_diff) * (uint64_t)sh.threads < lanes)
         return 0;                  // (a grid that the caller made smaller than that stays as it is)
     double lo = P->seg[0].pressure, hi = lo;
     for (const auto& s : P->seg) {
         lo = std::min(lo, s.pressure);
         hi = std::max(hi, s.pressure);
     }
-    const uint64_t per_lane = total / ((uint64_t)n_simd * 64);
-    if (per_lane >= (hi > 2.0 * lo ? 16u : 80u)) return 0;
+    return (hi > 2.0 * lo ? 16 : 80) * lanes - 1;
+}
+
+static int whole_waves(const Plan* P, uint64_t total, const Shape& sh, bool fp64)
+{
+    if (total == 0 || total > whole_limit(P, sh)) return 0;
+    const uint64_t per_lane = total / (4 * (uint64_t)P->n_cu * 64);
     if (fp64) return per_lane < 8 ? 2 : 3;
     return per_lane < 4 ? 2 : per_lane < 20 ? 3 : 4;
 }
@@ -1058,10 +1082,17 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
     const uint64_t per_round = n_rounds ? (total + n_rounds - 1) / n_rounds : 0;
     const int blocks = blocks_of(per_round, sh.blocks, sh.threads, a.n_simd);
     const int blocks_diff = blocks_of(per_round, a.arr_E ? blocks_diff_arr : sh.blocks_diff, sh.threads, a.n_simd);
-    // every queue slot a round can reserve: its atoms plus, with two kernels, at most one unused run per wave
+    // every queue slot a round can reserve: its atoms plus at most one unused run per wave; in one kernel, its
+    // waves have fixed slots, at least a refill's
     const uint64_t waves = (uint64_t)blocks * (uint64_t)((sh.threads + 63) / 64);
     const int ww = whole_waves(P, per_round, sh, std::is_same<R, double>::value);
-    if (n_rounds && per_round + (ww > 0 ? 0 : waves * QUEUE_CHUNK) > q.cap) {
+    const uint64_t whole_grid = std::min<uint64_t>((uint64_t)P->n_cu, std::max<uint64_t>(1, per_round));
+    const uint64_t n_whole = whole_grid * 4 * (uint64_t)ww;
+    const uint64_t share = ww > 0 ? (per_round + n_whole - 1) / n_whole : 0;
+    const uint64_t wave_slots = ww > 0 ? std::min(share, q.cap / n_whole) : 0;
+    const bool limited = wave_slots < share;
+    if (n_rounds && (ww > 0 ? limited && (wave_slots < 64 || !K::LIMITED)
+                            : per_round + waves * QUEUE_CHUNK > q.cap)) {
         set_error("internal: round larger than the thermalisation queue");
         return SPX_ESTATE;
     }
@@ -1070,11 +1101,11 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
         a.tbase = r * per_round;
         a.total = (a.tbase + per_round < total) ? per_round : total - a.tbase;
         if (ww > 0) {
-            const uint64_t grid = std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)P->n_cu, a.total));
-            a.chunk_ballistic = (uint32_t)((a.total + grid * 4 * ww - 1) / (grid * 4 * ww));
+            a.chunk_ballistic = (uint32_t)share;
+            a.wave_slots = (uint32_t)wave_slots;
             KLaunch k;
-            k.func = K::whole(P, a.arr_E != nullptr);
-            k.grid = dim3((unsigned)grid);
+            k.func = K::whole(P, a.arr_E != nullptr, limited);
+            k.grid = dim3((unsigned)whole_grid);
             k.block = dim3((unsigned)(256 * ww));
             k.smem = (uint32_t)smem;
             k.phase = 3;

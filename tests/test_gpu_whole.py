@@ -63,9 +63,9 @@ def test_fp64_equals_two_kernels(n):
     assert np.array_equal(recs[0][:n], recs[1][:n])
 
 
-@pytest.mark.parametrize("n", [1398080, 1398081, 3000000])
-def test_rounds_of_the_scratch_array(n):
-    # 1 398 080 slots: one full round, two, three
+@pytest.mark.parametrize("n", [1398080, 1398081, 3000000, 80 * LANES + 5])
+def test_scratch_array(n):
+    # its 1 398 080 slots: all of them, then passes of a wave over its own slots, then two rounds of those
     say(f"{n} atoms from the scratch array")
     plan = spx.Plan([si.single_ni(0.5, n)], si.Params())
     ref = plan.run(seed=9, records=True)
