@@ -293,7 +293,8 @@ int spx_set_launch(spx_plan* plan, int32_t blocks, int32_t threads, int32_t refi
 
 /* Device time [ms] of the two phases of the last FP32 spx_run of this plan, summed over its
  * rounds (HIP events recorded between the kernels; waits for that run to finish).  Where both
- * phases run in one kernel, its time, split as sampled waves' times in them.  SPX_ESTATE before the first FP32 run. */
+ * phases run in one kernel, its time by the device's clock, split as sampled waves' times in them.
+ * SPX_ESTATE before the first FP32 run. */
 int spx_phase_times(spx_plan* plan, float* ms_ballistic, float* ms_diffusive);
 
 /* Copy the FP64 scattering table to the host: h_theta[ne * ns] (row i = log10 eps node),

@@ -685,7 +685,8 @@ Shape plan_shape(const Plan* P)
 }
 
 // The graph of a run: its launches as a chain of kernel nodes, with the phase events of each
-// round (recorded before the ballistic kernel, between the kernels and after the diffusive one).
+// round (recorded before the ballistic kernel, between the kernels and after the diffusive one; not where
+// one kernel takes both phases and keeps its own time: event nodes make such a short graph 21 us longer).
 static int build_graph(Plan* P, const std::vector<KLaunch>& L)
 {
     const size_t n_rounds = (size_t)rounds_of(P->n_tickets);
@@ -716,7 +717,7 @@ static int build_graph(Plan* P, const std::vector<KLaunch>& L)
         return SPX_OK;
     };
     for (const KLaunch& k : L) {
-        if (k.phase & 1) {
+        if (k.phase == 1) {
             if (round >= n_rounds) {
                 set_error("internal: more rounds in the run than in the plan");
                 return SPX_ESTATE;
@@ -737,8 +738,9 @@ static int build_graph(Plan* P, const std::vector<KLaunch>& L)
         prev = n;
         P->graph_launches.push_back(k);
         P->graph_nodes.push_back(n);
-        if (k.phase & 1) SPX_TRY(chain_event(P->phase_events[3 * round + 1]));
-        if (k.phase & 2) SPX_TRY(chain_event(P->phase_events[3 * round++ + 2]));
+        if (k.phase == 1) SPX_TRY(chain_event(P->phase_events[3 * round + 1]));
+        if (k.phase == 2) SPX_TRY(chain_event(P->phase_events[3 * round + 2]));
+        if (k.phase & 2) ++round;
     }
     if (round != n_rounds) {
         set_error("internal: unexpected number of rounds in the transport graph");
@@ -1183,6 +1185,21 @@ int spx_phase_times(spx_plan* P, float* ms_ballistic, float* ms_diffusive)
         return SPX_ESTATE;
     }
     SPX_HIP(hipSetDevice(P->device));
+    for (const KLaunch& k : P->graph_launches)
+        if (k.phase == 3) {
+            // both phases in one kernel: its time by the device's clock, split as sampled waves' times
+            uint64_t t[4] = {0, 0, 0, 0};
+            int khz = 0;
+            SPX_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, P->device));
+            SPX_HIP(hipEventSynchronize(P->done_event));
+            SPX_HIP(hipMemcpyAsync(t, P->d_qstate + QS_TIMES, sizeof(t), hipMemcpyDeviceToHost, P->work_stream));
+            SPX_HIP(hipStreamSynchronize(P->work_stream));
+            const double ms = khz > 0 ? (double)(t[3] - t[2]) / khz : 0.0;
+            const double share = t[0] + t[1] ? (double)t[0] / (double)(t[0] + t[1]) : 0.5;
+            *ms_ballistic = (float)(share * ms);
+            *ms_diffusive = (float)((1.0 - share) * ms);
+            return SPX_OK;
+        }
     const size_t n_ev = 3 * (size_t)rounds_of(P->n_tickets);
     float b = 0.f, d = 0.f;
     for (size_t r = 0; r + 2 < n_ev; r += 3) {
@@ -1193,17 +1210,6 @@ int spx_phase_times(spx_plan* P, float* ms_ballistic, float* ms_diffusive)
         b += t1;
         d += t2;
     }
-    // both phases in one kernel: its time, split as its waves' times in them
-    for (const KLaunch& k : P->graph_launches)
-        if (k.phase == 3) {
-            uint64_t t[2] = {0, 0};
-            SPX_HIP(hipMemcpyAsync(t, P->d_qstate + QS_TIMES, sizeof(t), hipMemcpyDeviceToHost, P->work_stream));
-            SPX_HIP(hipStreamSynchronize(P->work_stream));
-            const double share = t[0] + t[1] ? (double)t[0] / (double)(t[0] + t[1]) : 0.5;
-            d += (float)((1.0 - share) * b);
-            b = (float)(share * b);
-            break;
-        }
     *ms_ballistic = b;
     *ms_diffusive = d;
     return SPX_OK;

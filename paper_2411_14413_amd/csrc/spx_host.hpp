@@ -123,7 +123,7 @@ static_assert(QUEUE_CHUNK == 64, "queue runs hold one slot per lane of a wave");
 // The round's three counters (ballistic tickets, queue length, diffusive tickets) sit 256 bytes
 // apart: every wave's claims and queue reservations are atomics on them, and on one cache line
 // the two kinds of atomics of the ballistic phase would queue behind each other.  QS_TIMES: ticks that
-// sampled waves of the whole kernel spent in either phase.
+// sampled waves of the whole kernel spent in either phase, its start and its end.
 constexpr uint64_t QS_TICKETS = 0, QS_QUEUE = 32, QS_DIFFUSIVE = 64, QS_TIMES = 96, QSTATE_WORDS = 128;
 constexpr uint64_t QUEUE_SLACK_WAVES = 8192;  // waves that may leave slots unused (32 per CU, 256 CUs)
 constexpr size_t LDS_COUNTERS_MAX = 16384;   // bytes: up to 256 segments

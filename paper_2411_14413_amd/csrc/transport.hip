@@ -779,6 +779,7 @@ __device__ __forceinline__ void whole_kernel(TransportArgs<R>& a, const SegDev<R
     T.tk = wave * a.chunk_ballistic < total ? wave * a.chunk_ballistic : total;
     T.tk_end = total - T.tk > a.chunk_ballistic ? T.tk + a.chunk_ballistic : total;
     uint64_t times[2] = {0, 0};
+    if (threadIdx.x == 0 && blockIdx.x == 0) a.qstate[QS_TIMES + 2] = wall_clock64();
     for (;;) {
         T.drained = T.tk == T.tk_end;
         const uint64_t t0 = wall_clock64();
@@ -806,6 +807,7 @@ __device__ __forceinline__ void whole_kernel(TransportArgs<R>& a, const SegDev<R
         atomicAdd((unsigned long long*)&a.qstate[QS_TIMES + 1], (unsigned long long)times[1]);
     }
     lds_flush(a, bt);
+    if (threadIdx.x == 0) atomicMax((unsigned long long*)&a.qstate[QS_TIMES + 3], (unsigned long long)wall_clock64());
 }
 
 // Four waves per SIMD (FP64: three) fit without spills in the steps.
@@ -894,12 +896,12 @@ int StreamSink::put(const KLaunch& k)
         set_error("internal: malformed kernel launch");
         return SPX_ESTATE;
     }
-    if (events && (k.phase & 1)) SPX_HIP(hipEventRecord(events[3 * round], st));
+    if (events && k.phase == 1) SPX_HIP(hipEventRecord(events[3 * round], st));
     void* args[8];
     k.pointers(args);
     SPX_HIP(hipLaunchKernel(k.func, k.grid, k.block, args, k.smem, st));
-    if (events && (k.phase & 1)) SPX_HIP(hipEventRecord(events[3 * round + 1], st));
-    if (events && (k.phase & 2)) SPX_HIP(hipEventRecord(events[3 * round++ + 2], st));
+    if (events && k.phase == 1) SPX_HIP(hipEventRecord(events[3 * round + 1], st));
+    if (events && k.phase == 2) SPX_HIP(hipEventRecord(events[3 * round++ + 2], st));
     return SPX_OK;
 }
 
@@ -1022,16 +1024,6 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
                     const Shape& sh, const QueueMem& q, LaunchSink& sink)
 {
     using K = Path<R>;
-    Ranges clear;
-    clear.add(o.counts, P->n_bins_total);
-    clear.add(o.counters, (uint64_t)P->n_seg * N_COUNTERS);
-    if (o.arr_E) {
-        clear.add(o.arr_E, (uint64_t)P->n_seg * SPX_ARRIVAL_E_BINS);
-        clear.add(o.arr_A, (uint64_t)P->n_seg * SPX_ARRIVAL_A_BINS);
-        clear.add(o.esum, P->n_bins_total);
-    }
-    clear.add(q.qstate, QSTATE_WORDS);     // the first round's
-    SPX_TRY(put_clear(clear, sink));
     TransportArgs<R> a;
     std::memset(&a, 0, sizeof(a));     // padding too: launches are compared bytewise
     a.segs = K::segs(P);
@@ -1097,6 +1089,17 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
         return SPX_ESTATE;
     }
     const SegDev<R>* segs = K::segs(P);
+    Ranges clear;
+    clear.add(o.counts, P->n_bins_total);
+    clear.add(o.counters, (uint64_t)P->n_seg * N_COUNTERS);
+    if (o.arr_E) {
+        clear.add(o.arr_E, (uint64_t)P->n_seg * SPX_ARRIVAL_E_BINS);
+        clear.add(o.arr_A, (uint64_t)P->n_seg * SPX_ARRIVAL_A_BINS);
+        clear.add(o.esum, P->n_bins_total);
+    }
+    // the first round's counters (the times of a run in one kernel outlast autotuning)
+    clear.add(q.qstate, ww > 0 ? QSTATE_WORDS : QS_TIMES);
+    SPX_TRY(put_clear(clear, sink));
     for (uint64_t r = 0; r < n_rounds; ++r) {
         a.tbase = r * per_round;
         a.total = (a.tbase + per_round < total) ? per_round : total - a.tbase;
@@ -1122,7 +1125,7 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
         a.chunk_ballistic = (uint32_t)cb;
         if (r > 0) {
             Ranges c;
-            c.add(q.qstate, QSTATE_WORDS);
+            c.add(q.qstate, QS_TIMES);
             SPX_TRY(put_clear(c, sink));
         }
         KLaunch bal;

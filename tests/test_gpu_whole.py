@@ -41,6 +41,9 @@ def test_equals_two_kernels(system, n, arrivals):
     outs = [plan.run(seed=77, records=True, arrivals=arrivals)]
     tb, td = plan.phase_times()
     assert tb > 0 and td > 0
+    if n == 255:
+        plan.autotune()
+        assert plan.phase_times() == (tb, td)
     plan.set_launch(LANES // 512, 256, 4, 16, 8)
     outs.append(plan.run(seed=77, records=True, arrivals=arrivals))
     torch.cuda.synchronize()
