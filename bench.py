@@ -5,7 +5,7 @@ Workload (default): the single planar Ni target of the paper's Methods geometry
 stand-in, three chambers in one batch -- Ar at 0.5 Pa, 0 Pa (line of sight) and
 2 Pa (thermalisation dominated) -- 1e7 particles each (3e7 per step), FP32
 transport with integer tallies.  A step is one replay of the plan's HIP graph:
-zero tallies, the persistent transport kernel over all three chambers, and the
+zero tallies, the transport kernels over all three chambers, and the
 FP64 normalisation of the tallies to deposition profiles.  Inputs are synthetic
 (seeded geometry and gas; every random number is generated on the GPU).
 

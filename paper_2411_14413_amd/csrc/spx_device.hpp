@@ -947,8 +947,9 @@ __device__ __forceinline__ bool diffusive_single(R lam_l2, uint32_t cfgcat, uint
 // below its cap) until those that hold a step have waited long enough.  Returns whether the lane
 // holds a step (in p.d, p.r2).
 //
-// Bound by VALU issue: every instruction of a wave takes four clocks of its SIMD (a transcendental
-// eight; a 32x32->64 multiply-add four, as an addition), so the round below (both steps of a Philox
+// Bound by VALU issue: every instruction of a wave takes four clocks (a transcendental eight; a
+// 32x32->64 multiply-add four, as an addition) and the SIMD's waves together issue one in 3.4 (counters,
+// single target), so the round below (both steps of a Philox
 // block) is written for its instruction count, 83 against 113 in a form that selected, committed and
 // counted each step apart.  A lane leaves the loop with the step that leaves its ball, so its
 // registers keep offset, direction and length without a copy; the even step goes from p.xc to b, the

@@ -65,7 +65,7 @@ template <typename R> struct alignas(16) ThermRec {
 static_assert(sizeof(ThermRec<float>) == 48, "ThermRec layout");
 static_assert(sizeof(ThermRec<double>) == 80, "ThermRec layout");
 
-// Launch arguments of the two transport kernels of a precision (one round = one chunk of the
+// Launch arguments of the transport kernels of a precision (one round = one chunk of the
 // ticket space: the ballistic phase of every ticket, then the diffusive phase of the atoms
 // it thermalised).
 template <typename R> struct TransportArgs {
@@ -201,7 +201,7 @@ struct LaunchSink {
     virtual ~LaunchSink() = default;
 };
 
-// Launch geometry and thresholds of the two persistent transport kernels.
+// Launch geometry of the two persistent transport kernels, thresholds of all.
 struct Shape {
     int blocks = 0, blocks_diff = 0, threads = 256, refill_min = REFILL, refill_ballistic = REFILL_BALLISTIC,
         defer_min = DEFER_MIN;

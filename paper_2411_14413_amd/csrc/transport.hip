@@ -1,13 +1,13 @@
 // transport.hip -- the transport kernels of both precisions and their tallies.
 //
 // Every (configuration, cathode) segment of a plan runs in rounds of at most ROUND_MAX (FP64:
-// ROUND_MAX64) tickets, each round as two persistent launches.  The ballistic kernel takes
-// every ticket of the round from its launch through its flights and collisions; an atom that
-// ends on a surface (or escapes) is finished there, an atom that thermalises is handed over to
-// a queue in HBM (48 B, in FP64 80 B, with the two numbers of its segment a step needs).  The
-// diffusive kernel then runs the walks of the queued atoms.  Each lane holds one atom in registers; when lanes die, the wave claims
-// a run of tickets with a single atomic (ballot + mbcnt prefix gives each dead lane its
-// ticket).  Splitting the history at thermalisation keeps every lane of a wave in the same
+// ROUND_MAX64) tickets, a long round as two persistent launches, another as one (whole_kernel).
+// The ballistic phase takes every ticket of the round from its launch through its flights and
+// collisions; an atom that ends on a surface (or escapes) is finished there, an atom that
+// thermalises is handed over to a queue in HBM (48 B, in FP64 80 B, with the two numbers of its
+// segment a step needs).  The diffusive phase then runs the walks of the queued atoms.  Each lane
+// holds one atom in registers; when lanes die, the wave claims a run of tickets with a single
+// atomic (ballot + mbcnt prefix gives each dead lane its ticket).  Splitting the history at thermalisation keeps every lane of a wave in the same
 // kind of event: new atoms (ballistic) and walkers (diffusive) never share a wave.  The
 // random numbers are keyed by (seed, segment, particle, event), so the result does not
 // depend on which lane, wave or launch ran an atom, nor on the queue order.  Deposits go
