@@ -1,6 +1,8 @@
 """Runs that take both phases in one kernel: sizes at the edges of its waves per SIMD, of its blocks and of
 its range, against the same run as a kernel per phase (which a grid of less than a wave per SIMD
 selects).  A history does not depend on the lane that takes it: every output is equal to the bit."""
+from dataclasses import replace
+
 import numpy as np
 import pytest
 
@@ -77,3 +79,22 @@ def test_scratch_array(n):
     torch.cuda.synchronize()
     for key in ("counts", "counters", "records", "profiles"):
         assert torch.equal(got[key].view(-1), ref[key].view(-1)), key
+
+
+@pytest.mark.parametrize("arrivals", [False, True])
+def test_the_largest_tally_and_counters_in_lds(arrivals):
+    # 256 segments (their counters 16 384 bytes) of 48 bins (the tally 49 152 bytes): all that a block may keep
+    say("256 segments of 48 bins")
+    cfgs = []
+    for c in range(64):
+        cfg = si.quaternary(0.5 + 0.005 * c, counts=[40, 20, 30, 10])
+        cfgs.append(replace(cfg, grid=replace(cfg.grid, nu=8, nv=6)))
+    plan = spx.Plan(cfgs, si.Params())
+    assert plan.n_segments == 256 and plan.n_bins == 12288
+    outs = [plan.run(seed=3, arrivals=arrivals)]
+    plan.set_launch(LANES // 512, 256, 4, 16, 8)
+    outs.append(plan.run(seed=3, arrivals=arrivals))
+    for key in KEYS:
+        if outs[0].get(key) is not None:
+            assert torch.equal(outs[0][key], outs[1][key]), key
+    assert outs[0]["counters"].sum(0)[0].item() == 6400
