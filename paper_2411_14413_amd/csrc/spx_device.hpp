@@ -471,13 +471,15 @@ struct SpanObjects {
 // where reads spread through the test cost several, and the tail of a run (one test per pass) keeps them
 // for many passes.  1e5 atoms of one cathode 431 -> 380 us, four cathodes 6.14 -> 5.96 ms, the 64-chamber
 // sweep's half 92.4 -> 91.8.  FP64 values would take twice the registers, and beside the code of the
-// absorbing objects they spill (four cathodes in chimneys, 2.3e7 atoms: 5.97 ms from the table, 6.24 as values), so
-// GeoOf takes the table there.
+// absorbing objects they spill at five waves per SIMD (four cathodes in chimneys, 2.3e7 atoms: 5.97 ms
+// from the table, 6.24 as values), so GeoOf takes the table there.  The tail of the kernel for both phases,
+// at four waves, takes values with objects too: in chimneys 1.2e5 atoms 0.73 -> 0.65 ms, 2.3e6 1.25 -> 1.20.
 template <typename R> struct SegGeo {
     R sub_n[3], sub_u[3], sub_v[3], sub_nc, sub_uc, sub_vc, half_u, half_v, sub_R2;
     R cat_n[3], cat_u[3], cat_v[3], cat_nc, cat_uc, cat_vc, cat_R2;
     R ch_R2, zlo, zhi;
-    int32_t shape;
+    int32_t shape, n_obj;
+    const ObjDev<R>* obj;
     __device__ __forceinline__ explicit SegGeo(const SegDev<R>& s)
     {
 #pragma unroll
@@ -503,6 +505,8 @@ template <typename R> struct SegGeo {
         zlo = s.zlo;
         zhi = s.zhi;
         shape = s.shape;
+        n_obj = s.n_obj;
+        obj = s.obj;
     }
 };
 template <bool OBJ, typename R>

@@ -571,7 +571,7 @@ k_ballistic64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
 // walkers end.  Bound by the latency of one pass, the longest walks being all that is left: the state
 // stays replicated in the span, so a pass starts without shuffles, and the surfaces are read once per
 // layout (GeoOf).
-template <bool ARR, bool OBJ, typename R>
+template <bool ARR, bool OBJ, bool WHOLE, typename R>
 __device__ __forceinline__ void tail_walk(const TransportArgs<R>& a, const BlockTally& bt,
                                           const SegDev<R>* __restrict__ segs, uint64_t D, int seg, R lam_l2,
                                           uint32_t cfgcat, uint32_t pid, Particle<R>& p, Walk<R>& wk, LaneAcc<true>& acc,
@@ -610,7 +610,7 @@ __device__ __forceinline__ void tail_walk(const TransportArgs<R>& a, const Block
             acc.seg = seg;
         }
         const SegDev<R>& S = segs[seg];
-        GeoOf<OBJ, R> geo(S);
+        GeoOf<OBJ && !WHOLE, R> geo(S);
         const uint64_t span_mask = sh == 6 ? ~0ull : (1ull << span) - 1;
         for (;;) {
             const uint32_t ej = p.e + 1u + (uint32_t)j;
@@ -711,7 +711,7 @@ __device__ __forceinline__ void diffusive_phase(TransportArgs<R>& a, const Block
             continue;
         }
         if (T.drained && __popcll(D) <= Walk<R>::COOP) {
-            tail_walk<ARR, OBJ>(a, bt, segs, D, seg, lam_l2, cfgcat, pid, p, wk, acc, lane);
+            tail_walk<ARR, OBJ, WHOLE>(a, bt, segs, D, seg, lam_l2, cfgcat, pid, p, wk, acc, lane);
             break;
         }
         diffusive_loop<ARR, OBJ>(a, bt, segs, seg, lam_l2, cfgcat, pid, p, wk, acc, T.drained);
