@@ -471,6 +471,7 @@ __device__ __forceinline__ QRun ballistic_phase(TransportArgs<R>& a, const Block
     LaneAcc<false> acc;
     int cur_pos = 0, last_pos = 0;        // wave-uniform current position in ticket order ...
     uint64_t cur_lo = 0, cur_hi = 0;      // ... and its ticket range (empty until the first refill)
+    int cur_seg = 0;                      // ... and its segment
     for (;;) {
         settle_ballistic<ARR>(a, bt, segs, pid, seg, p, acc, Q, lane);
         const uint64_t dead = __ballot(p.st == ST_DEAD);
@@ -507,6 +508,7 @@ __device__ __forceinline__ QRun ballistic_phase(TransportArgs<R>& a, const Block
             const uint64_t got = __ballot(my != NO_TICKET);
             if (got != 0) {
                 cur_pos = __builtin_amdgcn_readlane(last_pos, 63 - __clzll((long long)got));
+                cur_seg = __builtin_amdgcn_readlane(seg, 63 - __clzll((long long)got));
                 cur_lo = a.tfirst[cur_pos];
                 cur_hi = a.tfirst[cur_pos + 1];
             }
@@ -516,10 +518,14 @@ __device__ __forceinline__ QRun ballistic_phase(TransportArgs<R>& a, const Block
             if (drained) break;
             continue;
         }
-        const int s0 = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)B) - 1);
+        int s0 = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)B) - 1);
         if constexpr (std::is_same<R, double>::value) {
             // lanes of other segments wait their turn: a second copy of the flight with per-lane
-            // constants would only spill
+            // constants would only spill.  Those of segments that get no new lanes go first, or they
+            // would wait for as long as the present one has tickets (4.9e6 atoms of four cathodes in one
+            // kernel, a wave at a boundary: 9.3 ms, 6.3 this way)
+            const uint64_t old = B & __ballot(seg != cur_seg);
+            if (old != 0) s0 = __builtin_amdgcn_readlane(seg, __ffsll((unsigned long long)old) - 1);
             ballistic_loop<O>(a, segs + s0, pid, p, seg == s0, T.drained || drained);
         } else if (__ballot(p.st == ST_BALLISTIC && seg != s0) == 0) {
             ballistic_loop<O>(a, segs + s0, pid, p, true, T.drained || drained);
@@ -996,8 +1002,9 @@ static int blocks_of(uint64_t total, int blocks, int threads, int n_simd)
 // at 0.5 Pa, 1e5 atoms (1.5 tickets per lane of one wave per SIMD) 0.372 / 0.288, 0.300, 0.324; 1e6 (15)
 // 0.80 / 0.68, 0.62, 0.64; 5e6 (76) 1.96 / 2.40, 1.92, 1.74; 1e7 3.29 / 4.55, 3.56, 3.15; four cathodes, 7e6
 // 2.38 / 2.97, 2.35, 2.31, 2.3e7 5.95 / 9.2, 7.1, 6.6.  Chambers of 0.1 to 2 Pa: 3e5 atoms 2.96 / 2.32, 2.23,
-// 2.24; 1e6 3.59 / 4.03, 3.73, 3.47; 2e6 4.80 / 6.32, 5.40, 5.08.  FP64 (three waves at most), four
-// cathodes: 2e5 1.19 / 0.96, 0.88; 5e5 2.21 / 1.36, 1.46; 4e6 6.77 / 7.08, 5.30.
+// 2.24; 1e6 3.59 / 4.03, 3.73, 3.47; 2e6 4.80 / 6.32, 5.40, 5.08.  FP64 (three waves at most): four
+// cathodes, 2e5 1.21 / 0.96, 0.88; 5e5 1.78 / 1.36, 1.46; 3e6 4.52 / -, 4.32; single target, 1e6 2.28 / 1.93,
+// 2.09; 2e6 3.49 / -, 3.42; 3e6 4.40 / -, 4.81.
 uint64_t whole_limit(const Plan* P, const Shape& sh)
 {
     const uint64_t lanes = 4 * (uint64_t)P->n_cu * 64;
@@ -1008,7 +1015,7 @@ uint64_t whole_limit(const Plan* P, const Shape& sh)
         lo = std::min(lo, s.pressure);
         hi = std::max(hi, s.pressure);
     }
-    return (hi > 2.0 * lo ? 16 : 80) * lanes - 1;
+    return (hi > 2.0 * lo ? 16 : P->params.precision == 64 ? 32 : 80) * lanes - 1;
 }
 
 static int whole_waves(const Plan* P, uint64_t total, const Shape& sh, bool fp64)

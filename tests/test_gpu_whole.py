@@ -98,3 +98,18 @@ def test_the_largest_tally_and_counters_in_lds(arrivals):
         if outs[0].get(key) is not None:
             assert torch.equal(outs[0][key], outs[1][key]), key
     assert outs[0]["counters"].sum(0)[0].item() == 6400
+
+
+def test_fp64_segments_meet_in_a_wave():
+    # shares of many tickets, each segment's boundary inside one: the records of segments run alone
+    say("FP64, boundaries of segments inside the waves' shares")
+    counts = [150001, 7, 60013, 120002]
+    cfg = si.quaternary(0.5, counts=counts)
+    both = spx.records_to_numpy(spx.Plan([cfg], si.Params(), precision=64).run(seed=6, records=True)["records"])
+    more = si.quaternary(0.5, counts=[4 * c for c in counts])
+    far = spx.records_to_numpy(spx.Plan([more, si.single_ni(0.1, 14 * LANES)], si.Params(),
+                                        precision=64).run(seed=6, records=True)["records"])
+    first, first4 = 0, 0
+    for c in counts:
+        assert np.array_equal(both[first:first + c], far[first4:first4 + c])
+        first, first4 = first + c, first4 + 4 * c
