@@ -23,6 +23,9 @@ namespace spx {
 
 constexpr int KMAX = 16;
 constexpr int SQDIST_WAVE_ROWS = 4096;
+// Blocks of 256 threads that a launch may have: the threads of a grid have to fit 32 bits (a larger grid is
+// not refused but cut off, and the rest of the work not done).
+constexpr int64_t GRID_MAX = ((1ll << 32) - 1) / 256;
 
 __device__ __forceinline__ float weight(const float* a, const float* bb, const float* P, const float* M,
                                         const float* rho, const float* fref, int b, int k, int K)
@@ -467,53 +470,55 @@ static int bw_blocks(int B, int J)
 }
 static bool bw_fits(int J, int K) { return K <= BW_KMAX && J <= 4 * 64 * BW_JM; }
 
-// Area average: a wave per (profile, area), its lanes over the bins the square meets (about 100 of a 200 x
-// 200 wafer grid), the lanes' sums added in a tree.  Bound by the latency of one square's bins: with
-// one thread per square, 24 profiles x 342 areas took 22 us, one serial chain of loads each.
-__global__ void __launch_bounds__(256) k_area_gather(const double* __restrict__ prof, int n_prof, int nu, int nv,
+// Area average: G lanes per square (profile, area) over the bins it meets, row by row, the lanes' sums added in a
+// tree.  Few squares of many bins are bound by the latency of one square's bins, many small ones by the
+// instructions spent per square, which G lanes all spend: G is 1, 8 or 64 by the bins of a square (area_lanes).
+template <int G>
+__global__ void __launch_bounds__(256) k_area_gather(const double* __restrict__ prof, int64_t n, int nu, int nv,
                                                      double half_u, double half_v, const double* __restrict__ cen,
                                                      int n_areas, double hw, double* __restrict__ out)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t idx = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (idx >= (int64_t)n_prof * n_areas) return;
-    const int p = (int)(idx / n_areas), ai = (int)(idx - (int64_t)p * n_areas);
+    const int g = threadIdx.x & (G - 1);
     const double du = 2.0 * half_u / nu, dv = 2.0 * half_v / nv;
-    const double cu = cen[2 * ai], cv = cen[2 * ai + 1];
-    int iu0 = (int)floor((cu - hw + half_u) / du), iu1 = (int)floor((cu + hw + half_u) / du);
-    int iv0 = (int)floor((cv - hw + half_v) / dv), iv1 = (int)floor((cv + hw + half_v) / dv);
-    iu0 = iu0 < 0 ? 0 : iu0;
-    iv0 = iv0 < 0 ? 0 : iv0;
-    iu1 = iu1 > nu - 1 ? nu - 1 : iu1;
-    iv1 = iv1 > nv - 1 ? nv - 1 : iv1;
-    const double* pr = prof + (size_t)p * nu * nv;
-    double sw = 0.0, s = 0.0;
-    if (iu0 <= iu1) {
-        const int w = iu1 - iu0 + 1, dr = 64 / w, dc = 64 - dr * w;
-        int iv = iv0 + lane / w, iu = iu0 + lane % w;
-        while (iv <= iv1) {
-            const double v0 = -half_v + iv * dv, u0 = -half_u + iu * du;
-            const double ov = fmin(v0 + dv, cv + hw) - fmax(v0, cv - hw);
-            const double ou = fmin(u0 + du, cu + hw) - fmax(u0, cu - hw);
-            if (ov > 0.0 && ou > 0.0) {
-                const double wt = ou * ov;
-                sw += wt;
-                s += wt * pr[(size_t)iv * nu + iu];
-            }
-            iv += dr;
-            iu += dc;
-            if (iu > iu1) {
-                iu -= w;
-                ++iv;
+    for (int64_t idx = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G; idx < n; idx += (int64_t)gridDim.x * (256 / G)) {
+        const int64_t p = idx / n_areas;
+        const int ai = (int)(idx - p * n_areas);
+        const double cu = cen[2 * ai], cv = cen[2 * ai + 1];
+        int iu0 = (int)floor((cu - hw + half_u) / du), iu1 = (int)floor((cu + hw + half_u) / du);
+        int iv0 = (int)floor((cv - hw + half_v) / dv), iv1 = (int)floor((cv + hw + half_v) / dv);
+        iu0 = iu0 < 0 ? 0 : iu0;
+        iv0 = iv0 < 0 ? 0 : iv0;
+        iu1 = iu1 > nu - 1 ? nu - 1 : iu1;
+        iv1 = iv1 > nv - 1 ? nv - 1 : iv1;
+        const double* pr = prof + (size_t)p * nu * nv;
+        double sw = 0.0, s = 0.0;
+        if (iu0 <= iu1) {
+            const int w = iu1 - iu0 + 1, dr = G / w, dc = G - dr * w;
+            int iv = iv0 + g / w, iu = iu0 + g % w;
+            while (iv <= iv1) {
+                const double v0 = -half_v + iv * dv, u0 = -half_u + iu * du;
+                const double ov = fmin(v0 + dv, cv + hw) - fmax(v0, cv - hw);
+                const double ou = fmin(u0 + du, cu + hw) - fmax(u0, cu - hw);
+                if (ov > 0.0 && ou > 0.0) {
+                    const double wt = ou * ov;
+                    sw += wt;
+                    s += wt * pr[(size_t)iv * nu + iu];
+                }
+                iv += dr;
+                iu += dc;
+                if (iu > iu1) {
+                    iu -= w;
+                    ++iv;
+                }
             }
         }
-    }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        sw += __shfl_xor(sw, o);
-        s += __shfl_xor(s, o);
+        for (int o = G / 2; o > 0; o >>= 1) {
+            sw += __shfl_xor(sw, o);
+            s += __shfl_xor(s, o);
+        }
+        if (g == 0) out[idx] = sw > 0.0 ? s / sw : 0.0;
     }
-    if (lane == 0) out[idx] = sw > 0.0 ? s / sw : 0.0;
 }
 
 }  // namespace spx
@@ -638,6 +643,16 @@ extern "C" int spx_comp_sqdist(const float* d_c, const float* d_ct, int32_t B_t,
     return SPX_OK;
 }
 
+// Lanes of a square, by the bins it meets at most.  At 1, 8, 64 lanes [us]: 4e6 squares of 2 bins 50, 218, 1840;
+// 6.8e5 of 11 37, 49, 319; 8208 of 30 11.2, 8.8, 8.5; 6.8e5 of 100 908, 174, 376; 8208 of 100 26.2, 8.7, 8.8; 6.8e5
+// of 360 (bound 400) -, 443, 528, 8208 of them -, 21, 11; 8208 of 14641 4298, 733, 160.
+static int area_lanes(int nu, int nv, double half_u, double half_v, double half_width)
+{
+    const double bins = std::min<double>(nu, half_width / half_u * nu + 2.0) *
+                        std::min<double>(nv, half_width / half_v * nv + 2.0);
+    return bins <= 20.0 ? 1 : bins <= 256.0 ? 8 : 64;
+}
+
 extern "C" int spx_area_gather(const double* d_profiles, int32_t n_prof, int32_t nu, int32_t nv, double half_u,
                                double half_v, const double* d_centres, int32_t n_areas, double half_width,
                                double* d_out, void* stream)
@@ -648,8 +663,11 @@ extern "C" int spx_area_gather(const double* d_profiles, int32_t n_prof, int32_t
         return SPX_EINVAL;
     }
     const int64_t n = (int64_t)n_prof * n_areas;
-    hipLaunchKernelGGL(k_area_gather, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, (hipStream_t)stream,
-                       d_profiles, n_prof, nu, nv, half_u, half_v, d_centres, n_areas, half_width, d_out);
+    const int G = area_lanes(nu, nv, half_u, half_v, half_width);
+    const auto kern = G == 1 ? k_area_gather<1> : G == 8 ? k_area_gather<8> : k_area_gather<64>;
+    const int64_t blocks = std::min<int64_t>((n + 256 / G - 1) / (256 / G), GRID_MAX);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, d_profiles, n, nu, nv, half_u,
+                       half_v, d_centres, n_areas, half_width, d_out);
     SPX_HIP(hipGetLastError());
     return SPX_OK;
 }
