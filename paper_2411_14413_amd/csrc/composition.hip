@@ -23,9 +23,6 @@ namespace spx {
 
 constexpr int KMAX = 16;
 constexpr int SQDIST_WAVE_ROWS = 4096;
-// Blocks of 256 threads that a launch may have: the threads of a grid have to fit 32 bits (a larger grid is
-// not refused but cut off, and the rest of the work not done).
-constexpr int64_t GRID_MAX = ((1ll << 32) - 1) / 256;
 
 __device__ __forceinline__ float weight(const float* a, const float* bb, const float* P, const float* M,
                                         const float* rho, const float* fref, int b, int k, int K)
@@ -547,9 +544,12 @@ extern "C" int spx_comp_forward(const float* d_f, const float* d_a, const float*
                                   k_comp_forward<3, false>, k_comp_forward<4, false>, k_comp_forward<5, false>,
                                   k_comp_forward<6, false>, k_comp_forward<7, false>, k_comp_forward<8, false>};
     const Kernel kern = vec ? k_comp_forward<4, true> : by_k[K <= 8 ? K : 0];
-    hipLaunchKernelGGL(kern, dim3((unsigned)((B + rows - 1) / rows)), dim3(256), 0, (hipStream_t)stream, d_f, d_a, d_b,
-                       d_P, d_M, d_rho, d_fref, d_c, B, J, K, rows);
-    SPX_HIP(hipGetLastError());
+    for (int64_t b0 = 0; b0 < B; b0 += GRID_MAX * rows) {
+        const int n = (int)std::min<int64_t>(B - b0, GRID_MAX * rows);
+        hipLaunchKernelGGL(kern, dim3((unsigned)((n + rows - 1) / rows)), dim3(256), 0, (hipStream_t)stream, d_f, d_a, d_b,
+                           d_P + b0 * K, d_M, d_rho, d_fref, d_c + b0 * J * K, n, J, K, rows);
+        SPX_HIP(hipGetLastError());
+    }
     return SPX_OK;
 }
 
@@ -615,8 +615,11 @@ extern "C" int spx_comp_backward(const float* d_f, const float* d_a, const float
                            d_gf, d_ga, d_gb, d_gP, d_gM,  d_grho, d_gfref};
     SPX_TRY(check_backward(ptrs, 15, B, J, K));
     hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_comp_bw_w<256>, dim3(B), dim3(256), 0, st, d_f, d_a, d_b, d_P, d_M, d_rho, d_fref, d_gc,
-                       d_gP, B, J, K);
+    for (int64_t b0 = 0; b0 < B; b0 += GRID_MAX) {
+        const int n = (int)std::min<int64_t>(B - b0, GRID_MAX);
+        hipLaunchKernelGGL(k_comp_bw_w<256>, dim3((unsigned)n), dim3(256), 0, st, d_f, d_a, d_b, d_P + b0 * K, d_M, d_rho,
+                           d_fref, d_gc + b0 * J * K, d_gP + b0 * K, n, J, K);
+    }
     hipLaunchKernelGGL(k_comp_bw_f<256>, dim3(J), dim3(256), 0, st, d_f, d_a, d_b, d_P, d_M, d_rho, d_fref, d_gc,
                        d_gf, B, J, K);
     hipLaunchKernelGGL(k_comp_bw_params<256>, dim3(K), dim3(256), 0, st, d_a, d_b, d_P, d_M, d_rho, d_fref, d_gP,
@@ -637,8 +640,13 @@ extern "C" int spx_comp_sqdist(const float* d_c, const float* d_ct, int32_t B_t,
         hipLaunchKernelGGL(k_sqdist<4>, dim3((unsigned)B), dim3(256), 0, (hipStream_t)stream, d_c, d_ct, B_t, d_gloss,
                            d_loss, d_gc, B, J, K);
     else
-        hipLaunchKernelGGL(k_sqdist<1>, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, (hipStream_t)stream, d_c, d_ct,
-                           B_t, d_gloss, d_loss, d_gc, B, J, K);
+        for (int64_t b0 = 0; b0 < B; b0 += 4 * GRID_MAX) {
+            const int n = (int)std::min<int64_t>(B - b0, 4 * GRID_MAX);
+            const int64_t o = b0 * J * K;
+            hipLaunchKernelGGL(k_sqdist<1>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, (hipStream_t)stream, d_c + o,
+                               B_t == 1 ? d_ct : d_ct + o, B_t, d_gloss ? d_gloss + b0 : nullptr,
+                               d_loss ? d_loss + b0 : nullptr, d_gc ? d_gc + o : nullptr, n, J, K);
+        }
     SPX_HIP(hipGetLastError());
     return SPX_OK;
 }

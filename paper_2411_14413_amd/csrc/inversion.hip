@@ -15,6 +15,7 @@
 // so that they are the plain IEEE operations a reader would write down.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "spx_host.hpp"
@@ -406,9 +407,11 @@ extern "C" int spx_sweep_composition(const double* d_f, const double* d_a, const
         set_error("spx_sweep_composition: null pointer");
         return SPX_EINVAL;
     }
-    hipLaunchKernelGGL(k_sweep_composition<256>, dim3(T), dim3(256), 0, (hipStream_t)stream, d_f, d_a, d_b, d_P, d_M,
-                       d_rho, d_c, J, K);
-    SPX_HIP(hipGetLastError());
+    for (int64_t t0 = 0; t0 < T; t0 += GRID_MAX) {
+        hipLaunchKernelGGL(k_sweep_composition<256>, dim3((unsigned)std::min<int64_t>(T - t0, GRID_MAX)), dim3(256), 0,
+                           (hipStream_t)stream, d_f + t0 * K * J, d_a, d_b, d_P, d_M, d_rho, d_c + t0 * J * K, J, K);
+        SPX_HIP(hipGetLastError());
+    }
     return SPX_OK;
 }
 
@@ -421,8 +424,11 @@ extern "C" int spx_hull_area(const float* d_c, int32_t B, int32_t J, float* d_ar
     int n = 1;
     while (n < J) n <<= 1;
     const size_t smem = sizeof(double) * 2 * (size_t)(n + J);       // at most 64 KB
-    hipLaunchKernelGGL(k_hull_area<256>, dim3(B), dim3(256), smem, (hipStream_t)stream, d_c, J, d_area);
-    SPX_HIP(hipGetLastError());
+    for (int64_t b0 = 0; b0 < B; b0 += GRID_MAX) {
+        hipLaunchKernelGGL(k_hull_area<256>, dim3((unsigned)std::min<int64_t>(B - b0, GRID_MAX)), dim3(256), smem,
+                           (hipStream_t)stream, d_c + 3 * b0 * J, J, d_area + b0);
+        SPX_HIP(hipGetLastError());
+    }
     return SPX_OK;
 }
 

@@ -113,6 +113,9 @@ struct Outputs {
     uint64_t* esum = nullptr;
 };
 
+// Blocks of 256 threads that a launch may have: the threads of a grid have to fit 32 bits (a larger grid is
+// not refused but cut off, and the rest of the work not done).
+constexpr int64_t GRID_MAX = ((1ll << 32) - 1) / 256;
 constexpr uint64_t ROUND_MAX = 1ull << 28;   // tickets per round: a 12.9 GB queue of thermalised atoms
 // FP64 rounds: 1.3 GB of queue; where that much is not free, half the round, down to the smallest
 constexpr uint64_t ROUND_MAX64 = 1ull << 24, ROUND_MIN64 = 1ull << 16;
