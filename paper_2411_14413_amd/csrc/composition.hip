@@ -31,17 +31,21 @@ __device__ __forceinline__ float weight(const float* a, const float* bb, const f
 }
 
 // Forward: a block takes `rows` consecutive power vectors, whose weights it makes once (in LDS), and its
-// threads run over the rows' (b, j), which are contiguous in c.  Bound by HBM (4 K B written per (b, j)):
+// threads run over `span` (a multiple of 256) of the rows' (b, j), which are contiguous in c.  Bound by HBM (4 K B written per (b, j)):
 // with the weights made anew for every (b, j), two divisions each, and K stores of 4 B, 32768 x 342 x 4
 // took 68.9 us.  VEC: K == 4 and c aligned to 16 B, one store per (b, j); otherwise the compositions of
 // 256 (b, j) go through LDS, so that stores are contiguous (32768 x 342 x 3: 55 us with K stores K apart).
 constexpr int FWD_ROWS = 64;        // rows a block at most
+// Blocks that rows of many areas are split into, the device's 2048 resident ones twice.  One block a row / 512 / 2048 / 4096
+// blocks [us]: 1 x 1e6 x 4 1586, 8.9, 8.9, 8.7; 300 x 40000 x 4 76, 43, 34, 32; 2000 x 40000 x 3 391, 387, 239, 250;
+// 64 x 40000 x 9 472, 67, 38, 36.
+constexpr int64_t FWD_BLOCKS = 4096;
 template <int KT, bool VEC>
 __global__ void __launch_bounds__(256) k_comp_forward(const float* __restrict__ f, const float* __restrict__ a,
                                                       const float* __restrict__ bb, const float* __restrict__ P,
                                                       const float* __restrict__ M, const float* __restrict__ rho,
                                                       const float* __restrict__ fref, float* __restrict__ c, int B,
-                                                      int J, int Kr, int rows)
+                                                      int J, int Kr, int rows, int64_t span)
 {
     constexpr int KM = KT > 0 ? KT : KMAX;      // KT: elements known when compiled (0: any number)
     const int K = KT > 0 ? KT : Kr;
@@ -52,9 +56,9 @@ __global__ void __launch_bounds__(256) k_comp_forward(const float* __restrict__ 
     __syncthreads();
     float* cb = c + (size_t)b0 * J * K;
     const int dr = 256 / J, dj = 256 - dr * J;
-    const size_t total = (size_t)n_rows * J;
-    int r = threadIdx.x / J, j = threadIdx.x - r * J;
-    for (size_t i0 = 0; i0 < total; i0 += 256) {
+    const int64_t first = blockIdx.y * span, total = (int64_t)n_rows * J, end = first + span < total ? first + span : total;
+    int r = (int)((first + threadIdx.x) / J), j = (int)(first + threadIdx.x - (int64_t)r * J);
+    for (int64_t i0 = first; i0 < end; i0 += 256) {
         if (VEC) {
             if (r < n_rows) {
                 const float* wr = w + r * 4;
@@ -86,7 +90,7 @@ __global__ void __launch_bounds__(256) k_comp_forward(const float* __restrict__ 
                     if (k < K) tl[threadIdx.x * K + k] = y[k] * inv;
             }
             __syncthreads();
-            const size_t left = total - i0;
+            const int64_t left = end - i0;
             const int n = (int)(left < 256 ? left : 256) * K;
             float* out = cb + i0 * K;
             if (((uintptr_t)out & 15) == 0) {
@@ -539,15 +543,17 @@ extern "C" int spx_comp_forward(const float* d_f, const float* d_a, const float*
     if ((int64_t)rows * J < 256) rows = std::min(FWD_ROWS, 255 / J + 1);
     const bool vec = K == 4 && ((uintptr_t)d_c & 15) == 0;
     using Kernel = void (*)(const float*, const float*, const float*, const float*, const float*, const float*,
-                            const float*, float*, int, int, int, int);
+                            const float*, float*, int, int, int, int, int64_t);
     static const Kernel by_k[] = {k_comp_forward<0, false>, k_comp_forward<1, false>, k_comp_forward<2, false>,
                                   k_comp_forward<3, false>, k_comp_forward<4, false>, k_comp_forward<5, false>,
                                   k_comp_forward<6, false>, k_comp_forward<7, false>, k_comp_forward<8, false>};
     const Kernel kern = vec ? k_comp_forward<4, true> : by_k[K <= 8 ? K : 0];
     for (int64_t b0 = 0; b0 < B; b0 += GRID_MAX * rows) {
         const int n = (int)std::min<int64_t>(B - b0, GRID_MAX * rows);
-        hipLaunchKernelGGL(kern, dim3((unsigned)((n + rows - 1) / rows)), dim3(256), 0, (hipStream_t)stream, d_f, d_a, d_b,
-                           d_P + b0 * K, d_M, d_rho, d_fref, d_c + b0 * J * K, n, J, K, rows);
+        const int64_t groups = (n + rows - 1) / rows, tiles = ((int64_t)rows * J + 255) / 256;
+        const int64_t parts = std::min(tiles, (FWD_BLOCKS + groups - 1) / groups), span = (tiles + parts - 1) / parts * 256;
+        hipLaunchKernelGGL(kern, dim3((unsigned)groups, (unsigned)parts), dim3(256), 0, (hipStream_t)stream, d_f, d_a,
+                           d_b, d_P + b0 * K, d_M, d_rho, d_fref, d_c + b0 * J * K, n, J, K, rows, span);
         SPX_HIP(hipGetLastError());
     }
     return SPX_OK;
