@@ -22,7 +22,12 @@
 namespace spx {
 
 constexpr int KMAX = 16;
-constexpr int SQDIST_WAVE_ROWS = 4096;
+// Rows of the squared distance from which each is a wave's: the device holds 8192 waves, and fewer rows leave
+// it empty towards the end of long ones.  A wave / a block per row, loss and loss with gradient [us]: 4096
+// rows of 1368 10.1 + 12.1 / 8.2 + 10.2, of 160000 1188 + 1802 / 729 + 1165; 6144 rows of 1368 11.0 + 13.4 /
+// 11.5 + 13.8, of 160000 1294 + 2024 / 1089 + 1742; 8192 rows of 1368 10.9 + 16.3 / 14.9 + 17.2, of 160000
+// 1401 + 2311 / 1448 + 2315.
+constexpr int SQDIST_WAVE_ROWS = 8192;
 
 __device__ __forceinline__ float weight(const float* a, const float* bb, const float* P, const float* M,
                                         const float* rho, const float* fref, int b, int k, int K)
@@ -641,7 +646,6 @@ extern "C" int spx_comp_sqdist(const float* d_c, const float* d_ct, int32_t B_t,
         set_error("spx_comp_sqdist: invalid arguments");
         return SPX_EINVAL;
     }
-    // a block per row until every SIMD has a row to itself in several waves
     if (B < SQDIST_WAVE_ROWS)
         hipLaunchKernelGGL(k_sqdist<4>, dim3((unsigned)B), dim3(256), 0, (hipStream_t)stream, d_c, d_ct, B_t, d_gloss,
                            d_loss, d_gc, B, J, K);
