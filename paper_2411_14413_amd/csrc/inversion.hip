@@ -23,15 +23,19 @@
 namespace spx {
 
 constexpr int SWEEP_KMAX = 16;
+constexpr int SWEEP_WAVE_AREAS = 1536;
 constexpr int HULL_JMAX = 2048;
 constexpr int FIT_TMAX = 256;
 constexpr double SQRT3 = 1.7320508075688772;   // sqrt(3) rounded to double
 
 // ---- compositions of a sweep -----------------------------------------------------------
-// One workgroup per sweep point t, a wave per element for the means.  fref[k] = (sum_j f[t,k,j]) / J in the
-// order of 256 strided partial sums and a tree over them (lane l holds partials l, l + 64, l + 128
-// and l + 192), so results are repeatable and take one barrier.
-template <int THREADS>
+// One workgroup per sweep point t.  fref[k] = (sum_j f[t,k,j]) / J in the order of 256 strided partial sums and a
+// tree over them, so results are repeatable: a wave per element (lane l holds partials l, l + 64, l + 128
+// and l + 192) and one barrier, or LONG the whole workgroup for one element after the other, a partial a
+// thread, the same bits.  Bound by the workgroup's chain of loads.  A wave / the workgroup [us]: 8 points of 342
+// areas and 3 elements 11.6 / 10.8, of 16 14.6 / 21.3; 1500 areas 12.7 / 12.0, 38 / 43; 2048 14.9 / 12.7, 50 / 45;
+// 40000 224 / 163, 1434 / 960.
+template <int THREADS, bool LONG>
 __global__ __launch_bounds__(THREADS) void k_sweep_composition(const double* __restrict__ f,
                                                                const double* __restrict__ a,
                                                                const double* __restrict__ bb,
@@ -41,20 +45,34 @@ __global__ __launch_bounds__(THREADS) void k_sweep_composition(const double* __r
                                                                float* __restrict__ c, int J, int K)
 {
     __shared__ double w[SWEEP_KMAX];
+    __shared__ double part[LONG ? 2 : 1][LONG ? THREADS : 1];   // of successive elements in turn
     const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const double* ft = f + (size_t)t * K * J;
-    for (int k = tid >> 6; k < K; k += THREADS / 64) {
-        double s[4] = {0.0, 0.0, 0.0, 0.0};
-        for (int j0 = 0; j0 < J; j0 += 256) {
+    for (int k = LONG ? 0 : tid >> 6; k < K; k += LONG ? 1 : THREADS / 64) {
+        double v;
+        if constexpr (LONG) {
+            static_assert(THREADS == 256, "a partial sum a thread");
+            double s = 0.0;
+#pragma unroll 8
+            for (int j = tid; j < J; j += 256) s += ft[(size_t)k * J + j];
+            part[k & 1][tid] = s;
+            __syncthreads();
+            if (tid >= 64) continue;
+            const double* p = part[k & 1] + lane;
+            v = (p[0] + p[128]) + (p[64] + p[192]);
+        } else {
+            double s[4] = {0.0, 0.0, 0.0, 0.0};
+            for (int j0 = 0; j0 < J; j0 += 256) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int j = j0 + 64 * q + lane;
-                if (j < J) s[q] += ft[(size_t)k * J + j];
+                for (int q = 0; q < 4; ++q) {
+                    const int j = j0 + 64 * q + lane;
+                    if (j < J) s[q] += ft[(size_t)k * J + j];
+                }
             }
+            s[0] += s[2];
+            s[1] += s[3];
+            v = s[0] + s[1];
         }
-        s[0] += s[2];
-        s[1] += s[3];
-        double v = s[0] + s[1];
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
         if (lane == 0) {
@@ -408,8 +426,9 @@ extern "C" int spx_sweep_composition(const double* d_f, const double* d_a, const
         return SPX_EINVAL;
     }
     for (int64_t t0 = 0; t0 < T; t0 += GRID_MAX) {
-        hipLaunchKernelGGL(k_sweep_composition<256>, dim3((unsigned)std::min<int64_t>(T - t0, GRID_MAX)), dim3(256), 0,
-                           (hipStream_t)stream, d_f + t0 * K * J, d_a, d_b, d_P, d_M, d_rho, d_c + t0 * J * K, J, K);
+        const auto kern = J > SWEEP_WAVE_AREAS ? k_sweep_composition<256, true> : k_sweep_composition<256, false>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)std::min<int64_t>(T - t0, GRID_MAX)), dim3(256), 0, (hipStream_t)stream,
+                           d_f + t0 * K * J, d_a, d_b, d_P, d_M, d_rho, d_c + t0 * J * K, J, K);
         SPX_HIP(hipGetLastError());
     }
     return SPX_OK;
