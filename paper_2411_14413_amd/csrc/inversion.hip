@@ -149,8 +149,9 @@ __device__ __forceinline__ int hull_chain(double* x, double* y, int J, bool down
 }
 
 // One workgroup per library.  Points go to LDS in ternary-diagram coordinates.  Of many points those
-// that lie inside the polygon of the extreme points in 16 directions, by a margin far above rounding
-// (0.1 at.%^2 of every edge's cross product, where that of the FP32 test is 5e-3), cannot be on the hull
+// that lie inside the polygon of the extreme points in 16 directions, by a margin above the rounding of the
+// FP32 test (0.1 at.%^2 of every edge's cross product; where no coordinate exceeds 128 the factors are at most 256,
+// each within 3e-5, and the error is below 0.04: beyond that no point is left out), cannot be on the hull
 // and are left out: a point to the left of every edge of a closed polygon lies in the hull of its vertices,
 // whatever the vertices are, and a degenerate set has no such point.  The others, padded to a power
 // of two with +inf, are sorted by (x, y) with a bitonic network (a barrier only where pairs cross the
@@ -159,6 +160,7 @@ __device__ __forceinline__ int hull_chain(double* x, double* y, int J, bool down
 // about two turns a point one after the other, 0.23 us a point: with one lane walking both over index
 // stacks, a library of 342 areas took 203 us, with the two waves over all points 96 us.
 constexpr int HULL_DIRS = 16, HULL_FILTER_MIN = 64;
+constexpr float HULL_FILTER_REACH = 128.f;
 __constant__ const float HULL_COS[HULL_DIRS] = {1.f, 0.9238795f, 0.70710678f, 0.38268343f, 0.f, -0.38268343f, -0.70710678f,
                                                 -0.9238795f, -1.f, -0.9238795f, -0.70710678f, -0.38268343f, 0.f,
                                                 0.38268343f, 0.70710678f, 0.9238795f};
@@ -222,6 +224,8 @@ __global__ __launch_bounds__(THREADS) void k_hull_area(const float* __restrict__
                 vy[d0 + d] = (float)qy[at[d]];
             }
         __syncthreads();
+        bool near = true;
+        for (int d = 0; d < HULL_DIRS; ++d) near = near && fabsf(vx[d]) <= HULL_FILTER_REACH && fabsf(vy[d]) <= HULL_FILTER_REACH;
         for (int j0 = 0; j0 < J; j0 += THREADS) {
             const int j = j0 + tid;
             bool keep = j < J;
@@ -236,10 +240,10 @@ __global__ __launch_bounds__(THREADS) void k_hull_area(const float* __restrict__
                     const int p = (d + HULL_DIRS - 1) & (HULL_DIRS - 1);
                     const float cr = (vx[d] - vx[p]) * (fy - vy[p]) - (vy[d] - vy[p]) * (fx - vx[p]);
                     const bool edge = vi[d] != vi[p];
-                    inside = inside && (!edge || (cr > 0.1f && cr < 1e6f));
+                    inside = inside && (!edge || cr > 0.1f);
                     edges += edge ? 1 : 0;
                 }
-                keep = !(inside && edges >= 3);
+                keep = !(inside && near && edges >= 3);
             }
             const uint64_t m = __ballot(keep);
             int base = 0;

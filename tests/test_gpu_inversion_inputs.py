@@ -1,11 +1,10 @@
-"""What a measured library may look like to the tilt inversion: a tensor that takes part in a gradient, and
-compositions far from the range of at.% (other units, values not normalised).  The covered areas are
-the oracle's bit for bit (float64 value rounded to float), whatever the points' place and size."""
+"""Libraries that the inversion's kernels have to take as they are: compositions far from the range of at.%
+(other units, values not normalised), whose covered areas are the oracle's bit for bit (float64 value
+rounded to float), and areas that no atom reached, which have no composition."""
 import numpy as np
 import pytest
 
 import oracle
-import sputter_inputs as si
 from parity import say
 
 pytestmark = pytest.mark.gpu
@@ -17,24 +16,9 @@ if not torch.cuda.is_available():
 import paper_2411_14413_amd as spx  # noqa: E402
 
 
-def test_measured_library_in_a_gradient():
-    x = [11.0, 12.0, 13.0]
-    plan = spx.Plan([si.ternary(0.5, t, n_particles=1000, grid_n=40) for t in x], si.Params())
-    g = torch.Generator(device="cuda").manual_seed(1)
-    prof = torch.rand(plan.n_bins, dtype=torch.float64, device="cuda", generator=g) + 0.5
-    comp = si.ternary_composition_inputs()
-    meas = torch.rand(50, 3, device="cuda", generator=g)
-    cen = spx.area_centres(50)
-    ref = spx.invert_sweep(plan, {"profiles": prof}, x, comp, meas, centres=cen)
-    got = spx.invert_sweep(plan, {"profiles": prof}, x, comp, meas.clone().requires_grad_(True), centres=cen)
-    for k, v in ref.items():
-        assert not got[k].requires_grad, k
-        assert torch.equal(got[k], v) or (torch.isnan(got[k]).all() and torch.isnan(v).all()), k
-
-
 @pytest.mark.parametrize("J", [64, 342, 2048])
-@pytest.mark.parametrize("place, size", [(0.0, 1.0), (40.0, 10.0), (0.0, 300.0), (-200.0, 100.0), (1e5, 100.0), (3e4, 20.0), (0.0, 1e-3),
-                                         (0.0, 1e30)])
+@pytest.mark.parametrize("place, size", [(0.0, 1.0), (40.0, 10.0), (0.0, 300.0), (-200.0, 100.0), (1e5, 100.0), (9e5, 10.0), (988875.0, 7.5),
+                                         (0.0, 1e-3), (0.0, 1e30)])
 def test_covered_area_anywhere(J, place, size):
     say(f"{J} compositions around {place}, spread {size}")
     r = np.random.default_rng(J)
