@@ -29,7 +29,8 @@
  *   after the other.  Inside a stream capture spx_run / spx_run_ex enqueue their
  *   kernels directly on the capturing stream (they become nodes of the caller's graph;
  *   the plan's own graph is not used), the wait and the record are left out, and the
- *   capturing caller orders the runs of a plan itself: they share its queue.
+ *   capturing caller orders the runs of an FP32 plan itself: they share its queue.
+ *   Captured runs of an FP64 plan share nothing and need no order (see spx_run).
  *
  * Random numbers: Philox4x32-10, counter (particle, event, (config << 8) | cathode,
  * sub-block), key (seed low word, seed high word); a 32-bit word x gives
@@ -207,7 +208,8 @@ typedef struct spx_plan spx_plan;
  * more than 2^24 configurations.  Device memory: the tables, the segment constants and a queue
  * of thermalised atoms of 48 B (FP64 plans: 80 B) per ticket of a round.  The particles run in
  * equal rounds of at most 2^28 tickets, so at most ~12.9 GB; FP64 plans of at most 2^24 (1.3 GB),
- * where that is not free of half as many, down to 2^16.  SPX_ENOMEM if an allocation fails.
+ * where that is not free of half as many, down to 2^16, and where that is not free either they
+ * run without a queue (see spx_run).  SPX_ENOMEM if any other allocation fails.
  * *out is set only on success. */
 int spx_plan_create(const spx_config* h_cfgs, int32_t n_cfgs, const spx_params* h_params, spx_plan** out);
 
@@ -229,7 +231,9 @@ int spx_plan_layout(const spx_plan* plan, uint64_t* h_bin_off, uint64_t* h_first
  * precision 32 replays a HIP graph built on the first run and updated in place for new seeds
  * and buffers;
  * precision 64 enqueues the same two phases in FP64 (every position, energy and decision in
- * double) on `stream`, without a graph.  Asynchronous. */
+ * double) on `stream`, without a graph; inside a stream capture, and where the plan has no queue,
+ * a kernel without one takes a thread per atom through its whole history instead (the same outputs,
+ * four to seven times slower).  Asynchronous. */
 int spx_run(spx_plan* plan, uint64_t seed, uint64_t* d_counts, uint64_t* d_counters,
             double* d_profiles, spx_record* d_records, void* stream);
 

@@ -618,13 +618,15 @@ static int create(const spx_config* cfgs, int n_cfgs, const spx_params* prm, Pla
         P->queue_cap = (r ? (P->n_tickets + r - 1) / r : 0) + waves * QUEUE_CHUNK;
         if (dalloc(&P->d_queue, P->queue_cap * rec) == SPX_OK) break;
         (void)hipGetLastError();
-        if (prm->precision == 64 && P->round_max > ROUND_MIN64) {
-            P->round_max /= 2;
-            continue;
+        if (prm->precision == 32) {
+            set_error("hipMalloc of the thermalisation queue (" + std::to_string(P->queue_cap * rec) + " bytes) failed");
+            release(P);
+            return SPX_ENOMEM;
         }
-        set_error("hipMalloc of the thermalisation queue (" + std::to_string(P->queue_cap * rec) + " bytes) failed");
-        release(P);
-        return SPX_ENOMEM;
+        P->d_queue = nullptr;
+        P->queue_cap = 0;
+        if (P->round_max <= ROUND_MIN64) break;     // FP64 runs do without a queue then
+        P->round_max /= 2;
     }
     std::vector<uint64_t> bo(P->h_bin_off);
     bo.push_back(P->n_bins_total);
@@ -767,6 +769,8 @@ static int run(Plan* P, uint64_t seed, const Outputs& o, hipStream_t st)
     q.qstate = P->d_qstate;
     q.round_max = P->round_max;
     if (P->params.precision == 64) {
+        // a captured run has no queue to share: its replays may overlap with the plan's other runs
+        if (capturing) q.queue = nullptr;
         StreamSink ss(st, nullptr);
         SPX_TRY(build_transport<double>(P, seed, o, P->d_tfirst, P->n_tickets, P->shape64, q, ss));
     } else if (capturing) {

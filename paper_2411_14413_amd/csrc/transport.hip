@@ -1,7 +1,8 @@
 // transport.hip -- the transport kernels of both precisions and their tallies.
 //
 // Every (configuration, cathode) segment of a plan runs in rounds of at most ROUND_MAX (FP64:
-// ROUND_MAX64) tickets, a long round as two persistent launches, another as one (whole_kernel).
+// ROUND_MAX64) tickets, a long round as two persistent launches, another as one (whole_kernel).  (FP64
+// runs in a caller's graph: k_plain64.)
 // The ballistic phase takes every ticket of the round from its launch through its flights and
 // collisions; an atom that ends on a surface (or escapes) is finished there, an atom that
 // thermalises is handed over to a queue in HBM (48 B, in FP64 80 B, with the two numbers of its
@@ -830,6 +831,59 @@ k_whole64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
     whole_kernel<ARR, OBJ, false>(a, segs);
 }
 
+// FP64 runs that share nothing with other runs of their plan: a thread takes a ticket through its whole history,
+// every diffusive step tested (a ball of no radius), with no queue and no counters in memory.  For runs
+// recorded into a caller's graph, whose replays may overlap with any other work of the plan, and for plans
+// whose queue does not fit the memory.  The operations of a history, and so the outputs, are those of the two
+// phases, bit for bit.  9e5 atoms at 0.5 / 0 / 2 Pa take 70 ms (the two phases 10.4), 2.3e6 of four cathodes 23.4
+// (3.9), 1e5 of one 2.8 (0.77).
+template <bool ARR, bool OBJ>
+__global__ void __launch_bounds__(256) k_plain64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
+{
+    extern __shared__ unsigned long long lds[];
+    using O = std::conditional_t<OBJ, OwnObjects, NoObjects>;
+    BlockTally bt;
+    lds_setup(a, bt, lds);
+    LaneAcc<false> acc;
+    for (uint64_t g = (uint64_t)blockIdx.x * 256 + threadIdx.x; g < a.total; g += (uint64_t)gridDim.x * 256) {
+        int lo = 0, hi = a.n_seg;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (a.tfirst[mid] <= g) lo = mid; else hi = mid;
+        }
+        const int seg = (int)a.torder[lo];
+        const uint32_t pid = (uint32_t)(g - a.tfirst[lo]);
+        const SegDev<double>& s = segs[seg];
+        if (seg != acc.seg) {
+            flush_acc(a, bt, acc);
+            acc.seg = seg;
+        }
+        Particle<double> p;
+        Walk<double> wk;
+        Term t{HIT_NONE, -1, 0.f};
+        start(s, a.k0, a.k1, pid, p);
+        while (t.state == HIT_NONE && p.st == ST_BALLISTIC) t = step_mode<O>(s, a.tab, a.k0, a.k1, pid, a.cap, p);
+        const bool walks = t.state == HIT_NONE;
+        while (t.state == HIT_NONE) {
+            if (p.e >= a.cap) {
+                t.state = HIT_ESCAPED;
+                break;
+            }
+            p.r2 = -1.0;
+            diffusive_single(s.lam_l2, s.cfgcat, a.k0, a.k1, pid, p, wk);
+            t = diffusive_resolve(s, s, p, wk, O());
+            p.ndiff += t.state == HIT_NONE ? 1u : 0u;
+        }
+        acc.c[C_LAUNCHED] += 1u;
+        acc.c[C_THERMALIZED] += walks ? 1u : 0u;
+        acc.c[C_DIFFUSIVE] += p.ndiff;
+        acc.c[C_TESTED] += p.ndiff + (walks && t.state != HIT_ESCAPED ? 1u : 0u);
+        terminate<ARR>(a, bt, s, pid, p, t, acc);
+    }
+    flush_acc(a, bt, acc);
+    lds_flush(a, bt);
+}
+
 // Ranges of words to clear: a run's outputs and a round's counters.
 struct Ranges {
     uint64_t* p[6] = {};
@@ -958,6 +1012,7 @@ template <> struct Path<double> {
     static const void* diffusive(const Plan* P, bool arr) { return SPX_INSTANCE(k_diffusive64, arr, P->has_objects); }
     // (the queue of an FP64 plan holds its rounds)
     static const void* whole(const Plan* P, bool arr, bool) { return SPX_INSTANCE(k_whole64, arr, P->has_objects); }
+    static const void* plain(const Plan* P, bool arr) { return SPX_INSTANCE(k_plain64, arr, P->has_objects); }
     static constexpr int IDLE = WALK_IDLE64;
     static constexpr bool LIMITED = false;
 };
@@ -1026,6 +1081,40 @@ static int whole_waves(const Plan* P, uint64_t total, const Shape& sh, bool fp64
     return per_lane < 4 ? 2 : per_lane < 20 ? 3 : 4;
 }
 
+// The outputs of a run that its kernels add to.
+static Ranges output_ranges(const Plan* P, const Outputs& o)
+{
+    Ranges c;
+    c.add(o.counts, P->n_bins_total);
+    c.add(o.counters, (uint64_t)P->n_seg * N_COUNTERS);
+    if (o.arr_E) {
+        c.add(o.arr_E, (uint64_t)P->n_seg * SPX_ARRIVAL_E_BINS);
+        c.add(o.arr_A, (uint64_t)P->n_seg * SPX_ARRIVAL_A_BINS);
+        c.add(o.esum, P->n_bins_total);
+    }
+    return c;
+}
+
+// The launches of an FP64 run without a queue: 16 blocks a CU at most, whose threads take one ticket after another
+// (a block clears and flushes the LDS tally once).
+static int put_plain64(Plan* P, TransportArgs<double>& a, const SegDev<double>* segs, uint64_t total, size_t smem,
+                       const Outputs& o, LaunchSink& sink)
+{
+    SPX_TRY(put_clear(output_ranges(P, o), sink));
+    if (total > 0) {
+        a.total = total;
+        KLaunch k;
+        k.func = Path<double>::plain(P, a.arr_E != nullptr);
+        k.grid = dim3((unsigned)std::min<uint64_t>((total + 255) / 256, 16 * (uint64_t)P->n_cu));
+        k.block = dim3(256);
+        k.smem = (uint32_t)smem;
+        k.arg(a);
+        k.arg(segs);
+        SPX_TRY(sink.put(k));
+    }
+    return o.profiles ? put_normalize(P, o.counts, o.profiles, sink) : SPX_OK;
+}
+
 template <typename R>
 int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tfirst, uint64_t total,
                     const Shape& sh, const QueueMem& q, LaunchSink& sink)
@@ -1077,6 +1166,10 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
     a.lds_counters = lc ? 1 : 0;
     a.lds_tally = lt ? 1 : 0;
     a.lds_arrivals = la ? 1 : 0;
+    const SegDev<R>* segs = K::segs(P);
+    if constexpr (std::is_same<R, double>::value) {
+        if (!q.queue) return put_plain64(P, a, segs, total, smem, o, sink);
+    }
     const uint64_t n_rounds = rounds_of(total, q.round_max);
     const uint64_t per_round = n_rounds ? (total + n_rounds - 1) / n_rounds : 0;
     const int blocks = blocks_of(per_round, sh.blocks, sh.threads, a.n_simd);
@@ -1095,15 +1188,7 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
         set_error("internal: round larger than the thermalisation queue");
         return SPX_ESTATE;
     }
-    const SegDev<R>* segs = K::segs(P);
-    Ranges clear;
-    clear.add(o.counts, P->n_bins_total);
-    clear.add(o.counters, (uint64_t)P->n_seg * N_COUNTERS);
-    if (o.arr_E) {
-        clear.add(o.arr_E, (uint64_t)P->n_seg * SPX_ARRIVAL_E_BINS);
-        clear.add(o.arr_A, (uint64_t)P->n_seg * SPX_ARRIVAL_A_BINS);
-        clear.add(o.esum, P->n_bins_total);
-    }
+    Ranges clear = output_ranges(P, o);
     // the first round's counters (the times of a run in one kernel outlast autotuning)
     clear.add(q.qstate, ww > 0 ? QSTATE_WORDS : QS_TIMES);
     SPX_TRY(put_clear(clear, sink));
