@@ -781,6 +781,7 @@ static int run(Plan* P, uint64_t seed, const Outputs& o, hipStream_t st)
         StreamSink ss(st, nullptr);
         SPX_TRY(build_transport<float>(P, seed, o, P->d_tfirst, P->n_tickets, plan_shape(P), q, ss));
     } else {
+        q.times = P->d_qstate + QS_TIMES;
         ListSink ls;
         SPX_TRY(build_transport<float>(P, seed, o, P->d_tfirst, P->n_tickets, plan_shape(P), q, ls));
         bool same = P->graph_exec && ls.L.size() == P->graph_launches.size();

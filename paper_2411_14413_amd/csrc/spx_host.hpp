@@ -76,6 +76,7 @@ template <typename R> struct TransportArgs {
     ThermRec<R>* queue;         // thermalised atoms of the round (capacity >= tickets of a round)
     uint64_t* qstate;           // [QS_TICKETS] ballistic ticket counter, [QS_QUEUE] queue length,
                                 // [QS_DIFFUSIVE] diffusive ticket counter
+    uint64_t* times;            // whole kernel: ticks that sampled waves spent in either phase, start, end (nullable)
     unsigned long long* counts;
     unsigned long long* counters;
     spx_record* records;
@@ -125,8 +126,8 @@ constexpr uint64_t QUEUE_CHUNK = 64;         // queue slots a wave reserves per 
 static_assert(QUEUE_CHUNK == 64, "queue runs hold one slot per lane of a wave");
 // The round's three counters (ballistic tickets, queue length, diffusive tickets) sit 256 bytes
 // apart: every wave's claims and queue reservations are atomics on them, and on one cache line
-// the two kinds of atomics of the ballistic phase would queue behind each other.  QS_TIMES: ticks that
-// sampled waves of the whole kernel spent in either phase, its start and its end.
+// the two kinds of atomics of the ballistic phase would queue behind each other.  QS_TIMES: the times of
+// the plan's last run in one kernel.
 constexpr uint64_t QS_TICKETS = 0, QS_QUEUE = 32, QS_DIFFUSIVE = 64, QS_TIMES = 96, QSTATE_WORDS = 128;
 constexpr uint64_t QUEUE_SLACK_WAVES = 8192;  // waves that may leave slots unused (32 per CU, 256 CUs)
 constexpr size_t LDS_COUNTERS_MAX = 16384;   // bytes: up to 256 segments
@@ -217,6 +218,7 @@ struct QueueMem {
     void* queue = nullptr;       // ThermRec<R> of the plan's precision
     uint64_t cap = 0;            // slots
     uint64_t* qstate = nullptr;  // QSTATE_WORDS words: the round's counters
+    uint64_t* times = nullptr;   // qstate + QS_TIMES in runs that spx_phase_times answers for
     uint64_t round_max = ROUND_MAX;
 };
 

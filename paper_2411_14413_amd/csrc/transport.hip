@@ -786,7 +786,7 @@ __device__ __forceinline__ void whole_kernel(TransportArgs<R>& a, const SegDev<R
     T.tk = wave * a.chunk_ballistic < total ? wave * a.chunk_ballistic : total;
     T.tk_end = total - T.tk > a.chunk_ballistic ? T.tk + a.chunk_ballistic : total;
     uint64_t times[2] = {0, 0};
-    if (threadIdx.x == 0 && blockIdx.x == 0) a.qstate[QS_TIMES + 2] = wall_clock64();
+    if (a.times && threadIdx.x == 0 && blockIdx.x == 0) a.times[2] = wall_clock64();
     for (;;) {
         T.drained = T.tk == T.tk_end;
         const uint64_t t0 = wall_clock64();
@@ -809,12 +809,12 @@ __device__ __forceinline__ void whole_kernel(TransportArgs<R>& a, const SegDev<R
         T.tk = (uint32_t)e.q_end;
         if (T.tk == T.tk_end) break;
     }
-    if (threadIdx.x == 0 && blockIdx.x % 8 == 0) {
-        atomicAdd((unsigned long long*)&a.qstate[QS_TIMES], (unsigned long long)times[0]);
-        atomicAdd((unsigned long long*)&a.qstate[QS_TIMES + 1], (unsigned long long)times[1]);
+    if (a.times && threadIdx.x == 0 && blockIdx.x % 8 == 0) {
+        atomicAdd((unsigned long long*)&a.times[0], (unsigned long long)times[0]);
+        atomicAdd((unsigned long long*)&a.times[1], (unsigned long long)times[1]);
     }
     lds_flush(a, bt);
-    if (threadIdx.x == 0) atomicMax((unsigned long long*)&a.qstate[QS_TIMES + 3], (unsigned long long)wall_clock64());
+    if (a.times && threadIdx.x == 0) atomicMax((unsigned long long*)&a.times[3], (unsigned long long)wall_clock64());
 }
 
 // Four waves per SIMD (FP64: three) fit without spills in the steps.
@@ -1132,6 +1132,7 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
     a.torder = P->d_torder;
     a.queue = (ThermRec<R>*)q.queue;
     a.qstate = q.qstate;
+    a.times = q.times;
     a.counts = (unsigned long long*)o.counts;
     a.counters = (unsigned long long*)o.counters;
     a.records = o.records;
@@ -1189,8 +1190,8 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
         return SPX_ESTATE;
     }
     Ranges clear = output_ranges(P, o);
-    // the first round's counters (the times of a run in one kernel outlast autotuning)
-    clear.add(q.qstate, ww > 0 ? QSTATE_WORDS : QS_TIMES);
+    // the first round's counters
+    clear.add(q.qstate, ww > 0 && q.times ? QSTATE_WORDS : QS_TIMES);
     SPX_TRY(put_clear(clear, sink));
     for (uint64_t r = 0; r < n_rounds; ++r) {
         a.tbase = r * per_round;
