@@ -438,6 +438,9 @@ static int create(const spx_config* cfgs, int n_cfgs, const spx_params* prm, Pla
         P->h_bin_off.push_back(boff);
         P->h_first.push_back(first);
         P->has_objects = P->has_objects || !s.objs.empty();
+        P->n_objects += s.objs.size();
+        P->p_lo = boff == 0 ? s.pressure : std::min(P->p_lo, s.pressure);
+        P->p_hi = std::max(P->p_hi, s.pressure);
         boff += (uint64_t)s.nu * s.nv;
         first += s.N;
     }

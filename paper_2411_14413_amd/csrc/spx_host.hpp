@@ -230,6 +230,8 @@ struct spx_plan {
     std::vector<spx::SegHost> seg;
     int n_seg = 0;
     bool has_objects = false;               // a segment has absorbing objects
+    uint64_t n_objects = 0;                 // objects over all segments
+    double p_lo = 0.0, p_hi = 0.0;          // least and greatest pressure of a segment
     uint64_t n_bins_total = 0, n_particles_total = 0;
     std::vector<uint64_t> h_bin_off, h_first;
     std::vector<double> h_betamax;          // FP64 beta_max table copy (host)

@@ -1065,12 +1065,7 @@ uint64_t whole_limit(const Plan* P, const Shape& sh)
     const uint64_t lanes = 4 * (uint64_t)P->n_cu * 64;
     if (!sh.whole || (uint64_t)std::min(sh.blocks, sh.blocks_diff) * (uint64_t)sh.threads < lanes)
         return 0;                  // (a grid that the caller made smaller than that stays as it is)
-    double lo = P->seg[0].pressure, hi = lo;
-    for (const auto& s : P->seg) {
-        lo = std::min(lo, s.pressure);
-        hi = std::max(hi, s.pressure);
-    }
-    return (hi > 2.0 * lo ? 16 : P->params.precision == 64 ? 32 : 80) * lanes - 1;
+    return (P->p_hi > 2.0 * P->p_lo ? 16 : P->params.precision == 64 ? 32 : 80) * lanes - 1;
 }
 
 static int whole_waves(const Plan* P, uint64_t total, const Shape& sh, bool fp64)
@@ -1152,9 +1147,7 @@ int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tf
     // a pass of the surface tests takes about 180 instructions, and 70 more per absorbing object of
     // the segment (its test and its clearance): the idle rounds it is worth grow with it (four cathodes
     // in chimneys, seven objects a run: diffusive kernel 2.87 ms at 128 idle rounds, 2.66 at 400)
-    size_t n_obj = 0;
-    for (const auto& s : P->seg) n_obj += s.objs.size();
-    a.walk_idle = K::IDLE + (int32_t)(K::IDLE * 70 * n_obj / (180 * (size_t)P->n_seg));
+    a.walk_idle = K::IDLE + (int32_t)(K::IDLE * 70 * P->n_objects / (180 * (uint64_t)P->n_seg));
     a.n_bins = (uint32_t)P->n_bins_total;
     bool lc, lt, la;
     const size_t smem = transport_lds(P, o.arr_E != nullptr, &lc, &lt, &la);
