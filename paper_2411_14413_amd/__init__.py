@@ -228,8 +228,9 @@ class Plan:
                                    ctypes.byref(d)), "spx_get_launch")
         return dict(blocks=b.value, threads=t.value, refill_min=r.value, refill_ballistic=m.value, defer_min=d.value)
 
-    def set_launch(self, blocks: int = 0, threads: int = 256, refill_min: int = 8, refill_ballistic: int = 8,
+    def set_launch(self, blocks: int = 0, threads: int = 256, refill_min: int = 4, refill_ballistic: int = 16,
                    defer_min: int = 8):
+        """Launch parameters of the plan; the defaults are those of a plan that is not tuned."""
         check(lib().spx_set_launch(self._h, int(blocks), int(threads), int(refill_min), int(refill_ballistic),
                                    int(defer_min)), "spx_set_launch")
         return self.launch
