@@ -275,7 +275,8 @@ int spx_arrival_edges(double* h_energy_edges, double* h_cos_edges, float* h_ener
 /* Choose launch parameters of the FP32 transport by timing short runs on `stream` (a sample
  * with the plan's mix, its outputs in scratch memory the call allocates and frees): per block
  * size, the ballistic refill threshold by the ballistic kernel's time and the diffusive one by
- * the diffusive kernel's, then the deferral threshold by the diffusive kernel's time.
+ * the diffusive kernel's, then the deferral threshold by the diffusive kernel's time.  Where the plan's runs
+ * take both phases in one kernel, its thresholds by its time; blocks and threads stay as they are.
  * Synchronous; not allowed inside a stream capture (SPX_ESTATE); results are unaffected. */
 int spx_autotune(spx_plan* plan, void* stream);
 

@@ -865,6 +865,9 @@ static int autotune(Plan* P, hipStream_t st)
         if (rc == SPX_OK && hipEventCreate(&e) != hipSuccess) rc = SPX_EDEVICE;
     if (rc == SPX_OK && hipMemcpyAsync(d_tf, tf.data(), sizeof(uint64_t) * (n + 1), hipMemcpyHostToDevice, st) != hipSuccess)
         rc = SPX_EDEVICE;
+    // a plan whose runs take one kernel for both phases (the sample is the whole plan then) tunes that
+    // kernel's thresholds; its geometry is its own
+    const bool whole = tf[n] == P->n_tickets && P->n_tickets <= whole_limit(P, plan_shape(P));
     // One launch shape on the sample, best of two runs for each phase on its own: the ballistic
     // kernel's time depends on the ballistic refill threshold, the diffusive kernel's on the
     // diffusive refill and deferral thresholds, so each threshold is chosen by the time of its
@@ -874,7 +877,7 @@ static int autotune(Plan* P, hipStream_t st)
     };
     auto time_shape = [&](int blocks, int blocks_d, int t, int rmin, int rbal, int defer) -> PhaseMs {
         PhaseMs best;
-        for (int rep = 0; rep < 2 && rc == SPX_OK; ++rep) {
+        for (int rep = 0; rep < (whole ? 4 : 2) && rc == SPX_OK; ++rep) {
             Outputs to;
             to.counts = d_counts;
             to.counters = d_ctr;
@@ -885,7 +888,7 @@ static int autotune(Plan* P, hipStream_t st)
             sh.refill_min = rmin;
             sh.refill_ballistic = rbal;
             sh.defer_min = defer;
-            sh.whole = false;
+            sh.whole = whole;
             QueueMem q;
             q.queue = P->d_queue;
             q.cap = P->queue_cap;
@@ -915,8 +918,27 @@ static int autotune(Plan* P, hipStream_t st)
     const int thread_opts[] = {256, 512, 1024};
     // (refill_min, refill_ballistic): four runs measure four values of each threshold
     const int mode_opts[][2] = {{2, 12}, {4, 16}, {8, 24}, {16, 8}};
+    if (whole) {
+        // both phases' refill thresholds together, then the deferral threshold, by the kernel's time; the
+        // defaults stay unless something is faster by more than the runs differ
+        br = REFILL;
+        bm = REFILL_BALLISTIC;
+        best = time_shape(bb, bd, bt, br, bm, DEFER_MIN).b;
+        const auto consider = [&](int rmin, int rbal, int defer) {
+            if (rc != SPX_OK) return;
+            const float ms = time_shape(bb, bd, bt, rmin, rbal, defer).b;
+            if (rc != SPX_OK || !(ms < 0.98f * best)) return;
+            best = ms;
+            br = rmin;
+            bm = rbal;
+            bdef = defer;
+        };
+        for (const auto& ro : mode_opts)
+            if (ro[0] != REFILL || ro[1] != REFILL_BALLISTIC) consider(ro[0], ro[1], DEFER_MIN);
+        for (int defer : {2 * DEFER_MIN, 4 * DEFER_MIN, DEFER_MIN / 2}) consider(br, bm, defer);
+    }
     for (int t : thread_opts) {
-        if (rc != SPX_OK) break;
+        if (rc != SPX_OK || whole) break;
         int bpc = 0, bpc_d = 0;
         if (occupancy_transport32(P, t, &bpc, &bpc_d) != SPX_OK || bpc < 1 || bpc_d < 1) continue;
         const int blocks = bpc * P->n_cu, blocks_d = std::min(blocks, bpc_d * P->n_cu);
@@ -947,7 +969,7 @@ static int autotune(Plan* P, hipStream_t st)
     // then the deferral threshold for that shape, by the diffusive kernel's time: more held
     // steps per test pass pays off where steps leave their clearance balls often (near
     // surfaces, absorbing objects)
-    for (int defer = 2 * DEFER_MIN; defer <= 4 * DEFER_MIN && rc == SPX_OK; defer *= 2) {
+    for (int defer = 2 * DEFER_MIN; !whole && defer <= 4 * DEFER_MIN && rc == SPX_OK; defer *= 2) {
         const PhaseMs ms = time_shape(bb, bd, bt, br, bm, defer);
         if (rc != SPX_OK || !(ms.d < best_d)) break;     // doubling again only while it helps
         best_d = ms.d;
@@ -955,7 +977,7 @@ static int autotune(Plan* P, hipStream_t st)
     }
     // where doubling did not help, half of it: fewer held steps per test pass pays off where
     // walks are short and a held lane would otherwise idle longer
-    if (rc == SPX_OK && bdef == DEFER_MIN) {
+    if (rc == SPX_OK && !whole && bdef == DEFER_MIN) {
         const PhaseMs ms = time_shape(bb, bd, bt, br, bm, DEFER_MIN / 2);
         if (rc == SPX_OK && ms.d < best_d) bdef = DEFER_MIN / 2;
     }

@@ -291,7 +291,8 @@ template <typename R>
 int build_transport(Plan* P, uint64_t seed, const Outputs& o, const uint64_t* tfirst, uint64_t total,
                     const Shape& sh, const QueueMem& q, LaunchSink& sink);
 // A sink that launches on `st`; with `events` (3 per round, not while capturing) it records one
-// before each ballistic kernel, one after it and one after the diffusive kernel.
+// before each ballistic kernel, one after it and one after the diffusive kernel (a kernel for both
+// phases: one before it and both others after it).
 struct StreamSink : LaunchSink {
     hipStream_t st;
     const hipEvent_t* events;

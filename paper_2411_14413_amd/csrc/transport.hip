@@ -956,12 +956,12 @@ int StreamSink::put(const KLaunch& k)
         set_error("internal: malformed kernel launch");
         return SPX_ESTATE;
     }
-    if (events && k.phase == 1) SPX_HIP(hipEventRecord(events[3 * round], st));
+    if (events && (k.phase & 1)) SPX_HIP(hipEventRecord(events[3 * round], st));
     void* args[8];
     k.pointers(args);
     SPX_HIP(hipLaunchKernel(k.func, k.grid, k.block, args, k.smem, st));
-    if (events && k.phase == 1) SPX_HIP(hipEventRecord(events[3 * round + 1], st));
-    if (events && k.phase == 2) SPX_HIP(hipEventRecord(events[3 * round++ + 2], st));
+    if (events && (k.phase & 1)) SPX_HIP(hipEventRecord(events[3 * round + 1], st));
+    if (events && (k.phase & 2)) SPX_HIP(hipEventRecord(events[3 * round++ + 2], st));
     return SPX_OK;
 }
 
