@@ -1,5 +1,5 @@
 #!/usr/bin/env python3
-"""Benchmark: batched FP32 transport vs the plain FP64 per-segment comparator.
+"""Benchmark: batched FP32 transport vs a plain FP64 comparator.
 
 Workload (default): the single planar Ni target of the paper's Methods geometry
 stand-in, three chambers in one batch -- Ar at 0.5 Pa, 0 Pa (line of sight) and
@@ -9,8 +9,10 @@ zero tallies, the transport kernels over all three chambers, and the
 FP64 normalisation of the tallies to deposition profiles.  Inputs are synthetic
 (seeded geometry and gas; every random number is generated on the GPU).
 
-Prints ONE JSON line.  `value` is particles/s of the FP32 path; the FP64 plain
-comparator, collisions/s, the matched tally error, the ALU roofline of the
+Prints ONE JSON line.  `value` is particles/s of the FP32 path; the plain FP64
+comparator (`fp64_plain`: a thread per atom, every diffusive step tested, as a replayed graph runs
+it), the FP64 path of a run outside a graph (`fp64_phases`: the phases, queue and walks of the FP32
+path in double), collisions/s, the matched tally error, the ALU roofline of the
 transport kernel and the FP64 CPU oracle timed on this host are reported beside it.
 """
 import argparse
@@ -189,6 +191,31 @@ def time_steps(plan, bufs, seed, steps, warmup, phase_times=True, post=None):
     wall = time.perf_counter() - t0
     ms = [a.elapsed_time(b) for a, b in ev]
     return wall, ms, phases
+
+
+class CapturedRun:
+    """One run of a plan in a graph: an FP64 plan's captured run takes a thread per atom."""
+
+    def __init__(self, plan, bufs, seed):
+        import torch
+        self.graph = torch.cuda.CUDAGraph()
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.graph(self.graph, stream=s):
+            plan.run_into(seed, bufs, stream=s)
+
+    def run_into(self, seed, bufs):
+        self.graph.replay()
+
+
+def fp64_leg(run, plan, bufs, seed):
+    """Rates of two FP64 steps of `run`, and its tallies per segment."""
+    import numpy as np
+    wall, _, _ = time_steps(run, bufs, seed, 2, 1, phase_times=False)
+    c = bufs["counters"].view(plan.n_segments, -1).cpu().numpy().astype(np.float64)
+    leg = {"value": float(c[:, 0].sum()) / (wall / 2), "unit": "particles/s", "ms_per_step": wall * 1e3 / 2,
+           "collisions_per_s": float(c[:, 4].sum() + c[:, 5].sum()) / (wall / 2)}
+    return leg, [bufs["counts"][o:o + nv * nu].cpu().numpy() for o, (nv, nu) in zip(plan.bin_off, plan.shapes)]
 
 
 def cpu_model():
@@ -408,18 +435,16 @@ def main():
     if not args.no_fp64:
         plan64 = spx.Plan(cfgs, params, precision=64)
         bufs64 = plan64.allocate(profiles=True)
-        wall64, ms64, _ = time_steps(plan64, bufs64, args.seed, 2, 1, phase_times=False)
-        c64 = bufs64["counters"].view(plan.n_segments, spx._native.N_COUNTERS).cpu().numpy().astype(np.float64)
-        counts64 = [bufs64["counts"][o:o + nv * nu].cpu().numpy() for o, (nv, nu) in zip(plan64.bin_off, plan64.shapes)]
+        plain64 = CapturedRun(plan64, bufs64, args.seed)
+        result["fp64_plain"], counts64 = fp64_leg(plain64, plan64, bufs64, args.seed)
+        result["speedup_vs_fp64_plain"] = value / result["fp64_plain"]["value"]
+        result["fp64_phases"], same64 = fp64_leg(plan64, plan64, bufs64, args.seed)
+        result["fp64_phases"]["counts_equal_plain"] = all(np.array_equal(a, b) for a, b in zip(counts64, same64))
         eps64 = tally_error(counts64)
-        v64 = float(c64[:, 0].sum()) / (wall64 / 2)
-        result["fp64_plain"] = {"value": v64, "unit": "particles/s", "ms_per_step": wall64 * 1e3 / 2,
-                                "collisions_per_s": float(c64[:, 4].sum() + c64[:, 5].sum()) / (wall64 / 2)}
-        result["speedup_vs_fp64_plain"] = value / v64
         result["tally_error"] = {"fp32_batched": eps32, "fp64_plain": eps64,
                                  "max_rel_diff": max(abs(a / b - 1) for a, b in zip(eps32, eps64)),
                                  "definition": "median over non-empty bins of 1/sqrt(count), per chamber/cathode"}
-        del plan64, bufs64
+        del plain64, plan64, bufs64
     else:
         result["tally_error"] = {"fp32_batched": eps32}
 
