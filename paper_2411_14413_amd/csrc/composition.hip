@@ -467,7 +467,7 @@ __global__ void __launch_bounds__(1024) k_comp_bw_sum(const float* __restrict__ 
     }
 }
 
-// Blocks of the one-pass backward: about four rows a wave until every CU holds its blocks.
+// Blocks of the one-pass backward: a row a wave (J > 384: a block), then more of them each above BW_BLOCKS blocks.
 static int bw_blocks(int B, int J)
 {
     const int rpb = J <= 64 * BW_JM ? 4 : 1;

@@ -446,7 +446,7 @@ extern "C" int spx_hull_area(const float* d_c, int32_t B, int32_t J, float* d_ar
     }
     int n = 1;
     while (n < J) n <<= 1;
-    const size_t smem = sizeof(double) * 2 * (size_t)(n + J);       // at most 64 KB
+    const size_t smem = sizeof(double) * 2 * (size_t)(n + J);       // at most 64 KB, besides 0.2 KB of the kernel's own
     for (int64_t b0 = 0; b0 < B; b0 += GRID_MAX) {
         hipLaunchKernelGGL(k_hull_area<256>, dim3((unsigned)std::min<int64_t>(B - b0, GRID_MAX)), dim3(256), smem,
                            (hipStream_t)stream, d_c + 3 * b0 * J, J, d_area + b0);

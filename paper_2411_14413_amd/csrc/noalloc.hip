@@ -6,8 +6,8 @@
 // entry point keeps them in `scratch`, a static device array of this file, and enqueues the
 // kernels directly on the caller's stream (no graph to instantiate), so it can be called
 // where hipMalloc cannot: inside a stream capture, in a serving loop, in a harness that
-// forbids allocation.  A larger plan runs in more rounds of the queue; the tallies, counters
-// and records do not depend on the rounds.
+// forbids allocation.  A larger plan runs in passes of its waves over their queue slots, or in more
+// rounds of the queue; the tallies, counters and records do not depend on them.
 #include <hip/hip_runtime.h>
 
 #include <mutex>

@@ -401,12 +401,13 @@ __device__ __forceinline__ void escape_capped(const TransportArgs<R>& a, const B
     }
 }
 
-// The held steps of the wave (mask H != 0), tested together: with the geometry read once for
-// the wave when they share a segment (the common case), else each lane reading its own.
+// The held steps of the wave, tested together, each lane with its own segment's geometry.  (A second copy of the
+// test, for lanes of one segment with the geometry in scalar registers, was slower: half the 64-chamber
+// sweep 93.5 ms with it, 92.2 without.)
 template <bool ARR, bool OBJ, typename R>
 __device__ __forceinline__ void resolve_held(const TransportArgs<R>& a, const BlockTally& bt,
                                              const SegDev<R>* __restrict__ segs, int seg, uint32_t pid,
-                                             Particle<R>& p, Walk<R>& wk, LaneAcc<true>& acc, bool held, uint64_t H)
+                                             Particle<R>& p, Walk<R>& wk, LaneAcc<true>& acc, bool held)
 {
     if (std::is_same<R, float>::value) acc.c[C_TESTED] += held ? 1u : 0u;
     if (held) {
@@ -446,8 +447,7 @@ __device__ __forceinline__ void diffusive_loop(const TransportArgs<R>& a, const 
             escape_capped<ARR>(a, bt, segs, seg, pid, p, acc, walks && p.e >= a.cap);
             if (p.st == ST_DIFFUSIVE) held = diffusive_single(lam_l2, cfgcat, a.k0, a.k1, pid, p, wk);
         }
-        const uint64_t H = __ballot(held);
-        if (H != 0) resolve_held<ARR, OBJ>(a, bt, segs, seg, pid, p, wk, acc, held, H);
+        if (__ballot(held) != 0) resolve_held<ARR, OBJ>(a, bt, segs, seg, pid, p, wk, acc, held);
         M = __ballot(p.st == ST_DIFFUSIVE);
         if (M == 0 || (!drained && __popcll(__ballot(p.st == ST_DEAD)) >= a.refill_min) ||
             (drained && __popcll(M) <= Walk<R>::COOP))
@@ -572,8 +572,8 @@ k_ballistic64(TransportArgs<double> a, const SegDev<double>* __restrict__ segs)
 }
 
 // The last walks of a drained wave (its lanes in D, at most Walk<R>::COOP, none with a held step), walked
-// to their ends by the whole wave: each walker gets a span of 64, 32, 16, 8 or 4 lanes, all of which hold
-// its state, and lane j of the span draws step e + 1 + j.  A pass takes every walker's steps up to the
+// to their ends by the whole wave: each walker gets a span of 64, 32, 16, 8, 4 or (FP64) 2 lanes, all of which
+// hold its state, and lane j of the span draws step e + 1 + j.  A pass takes every walker's steps up to the
 // first that leaves its ball (or to the event cap), then tests those.  Spans are laid out anew as
 // walkers end.  Bound by the latency of one pass, the longest walks being all that is left: the state
 // stays replicated in the span, so a pass starts without shuffles, and the surfaces are read once per
@@ -785,13 +785,14 @@ __device__ __forceinline__ void whole_kernel(TransportArgs<R>& a, const SegDev<R
     Tickets T;
     T.tk = wave * a.chunk_ballistic < total ? wave * a.chunk_ballistic : total;
     T.tk_end = total - T.tk > a.chunk_ballistic ? T.tk + a.chunk_ballistic : total;
+    constexpr bool TIMED = std::is_same<R, float>::value;   // (there are no phase times of FP64 runs)
     uint64_t times[2] = {0, 0};
-    if (a.times && threadIdx.x == 0 && blockIdx.x == 0) a.times[2] = wall_clock64();
+    if (TIMED && a.times && threadIdx.x == 0 && blockIdx.x == 0) a.times[2] = wall_clock64();
     for (;;) {
         T.drained = T.tk == T.tk_end;
-        const uint64_t t0 = wall_clock64();
+        const uint64_t t0 = TIMED ? wall_clock64() : 0;
         const QRun e = ballistic_phase<ARR, OBJ, true, LIMITED>(a, bt, segs, T, QRun{slot, slot + a.wave_slots}, lane);
-        const uint64_t t1 = wall_clock64();
+        const uint64_t t1 = TIMED ? wall_clock64() : 0;
         // publish the wave's records to the block: all lanes' stores, then next, then end
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_wave_barrier();
@@ -804,17 +805,17 @@ __device__ __forceinline__ void whole_kernel(TransportArgs<R>& a, const SegDev<R
         diffusive_phase<ARR, OBJ, true>(a, bt, segs, BlockQueue{next, end, own, LIMITED ? 1u : blockDim.x / 64}, 0u, 0u,
                                         lane);
         times[0] += t1 - t0;
-        times[1] += wall_clock64() - t1;
+        times[1] += (TIMED ? wall_clock64() : 0) - t1;
         if (!LIMITED) break;
         T.tk = (uint32_t)e.q_end;
         if (T.tk == T.tk_end) break;
     }
-    if (a.times && threadIdx.x == 0 && blockIdx.x % 8 == 0) {
+    if (TIMED && a.times && threadIdx.x == 0 && blockIdx.x % 8 == 0) {
         atomicAdd((unsigned long long*)&a.times[0], (unsigned long long)times[0]);
         atomicAdd((unsigned long long*)&a.times[1], (unsigned long long)times[1]);
     }
     lds_flush(a, bt);
-    if (a.times && threadIdx.x == 0) atomicMax((unsigned long long*)&a.times[3], (unsigned long long)wall_clock64());
+    if (TIMED && a.times && threadIdx.x == 0) atomicMax((unsigned long long*)&a.times[3], (unsigned long long)wall_clock64());
 }
 
 // Four waves per SIMD (FP64: three) fit without spills in the steps.
