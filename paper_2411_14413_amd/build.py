@@ -13,8 +13,8 @@ SOURCES = ["api.hip", "transport.hip", "table_build.hip", "composition.hip", "in
 ARCH = "gfx950"
 # Machine-level loop-invariant code motion keeps the polynomials' constants of the FP64 library functions
 # and the segments' constants in vector registers across the transport loops and spills them: the FP64
-# ballistic kernel took 256 VGPRs and 346 spills (129 and none without), the FP64 walk 23 spills
-# at 168 VGPRs (none), the FP32 walk 47 (10).
+# ballistic kernel took 256 VGPRs and 346 spills (121 and none without), the FP64 walk 23 spills
+# at 168 VGPRs (139 and none), the FP32 walk 47 (14, in its instances 8 to 25).
 SOURCE_FLAGS = {"transport.hip": ["-mllvm", "-disable-machine-licm"]}
 
 FLAGS = [

@@ -1058,7 +1058,12 @@ static int blocks_of(uint64_t total, int blocks, int threads, int n_simd)
 // at 0.5 Pa, 1e5 atoms (1.5 tickets per lane of one wave per SIMD) 0.372 / 0.288, 0.300, 0.324; 1e6 (15)
 // 0.80 / 0.68, 0.62, 0.64; 5e6 (76) 1.96 / 2.40, 1.92, 1.74; 1e7 3.29 / 4.55, 3.56, 3.15; four cathodes, 7e6
 // 2.38 / 2.97, 2.35, 2.31, 2.3e7 5.95 / 9.2, 7.1, 6.6.  Chambers of 0.1 to 2 Pa: 3e5 atoms 2.96 / 2.32, 2.23,
-// 2.24; 1e6 3.59 / 4.03, 3.73, 3.47; 2e6 4.80 / 6.32, 5.40, 5.08.  FP64 (three waves at most): four
+// 2.24; 1e6 3.59 / 4.03, 3.73, 3.47; 2e6 4.80 / 6.32, 5.40, 5.08.  One chamber at 2 Pa, two / one as the rule has its
+// waves: 1e6 5.63 / 5.32, 3e6 12.1 / 11.7, 5e6 17.83 / 17.86.  The pressures count by their extremes alone, and
+// the line at a ratio of two is on the safe side for those between: eight chambers from 0.5 Pa up, 2e6 and 5e6
+// atoms, to 1.5 times 1.61 / 1.21 and 2.95 / 2.46, to 2.2 times 2.24 / 2.04 and 4.15 / 3.96, to 3 times 3.15 /
+// 3.00 and 5.74 / 5.73, to 5 times 6.23 / 6.13 and 10.6 / 11.2; 64 chambers of 0.1 to 2 Pa 4.42 / 4.53 and 6.37 /
+// 7.66; ten atoms at 0.1 Pa beside 3e6 at 0.5 1.42 / 1.15.  FP64 (three waves at most): four
 // cathodes, 2e5 1.21 / 0.96, 0.88; 5e5 1.78 / 1.36, 1.46; 3e6 4.52 / -, 4.32; single target, 1e6 2.28 / 1.93,
 // 2.09; 2e6 3.49 / -, 3.42; 3e6 4.40 / -, 4.81.
 uint64_t whole_limit(const Plan* P, const Shape& sh)
