@@ -356,14 +356,15 @@ __global__ void __launch_bounds__(256) k_comp_bw(const float* __restrict__ f, co
 #pragma unroll
                     for (int k = 0; k < K; ++k) g[k] = gb[(size_t)j * K + k];
                 }
-                float S = 0.f, gy = 0.f;
+                float y[K], S = 0.f, dotgc = 0.f;
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
-                    const float y = w[k] * fr[m][k];
-                    S += y;
-                    gy += g[k] * y;
+                    y[k] = w[k] * fr[m][k];
+                    S += y[k];
                 }
-                const float dotgc = 100.f * gy / S;
+                const float inv = 100.f / S;        // g times a composition: no product beyond the range of its factors
+#pragma unroll
+                for (int k = 0; k < K; ++k) dotgc += g[k] * (y[k] * inv);
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     const float gyk = (100.f * g[k] - dotgc) / S;
