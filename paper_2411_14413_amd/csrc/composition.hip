@@ -485,7 +485,7 @@ __global__ void __launch_bounds__(256) k_area_gather(const double* __restrict__ 
                                                      double half_u, double half_v, const double* __restrict__ cen,
                                                      int n_areas, double hw, double* __restrict__ out)
 {
-    const int g = threadIdx.x & (G - 1);
+    const uint32_t g = threadIdx.x & (G - 1);
     const double du = 2.0 * half_u / nu, dv = 2.0 * half_v / nv;
     for (int64_t idx = (int64_t)blockIdx.x * (256 / G) + threadIdx.x / G; idx < n; idx += (int64_t)gridDim.x * (256 / G)) {
         const int64_t p = idx / n_areas;
@@ -499,10 +499,11 @@ __global__ void __launch_bounds__(256) k_area_gather(const double* __restrict__ 
         iv1 = iv1 > nv - 1 ? nv - 1 : iv1;
         const double* pr = prof + (size_t)p * nu * nv;
         double sw = 0.0, s = 0.0;
-        if (iu0 <= iu1) {
-            const int w = iu1 - iu0 + 1, dr = G / w, dc = G - dr * w;
-            int iv = iv0 + g / w, iu = iu0 + g % w;
-            while (iv <= iv1) {
+        // (a square beyond the grid, however far, has its first row past the last; unsigned: no sum below wraps)
+        if (iu0 <= iu1 && iv0 <= iv1) {
+            const uint32_t w = (uint32_t)(iu1 - iu0) + 1, dr = G / w, dc = G - dr * w;
+            uint32_t iv = (uint32_t)iv0 + g / w, iu = (uint32_t)iu0 + g % w;
+            while (iv <= (uint32_t)iv1) {
                 const double v0 = -half_v + iv * dv, u0 = -half_u + iu * du;
                 const double ov = fmin(v0 + dv, cv + hw) - fmax(v0, cv - hw);
                 const double ou = fmin(u0 + du, cu + hw) - fmax(u0, cu - hw);
@@ -513,7 +514,7 @@ __global__ void __launch_bounds__(256) k_area_gather(const double* __restrict__ 
                 }
                 iv += dr;
                 iu += dc;
-                if (iu > iu1) {
+                if (iu > (uint32_t)iu1) {
                     iu -= w;
                     ++iv;
                 }
