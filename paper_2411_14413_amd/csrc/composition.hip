@@ -60,9 +60,10 @@ __global__ void __launch_bounds__(256) k_comp_forward(const float* __restrict__ 
     for (int i = threadIdx.x; i < n_rows * K; i += 256) w[i] = weight(a, bb, P, M, rho, fref, b0 + i / K, i % K, K);
     __syncthreads();
     float* cb = c + (size_t)b0 * J * K;
-    const int dr = 256 / J, dj = 256 - dr * J;
+    const uint32_t dr = 256 / J, dj = 256 - dr * J;     // (unsigned: j + dj may pass 2^31)
     const int64_t first = blockIdx.y * span, total = (int64_t)n_rows * J, end = first + span < total ? first + span : total;
-    int r = (int)((first + threadIdx.x) / J), j = (int)(first + threadIdx.x - (int64_t)r * J);
+    int r = (int)((first + threadIdx.x) / J);
+    uint32_t j = (uint32_t)(first + threadIdx.x - (int64_t)r * J);
     for (int64_t i0 = first; i0 < end; i0 += 256) {
         if (VEC) {
             if (r < n_rows) {
@@ -108,7 +109,7 @@ __global__ void __launch_bounds__(256) k_comp_forward(const float* __restrict__ 
         }
         r += dr;
         j += dj;
-        if (j >= J) {
+        if (j >= (uint32_t)J) {
             j -= J;
             ++r;
         }

@@ -67,3 +67,12 @@ def test_sweep_composition():
     say(f"{T} sweep points of one area and one element")
     one = [torch.ones(1, dtype=torch.float64, device="cuda") for _ in range(5)]
     assert (spx.sweep_composition(torch.full((T, 1, 1), 0.5, dtype=torch.float64, device="cuda"), *one) == 100.0).all()
+
+
+def test_composition_of_the_most_areas():
+    J = 2**31 - 1
+    say(f"one row of {J} areas")
+    xs = _comp_inputs(1, 1, 1)
+    xs[0] = torch.full((1, J), 0.25, device="cuda")
+    c = spx.comp_forward(*xs)
+    assert float((c - 100.0).abs_().max()) < 2e-4
