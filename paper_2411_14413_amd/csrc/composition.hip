@@ -363,9 +363,10 @@ __global__ void __launch_bounds__(256) k_comp_bw(const float* __restrict__ f, co
                     y[k] = w[k] * fr[m][k];
                     S += y[k];
                 }
-                const float inv = 100.f / S;        // g times a composition: no product beyond the range of its factors
+                const float inv = 1.f / S;          // g times a fraction: no product beyond the range of its factors
 #pragma unroll
                 for (int k = 0; k < K; ++k) dotgc += g[k] * (y[k] * inv);
+                dotgc *= 100.f;
 #pragma unroll
                 for (int k = 0; k < K; ++k) {
                     const float gyk = (100.f * g[k] - dotgc) / S;

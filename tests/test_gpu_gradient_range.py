@@ -12,7 +12,7 @@ if not torch.cuda.is_available():
 import paper_2411_14413_amd as spx  # noqa: E402
 
 
-@pytest.mark.parametrize("rate, grad", [(1.0, 1.0), (1e-20, 1e-20), (1e-25, 1e-10), (1e18, 1e22), (1e-12, 1e-30)])
+@pytest.mark.parametrize("rate, grad", [(1.0, 1.0), (1e-20, 1e-20), (1e-25, 1e-10), (1e18, 1e22), (1e-12, 1e-30), (3e-38, 1e-10)])
 @pytest.mark.parametrize("J, K", [(342, 4), (400, 3), (50, 8), (1600, 2)])
 def test_backward(J, K, rate, grad):
     g = torch.Generator(device="cuda").manual_seed(J)
