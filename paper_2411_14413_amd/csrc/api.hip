@@ -611,14 +611,22 @@ static int create(const spx_config* cfgs, int n_cfgs, const spx_params* prm, Pla
     std::vector<uint64_t> tfirst(n + 1, 0);
     for (int o = 0; o < n; ++o) tfirst[o + 1] = tfirst[o] + P->seg[order[o]].N;
     P->n_tickets = tfirst[n];
-    // thermalisation queue of one round: an atom per ticket of a round (FP32 48 B, FP64 80 B), plus the
-    // slots a resident wave may leave unused
+    if (prm->precision == 64 && shape_transport64(P) != SPX_OK) {
+        release(P);
+        return SPX_EDEVICE;
+    }
+    // thermalisation queue of one round: an atom per ticket of a round (FP32 48 B, FP64 80 B), plus the slots
+    // a wave may leave unused: of the resident waves (FP32, whose launch shape may change), of the launch's
+    // (FP64; of a round in one kernel one a wave, where the waves' shares are rounded up)
     const size_t rec = prm->precision == 32 ? sizeof(ThermRec<float>) : sizeof(ThermRec<double>);
     const uint64_t waves = std::max<uint64_t>(QUEUE_SLACK_WAVES, (uint64_t)P->n_cu * 32);
     P->round_max = prm->precision == 32 ? ROUND_MAX : ROUND_MAX64;
     for (;;) {
-        const uint64_t r = rounds_of(P->n_tickets, P->round_max);
-        P->queue_cap = (r ? (P->n_tickets + r - 1) / r : 0) + waves * QUEUE_CHUNK;
+        const uint64_t r = rounds_of(P->n_tickets, P->round_max), per_round = r ? (P->n_tickets + r - 1) / r : 0;
+        const Shape& sh = P->shape64;
+        P->queue_cap = per_round + (prm->precision == 32                      ? waves * QUEUE_CHUNK
+                                    : per_round <= whole_limit(P, sh) ? 16 * (uint64_t)P->n_cu
+                                                                      : (uint64_t)sh.blocks * (sh.threads / 64) * QUEUE_CHUNK);
         if (dalloc(&P->d_queue, P->queue_cap * rec) == SPX_OK) break;
         (void)hipGetLastError();
         if (prm->precision == 32) {
@@ -655,10 +663,6 @@ static int create(const spx_config* cfgs, int n_cfgs, const spx_params* prm, Pla
     P->max_blocks_per_cu = bpc;
     P->blocks = bpc * P->n_cu;
     P->blocks_diff = std::min(P->blocks, bpc_d * P->n_cu);
-    if (prm->precision == 64 && shape_transport64(P) != SPX_OK) {
-        release(P);
-        return SPX_EDEVICE;
-    }
     *out = P;
     return SPX_OK;
 }
