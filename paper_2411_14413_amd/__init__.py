@@ -465,7 +465,9 @@ def invert_sweep(plan, out, x, comp, measured, centres=None, half_width: float =
     # a row more than the sweep: the measured library, so that one launch finds every covered area
     libs = torch.empty(T + 1, J, K, dtype=torch.float32, device=f.device)
     c = _sweep_composition(f, *comp, stream=stream, out=libs[:T])
-    meas = _f32(measured).detach().reshape(1, J, K)     # (copied below: its gradient stays out of the outputs)
+    meas = _f32(measured).reshape(1, J, K)
+    if meas.requires_grad:
+        meas = meas.detach()                   # copied below: its gradient stays out of the outputs
     loss = comp_sqdist(c, meas, stream=stream)
     res = dict(f=f, c=c, loss=loss, x_min_de=sweep_fit(x, loss, FIT_MIN, stream=stream))
     if K == 3:

@@ -45,6 +45,8 @@ constexpr int FWD_ROWS = 64;        // rows a block at most
 // blocks [us]: 1 x 1e6 x 4 1586, 8.9, 8.9, 8.7; 300 x 40000 x 4 76, 43, 34, 32; 2000 x 40000 x 3 391, 387, 239, 250;
 // 64 x 40000 x 9 472, 67, 38, 36.
 constexpr int64_t FWD_BLOCKS = 4096;
+// ... of four times 256 (b, j) at least: for fewer the weights cost more (1024 x 342 x 4 5.2 us unsplit, 5.9 in thirds).
+constexpr int64_t FWD_TILES = 4;
 template <int KT, bool VEC>
 __global__ void __launch_bounds__(256) k_comp_forward(const float* __restrict__ f, const float* __restrict__ a,
                                                       const float* __restrict__ bb, const float* __restrict__ P,
@@ -62,7 +64,7 @@ __global__ void __launch_bounds__(256) k_comp_forward(const float* __restrict__ 
     float* cb = c + (size_t)b0 * J * K;
     const uint32_t dr = 256 / J, dj = 256 - dr * J;     // (unsigned: j + dj may pass 2^31)
     const int64_t first = blockIdx.y * span, total = (int64_t)n_rows * J, end = first + span < total ? first + span : total;
-    int r = (int)((first + threadIdx.x) / J);
+    int r = first == 0 ? (int)threadIdx.x / J : (int)((first + threadIdx.x) / J);
     uint32_t j = (uint32_t)(first + threadIdx.x - (int64_t)r * J);
     for (int64_t i0 = first; i0 < end; i0 += 256) {
         if (VEC) {
@@ -560,7 +562,8 @@ extern "C" int spx_comp_forward(const float* d_f, const float* d_a, const float*
     for (int64_t b0 = 0; b0 < B; b0 += GRID_MAX * rows) {
         const int n = (int)std::min<int64_t>(B - b0, GRID_MAX * rows);
         const int64_t groups = (n + rows - 1) / rows, tiles = ((int64_t)rows * J + 255) / 256;
-        const int64_t parts = std::min(tiles, (FWD_BLOCKS + groups - 1) / groups), span = (tiles + parts - 1) / parts * 256;
+        const int64_t parts = std::min((tiles + FWD_TILES - 1) / FWD_TILES, (FWD_BLOCKS + groups - 1) / groups);
+        const int64_t span = (tiles + parts - 1) / parts * 256;
         hipLaunchKernelGGL(kern, dim3((unsigned)groups, (unsigned)parts), dim3(256), 0, (hipStream_t)stream, d_f, d_a,
                            d_b, d_P + b0 * K, d_M, d_rho, d_fref, d_c + b0 * J * K, n, J, K, rows, span);
         SPX_HIP(hipGetLastError());

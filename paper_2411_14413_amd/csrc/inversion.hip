@@ -170,7 +170,7 @@ __global__ __launch_bounds__(THREADS) void k_hull_area(const float* __restrict__
     extern __shared__ double pts[];                     // x, y sorted; x, y for the upper chain
     __shared__ int len[2];
     __shared__ float vx[HULL_DIRS], vy[HULL_DIRS];      // the extreme points
-    __shared__ int vi[HULL_DIRS], kept;
+    __shared__ int vi[HULL_DIRS], kept, far;            // far: an extreme point lies beyond the filter's reach
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     if (J < 3) {
         if (tid == 0) area[b] = 0.f;
@@ -186,7 +186,10 @@ __global__ __launch_bounds__(THREADS) void k_hull_area(const float* __restrict__
         qx[j] = c1 + 0.5 * c2;
         qy[j] = c2 * (SQRT3 / 2.0);
     }
-    if (tid == 0) kept = 0;
+    if (tid == 0) {
+        kept = 0;
+        far = 0;
+    }
     __syncthreads();
     if (filter) {
         // four directions a wave: the lanes' extremes of their points, then those of the lanes
@@ -222,10 +225,10 @@ __global__ __launch_bounds__(THREADS) void k_hull_area(const float* __restrict__
                 vi[d0 + d] = at[d];
                 vx[d0 + d] = (float)qx[at[d]];
                 vy[d0 + d] = (float)qy[at[d]];
+                if (!(fabsf(vx[d0 + d]) <= HULL_FILTER_REACH && fabsf(vy[d0 + d]) <= HULL_FILTER_REACH)) far = 1;
             }
         __syncthreads();
-        bool near = true;
-        for (int d = 0; d < HULL_DIRS; ++d) near = near && fabsf(vx[d]) <= HULL_FILTER_REACH && fabsf(vy[d]) <= HULL_FILTER_REACH;
+        const bool near = far == 0;
         for (int j0 = 0; j0 < J; j0 += THREADS) {
             const int j = j0 + tid;
             bool keep = j < J;
